@@ -13,16 +13,17 @@ constexpr int kThreads = 256;   // 4 wave64 per block
 constexpr int kTileX = 64;      // contiguous axis: one wave64 spans a tile row
 constexpr int kSincHalfWidth = 4;   // windowed-sinc taps: 2 r nodes per axis
 
-// Launch shapes of the step kernels: rows per thread x wave64s per block (the
-// tile is 64 x rows * waves) and, in 3D, planes per block.  The fastest
-// measured on 1104^2 and 316^3.  The 3D adjoint shape also serves every step
-// with two stencil fields (adjoint, fourth-order adjoint correction, medium);
-// the adjoint steps that image from a stored v (one stencil field) take a
-// taller tile of their own, with the adjoint's chunk length.
+// Launch shapes of the step kernels.  2D: rows per thread x wave64s per block
+// (the tile is 64 x rows * waves), the fastest measured on 1104^2.  3D: points
+// of a row per thread x wave64s per block (64 x points * waves); kernels with
+// one stencil field take four points, those with two (adjoint with the fused
+// imaging, fourth-order adjoint correction, y = 2 medium) two.
 constexpr int kRy2d = 4, kWaves2d = 4;
-constexpr int kRy3dFwd = 4, kWaves3dFwd = 8, kZc3dFwd = 32;
-constexpr int kRy3dAdj = 2, kWaves3dAdj = 4, kZc3dAdj = 16;
-constexpr int kRy3dAdjV = 4, kWaves3dAdjV = 4;
+constexpr int kVx3dOne = 4, kVx3dTwo = 2, kWaves3d = 4;
+// Planes of a 3D block (chunk_planes in stride_api.cpp).
+constexpr int kZc3dMin = 4, kZc3dOne = 8, kZc3dTwo = 16;
+// Infinity Cache of the part, in bytes.
+constexpr long long kCacheBytes = 256ll << 20;
 constexpr int kPitchAlign = 16;     // row pitch of the fields, in floats (64 B)
 
 // Padded grid as laid out in the workspace.  Axis nd-1 is contiguous.
@@ -106,10 +107,9 @@ struct StepParams {
     int img_stride;
     SampleSet smp;    // sampling of A at `step`
     // medium steps only: gamma_a = -D_a ln rho per axis, and the attenuation
-    // field (att_power 0: 2 alpha0 vp added to the damping; 2: beta = 2 alpha0 vp / dt)
+    // field (kMediumY0: 2 alpha0 vp added to the damping; kMedium: beta = 2 alpha0 vp / dt)
     const float* gam[3];
     const float* att;
-    int att_power;
     float* V;         // kStepV: L u^n + S^n out; kImageV: that of u^m in
     const float* V2;  // kImageV: that of u^{m+1} (NULL: one imaging term per step)
 };
@@ -122,19 +122,19 @@ struct SlotStep {
 };
 
 struct LaunchShape {
-    int ty;               // tile rows (waves x rows per thread)
-    int ry, waves;        // rows per thread, wave64s per block
+    int ty;               // tile rows
+    int ry, waves;        // 2D: rows per thread; wave64s per block
     int tiles_x, tiles_y, tiles_xy;
     int zc, nzc;          // 3D: planes per block and number of z chunks
     int tile_blocks;      // logical tile blocks (before XCD padding)
     int tile_blocks_pad;  // rounded up to a multiple of 8 XCDs
 };
 
-// Rows per thread and waves per block of the step kernels for a dimension
-// and direction (the tile is 64 x ry*waves).
-void tile_shape(int nd, bool adjoint, int* ry, int* waves);
-// Shape of the adjoint steps imaging from a stored v (kImageV, kAdjPlain).
-void tile_shape_v(int nd, int* ry, int* waves);
+// Rows per thread and waves per block of the 2D step kernels for a direction
+// (the tile is 64 x ry*waves).
+void tile_shape_2d(bool adjoint, int* ry, int* waves);
+// Whether a 3D step loads its point values with the non-temporal policy.
+bool stream_3d(const Dims& d, bool adjoint, int mode);
 
 // What a step launch computes.  Fourth-order time runs two launches per
 // forward step and three per adjoint step (kPrep on u^m and on w^{m+1}, then
@@ -145,15 +145,15 @@ enum StepMode {
     kCorrect = 2, // C = a (2 D + A + (k/12) L A) - b B, A = p, D = u^n;
                   // adjoint: C = a (2 D + A + (k/12) L A + k R^T g) - b B with A = q,
                   // D = w^{m+1}, and G += U (D + A/12) + (k/12) D L U with U = p
-    kMedium = 3,  // forward step in a heterogeneous medium, B a stencil field too:
-                  // C = a (2 A + k (L A + sum_a gam_a D_a A + S [+ att (L A - L B)])) - b B,
-                  // with att added to the damping instead when att_power is 0; with V
-                  // given it also stores the imaging factor of the vp gradient there
+    kMedium = 3,  // forward step in a heterogeneous medium (y = 2), B a stencil field too:
+                  // C = a (2 A + k (L A + sum_a gam_a D_a A + S + att (L A - L B))) - b B;
+                  // with V given it also stores the imaging factor of the vp gradient there
     kStepV = 4,   // forward kStep that also stores V = L A + S (full-history gradients)
     kImageV = 5,  // adjoint kStep whose imaging reads V = L u^m + S^m instead of the
                   // stencil of u^m: G += A V, and with V2 the previous step's term as
                   // well, G = fma(A, V, fma(B, V2, G)) (B = w^{m+2})
-    kAdjPlain = 6 // adjoint kStep without imaging (the step before a kImageV with V2)
+    kAdjPlain = 6,// adjoint kStep without imaging (the step before a kImageV with V2)
+    kMediumY0 = 7 // kMedium with att added to the damping (y = 0): B is a point value
 };
 
 // Perfectly matched layer: the memory-variable correction of one step, for
@@ -196,7 +196,7 @@ void launch_step_batched(const Dims& d, int R, bool adjoint, int mode, const Ste
 void launch_accumulate(float* dst, const float* src, long long n, hipStream_t s);
 void launch_step(const Dims& d, int R, bool adjoint, const StencilCoef& cf, const SpongeCoef& sp,
                  const LaunchShape& ls, const StepParams& p, hipStream_t s);
-// Launches of the mode steps: forward kPrep, kCorrect, kMedium or kStepV; adjoint
+// Launches of the mode steps: forward kPrep, kCorrect, kMedium[Y0] or kStepV; adjoint
 // kCorrect or kImageV.
 void launch_step_mode(const Dims& d, int R, bool adjoint, int mode, const StencilCoef& cf,
                       const SpongeCoef& sp, const LaunchShape& ls, const StepParams& p, hipStream_t s);

@@ -213,8 +213,11 @@ __device__ __forceinline__ float tile_point_signal(const TileEntry* ent, TileEnt
 // as k inj (A = q = k L w^{m+1}, D = w^{m+1}):
 //   w^m = a (2 w^{m+1} + q + (k/12) L q + k inj) - b w^{m+2}.
 // uu: the point field D; bb, kk: B and k.
+template <int MODE>
+constexpr bool kIsMedium = MODE == kMedium || MODE == kMediumY0;
+
 template <bool ADJ, int MODE>
-constexpr bool kInjApart = (ADJ && MODE == kCorrect) || MODE == kMedium;
+constexpr bool kInjApart = (ADJ && MODE == kCorrect) || kIsMedium<MODE>;
 
 template <bool ADJ, int MODE>
 __device__ __forceinline__ float step_out(float ctr, float lap, float inj, float uu, float bb,
@@ -234,13 +237,14 @@ __device__ __forceinline__ float step_out(float ctr, float lap, float inj, float
 
 // Output of a medium step.  lap = L u, dens = sum_a gamma_a D_a u, inj the
 // injected value, lapb = L u^{n-1}, prev = u^{n-1}; at is the attenuation
-// field: added to the damping (att_power 0) or weighting L u - L u^{n-1} (2).
+// field: weighting L u - L u^{n-1} (Y2) or added to the damping (y = 0).
+template <bool Y2>
 __device__ __forceinline__ float medium_out(float ctr, float lap, float dens, float inj,
-                                            float lapb, float prev, float kk, float at,
-                                            int att_power, float eta, float half_dt)
+                                            float lapb, float prev, float kk, float at, float eta,
+                                            float half_dt)
 {
     float rhs = lap + dens + inj;
-    if (att_power == 2)
+    if constexpr (Y2)
         rhs = fmaf(at, lap - lapb, rhs);
     else
         eta += at;
@@ -253,12 +257,12 @@ __device__ __forceinline__ float medium_out(float ctr, float lap, float dens, fl
 //   y = 0:  h = v + (att a dt/4) ((2 u^{n-1} - 2 u) / k - v)  (att = 2 alpha0 vp, a the
 //           step's damping factor with the attenuation),
 // v the step's right-hand side L u + sum_a gamma_a D_a u + S (+ beta (L u - L u^{n-1})).
+template <bool Y2>
 __device__ __forceinline__ float medium_h(float ctr, float lap, float dens, float inj, float lapb,
-                                          float prev, float kk, float at, int att_power, float eta,
-                                          float half_dt)
+                                          float prev, float kk, float at, float eta, float half_dt)
 {
     float v = lap + dens + inj;
-    if (att_power == 2) {
+    if constexpr (Y2) {
         const float dl = lap - lapb;
         v = fmaf(at, dl, v);
         return fmaf(0.5f * at, dl, v);
@@ -293,9 +297,10 @@ __device__ __forceinline__ void step2d_body(const Dims& d, const StencilCoef& cf
     constexpr int LW = kTileX + 2 * R;
     constexpr int LH = TY + 2 * R;
     constexpr int RW = (LH + WAVES - 1) / WAVES;    // tile rows loaded per wave
-    constexpr bool MED = MODE == kMedium;
+    constexpr bool MED = kIsMedium<MODE>;
+    constexpr bool MED2 = MODE == kMedium;          // B a stencil field
     constexpr bool ONE = MODE == kImageV || MODE == kAdjPlain;      // adjoint with one stencil field
-    constexpr int NF = (ADJ && !ONE) || MED ? 2 : 1;   // stencil fields A (and U, or B)
+    constexpr int NF = (ADJ && !ONE) || MED2 ? 2 : 1;  // stencil fields A (and U, or B)
     __shared__ float sF[NF][LH * LW];
     __shared__ float sS[NF][TY * kTileX];           // injected signal per tile point
 
@@ -368,7 +373,7 @@ __device__ __forceinline__ void step2d_body(const Dims& d, const StencilCoef& cf
             const int gy = y0 + wy * RY + j;
             po[j] = xin && gy < n0 ? gy * s0 + gx : -1;
             const int bo = po[j] >= 0 ? po[j] * 4 : -1;
-            if constexpr (MODE != kPrep && !MED)
+            if constexpr (MODE != kPrep && !MED2)
                 bb[j] = bload(rb, bo);
             kk[j] = bload(rk, bo);
             if constexpr (MODE == kCorrect)
@@ -490,14 +495,20 @@ __device__ __forceinline__ void step2d_body(const Dims& d, const StencilCoef& cf
                 dy = fmaf(cf.d[0][q], SA[q * LW] - SA[-q * LW], dy);
                 dx = fmaf(cf.d[1][q], SA[q] - SA[-q], dx);
             }
-            const float* SB = &sF[1][(ly + R) * LW + lx + R];
-            const float lapb = lap2d<R, LW>(SB, cf);
+            float prev, lapb = 0.f;
+            if constexpr (MED2) {
+                const float* SB = &sF[NF - 1][(ly + R) * LW + lx + R];
+                lapb = lap2d<R, LW>(SB, cf);
+                prev = SB[0];
+            } else {
+                prev = bb[j];
+            }
             const float dens = fmaf(mgy[j], dy, mgx[j] * dx);
-            p.C[po[j]] = medium_out(ctr, lap, dens, inj, lapb, SB[0], kk[j], mat[j], p.att_power, eta,
-                                    sp.half_dt);
+            p.C[po[j]] = medium_out<MED2>(ctr, lap, dens, inj, lapb, prev, kk[j], mat[j], eta,
+                                          sp.half_dt);
             if (p.V)   // gradient forward: the imaging factor, read once by the adjoint
-                __builtin_nontemporal_store(medium_h(ctr, lap, dens, inj, lapb, SB[0], kk[j], mat[j],
-                                                     p.att_power, eta, sp.half_dt),
+                __builtin_nontemporal_store(medium_h<MED2>(ctr, lap, dens, inj, lapb, prev, kk[j],
+                                                           mat[j], eta, sp.half_dt),
                                             p.V + po[j]);
             continue;
         }
@@ -518,417 +529,7 @@ __device__ __forceinline__ void step2d_body(const Dims& d, const StencilCoef& cf
 }
 
 // ----------------------------------------------------------------------- 3D
-//
-// One block = one 64 x TY column tile marching along axis 0 over a chunk of
-// planes.  Each thread keeps the 2R+1 axis-0 neighbours of its RY points in a
-// rotating register queue (the march is unrolled by 2R+1 so that the queue
-// never shifts).  The plane tile with its halo goes to a double-buffered LDS
-// slot, so one barrier per plane suffices.  The march is software-pipelined:
-// while plane z is computed, the loads of plane z+1 (the queue's lead plane,
-// the halo, and the streamed point values of B, K, G) are in flight.  All
-// global accesses are raw buffer accesses with per-plane descriptors: offsets
-// outside the grid read 0 and drop stores, so no access needs a branch.
-
-template <int R, bool ADJ, int RY, int WAVES, int MODE = kStep>
-__device__ __forceinline__ void step3d_body(const Dims& d, const StencilCoef& cf,
-                                            const SpongeCoef& sp, const StepParams& p,
-                                            const LaunchShape& ls, const int b)
-{
-    constexpr int NT = 64 * WAVES;
-    constexpr int TY = WAVES * RY;
-    constexpr int LW = kTileX + 2 * R;
-    constexpr int LH = TY + 2 * R;
-    constexpr int Q = 2 * R + 1;
-    constexpr int NYH = 2 * R * kTileX;             // halo rows above/below
-    constexpr int NXH = 2 * R * TY;                 // halo columns left/right
-    constexpr int HY = (NYH + NT - 1) / NT;
-    constexpr int HX = (NXH + NT - 1) / NT;
-    constexpr bool MED = MODE == kMedium;
-    constexpr bool ONE = MODE == kImageV || MODE == kAdjPlain;      // adjoint with one stencil field
-    constexpr int NF = (ADJ && !ONE) || MED ? 2 : 1;   // stencil fields: A (and U, or B)
-    constexpr int PLANE = LH * LW;
-    constexpr int PL = TY * kTileX;                 // block-local points per plane
-    __shared__ float sF[2][NF][PLANE];
-    __shared__ float sS[2][NF][PL];                 // injected signal per plane point
-    __shared__ int2 sE[NF][NT];                     // entry (local point, value) per thread
-
-    if (b >= ls.tile_blocks_pad) {
-        sample_block(p.smp, p.A, p.step, b - ls.tile_blocks_pad);
-        return;
-    }
-    const int lb = xcd_logical(b, ls.tile_blocks_pad);
-    if (lb >= ls.tile_blocks)
-        return;
-    const int zci = lb / ls.tiles_xy;
-    const int tile = lb - zci * ls.tiles_xy;
-    const int y0 = (tile / ls.tiles_x) * TY;
-    const int x0 = (tile % ls.tiles_x) * kTileX;
-    const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];
-    const int z0 = zci * ls.zc;
-    const int z1 = min(z0 + ls.zc, n0);
-    const long long s0 = d.st[0];
-    const int s1 = (int)d.st[1];
-    const int tid = threadIdx.x;
-    const int lx = tid & 63;
-    const int wy = tid >> 6;
-    const int gx = x0 + lx;
-    const bool xin = gx < n2;
-    const float* F[2] = {p.A, ADJ ? p.U : (MED ? p.B : p.A)};
-
-    // plane-independent geometry: byte offsets within a plane (-1 = outside)
-    const int plane_bytes = (int)(s0 * 4);
-    int rbo[RY];
-    bool rin[RY];
-    float ey[RY];
-    const int dxd = layer_depth(gx, n2, d.nb);
-    const float ex = sp.e[2] * (float)(dxd * dxd);
-#pragma unroll
-    for (int j = 0; j < RY; ++j) {
-        const int gy = y0 + wy * RY + j;
-        rin[j] = xin && gy < n1;
-        rbo[j] = rin[j] ? (gy * s1 + gx) * 4 : -1;
-        const int dyd = layer_depth(gy, n1, d.nb);
-        ey[j] = fmaf(sp.e[1], (float)(dyd * dyd), ex);
-    }
-    int hy_l[HY], hy_o[HY];
-#pragma unroll
-    for (int h = 0; h < HY; ++h) {
-        const int i = tid + h * NT;
-        hy_l[h] = -1;
-        hy_o[h] = -1;
-        if (i < NYH) {
-            const int hr = i / kTileX;
-            const int c = i - hr * kTileX;
-            const int ly = hr < R ? hr - R : TY + hr - R;
-            const int gy = y0 + ly;
-            const int g = x0 + c;
-            hy_l[h] = (ly + R) * LW + c + R;
-            if (gy >= 0 && gy < n1 && g < n2)
-                hy_o[h] = (gy * s1 + g) * 4;
-        }
-    }
-    int hx_l[HX], hx_o[HX];
-#pragma unroll
-    for (int h = 0; h < HX; ++h) {
-        const int i = tid + h * NT;
-        hx_l[h] = -1;
-        hx_o[h] = -1;
-        if (i < NXH) {
-            const int row = i / (2 * R);
-            const int cc = i - row * (2 * R);
-            const int lxx = cc < R ? cc - R : kTileX + cc - R;
-            const int g = x0 + lxx;
-            const int gy = y0 + row;
-            hx_l[h] = (row + R) * LW + lxx + R;
-            if (g >= 0 && g < n2 && gy < n1)
-                hx_o[h] = (gy * s1 + g) * 4;
-        }
-    }
-    auto rsrc = [&](const float* f, int z) {
-        const bool in = z >= 0 && z < n0;
-        return plane_rsrc(f + (long long)(in ? z : 0) * s0, in ? plane_bytes : 0);
-    };
-
-    // queue slot (i + t) % Q holds plane z0 + i + t - R at march iteration i
-    float q[NF][RY][Q];
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int t = 0; t < 2 * R; ++t) {
-            const auto r = rsrc(F[f], z0 - R + t);
-#pragma unroll
-            for (int j = 0; j < RY; ++j)
-                q[f][j][t] = bload(r, rbo[j]);
-        }
-
-    float pl[NF][RY], phy[NF][HY], phx[NF][HX];
-    float pb[RY], pk[RY], pg[RY], pu[RY], pm[4][RY], pv[RY], pv2[RY];
-    auto prefetch = [&](int z) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            const auto rz = rsrc(F[f], z);
-            const auto rl = rsrc(F[f], z + R);
-#pragma unroll
-            for (int j = 0; j < RY; ++j)
-                pl[f][j] = bload(rl, rbo[j]);
-#pragma unroll
-            for (int h = 0; h < HY; ++h)
-                phy[f][h] = bload(rz, hy_o[h]);
-#pragma unroll
-            for (int h = 0; h < HX; ++h)
-                phx[f][h] = bload(rz, hx_o[h]);
-        }
-        const auto rb = rsrc(p.B, z);
-        const auto rk = rsrc(p.K, z);
-#pragma unroll
-        for (int j = 0; j < RY; ++j) {
-            if constexpr (MODE != kPrep && !MED)
-                pb[j] = bload_stream(rb, rbo[j]);
-            pk[j] = bload_stream(rk, rbo[j]);
-        }
-        if constexpr (MED) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const auto rm = rsrc(m < 3 ? p.gam[m] : p.att, z);
-#pragma unroll
-                for (int j = 0; j < RY; ++j)
-                    pm[m][j] = bload_stream(rm, rbo[j]);
-            }
-        }
-        if constexpr (MODE == kCorrect) {
-            const auto ru = rsrc(p.D, z);
-#pragma unroll
-            for (int j = 0; j < RY; ++j)
-                pu[j] = bload_stream(ru, rbo[j]);
-        }
-        if constexpr (ADJ && MODE != kAdjPlain) {
-            const auto rg = rsrc(p.G, z);
-#pragma unroll
-            for (int j = 0; j < RY; ++j)
-                pg[j] = bload_stream(rg, rbo[j]);
-        }
-        if constexpr (MODE == kImageV) {
-            const auto rv = rsrc(p.V, z);
-            // with V2 absent the descriptor is empty and its loads read 0
-            const auto r2 = p.V2 ? rsrc(p.V2, z) : plane_rsrc(p.V, 0);
-#pragma unroll
-            for (int j = 0; j < RY; ++j) {
-                pv[j] = bload_stream(rv, rbo[j]);
-                pv2[j] = bload_stream(r2, rbo[j]);
-            }
-        }
-    };
-
-    // Injection entries of the block (uniform range).  Thread t takes entry t,
-    // sums the signal over the point's run and parks (local point, value) in
-    // LDS; before the barrier of each plane it writes the value of its entry
-    // of that plane to the LDS plane array, where the point's thread takes
-    // (and clears) it after the barrier.  Blocks with more than NT entries
-    // read the rest at every plane.
-    constexpr bool INJ = MODE != kCorrect || ADJ;
-    constexpr bool IMG = ADJ && MODE != kCorrect && !ONE;
-    int eb0 = 0, ne0 = 0;
-    if constexpr (INJ) {
-        eb0 = p.inj.ptr[lb];
-        ne0 = p.inj.ptr[lb + 1] - eb0;
-    }
-    int eb1 = 0, ne1 = 0;
-    if constexpr (IMG) {
-        eb1 = p.img.ptr[lb];
-        ne1 = p.img.ptr[lb + 1] - eb1;
-    }
-    const bool inj_any = ne0 > 0;
-    const bool img_any = IMG && ne1 > 0;
-    prefetch(z0);
-    if (inj_any || img_any) {
-        int il0 = -1, il1 = -1;
-        float iv0 = 0.f, iv1 = 0.f;
-        if (tid < ne0) {
-            const TileEntry e = p.inj.ent[eb0 + tid];
-            if (e.run > 0) {
-                il0 = e.local;
-                iv0 = tile_point_signal<MODE == kPrep>(p.inj.ent + eb0 + tid, e, p.inj_sig,
-                                                       p.inj_stride, p.step);
-            }
-        }
-        if constexpr (IMG) {
-            if (tid < ne1) {
-                const TileEntry e = p.img.ent[eb1 + tid];
-                if (e.run > 0) {
-                    il1 = e.local;
-                    iv1 = tile_point_signal(p.img.ent + eb1 + tid, e, p.img_sig, p.img_stride, p.step);
-                }
-            }
-        }
-#pragma unroll
-        for (int bsel = 0; bsel < 2; ++bsel)
-#pragma unroll
-            for (int f = 0; f < NF; ++f)
-#pragma unroll
-                for (int j = 0; j < RY; ++j)
-                    sS[bsel][f][(wy * RY + j) * kTileX + lx] = 0.f;
-        sE[0][tid] = make_int2(il0, __float_as_int(iv0));
-        if constexpr (IMG)
-            sE[1][tid] = make_int2(il1, __float_as_int(iv1));
-        __syncthreads();
-        if (il0 >= 0 && il0 < PL)
-            sS[0][0][il0] = iv0;
-        if constexpr (IMG)
-            if (il1 >= 0 && il1 < PL)
-                sS[0][1][il1] = iv1;
-    }
-    // Entries beyond the first NT of the block, written at their plane.  A
-    // block's entries are sorted by point, so their planes never decrease.
-    // The adjoint (receiver sets of up to 512 taps a point fill some blocks
-    // with thousands of entries) keeps a cursor per thread over its entries
-    // (tid + NT, tid + 2 NT, ...) and at plane pz takes them until the first
-    // of a later plane: every entry is read once per chunk, plus one
-    // look-ahead per plane.  The forward step, whose source entries rarely
-    // overflow, scans them at every plane and keeps its registers.
-    int oc0 = tid + NT, oc1 = tid + NT;
-    auto overflow = [&](auto filt, const InjTable& T, int eb, int ne, int& oc, const float* sig,
-                        int stride, int pz, float* dst) {
-        if constexpr (ADJ) {
-            for (; oc < ne; oc += NT) {
-                const TileEntry en = T.ent[eb + oc];
-                const int ez = en.local / PL;
-                if (ez > pz)
-                    break;
-                if (en.run > 0 && ez == pz)
-                    dst[en.local - pz * PL] = tile_point_signal<decltype(filt)::value>(
-                        T.ent + eb + oc, en, sig, stride, p.step);
-            }
-        } else {
-            for (int e = tid + NT; e < ne; e += NT) {
-                const TileEntry en = T.ent[eb + e];
-                if (en.run > 0 && en.local / PL == pz)
-                    dst[en.local - pz * PL] = tile_point_signal<decltype(filt)::value>(
-                        T.ent + eb + e, en, sig, stride, p.step);
-            }
-        }
-    };
-
-    int buf = 0;
-    for (int zb = z0; zb < z1; zb += Q) {
-        unrolled_while<Q>([&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-            constexpr int slot_lead = (u + 2 * R) % Q;
-            constexpr int slot_c = (u + R) % Q;
-            const int z = zb + u;
-            if (z >= z1)
-                return false;
-            float bb[RY], kk[RY], gg[RY], uu[RY], mm[4][RY], vw[RY], vw2[RY];
-            float* S = &sF[buf][0][0];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                float* Sf = S + f * PLANE;
-#pragma unroll
-                for (int j = 0; j < RY; ++j) {
-                    q[f][j][slot_lead] = pl[f][j];
-                    Sf[(wy * RY + j + R) * LW + lx + R] = q[f][j][slot_c];
-                }
-#pragma unroll
-                for (int h = 0; h < HY; ++h)
-                    if (hy_l[h] >= 0)
-                        Sf[hy_l[h]] = phy[f][h];
-#pragma unroll
-                for (int h = 0; h < HX; ++h)
-                    if (hx_l[h] >= 0)
-                        Sf[hx_l[h]] = phx[f][h];
-            }
-#pragma unroll
-            for (int j = 0; j < RY; ++j) {
-                bb[j] = MODE != kPrep && !MED ? pb[j] : 0.f;
-                kk[j] = pk[j];
-                gg[j] = ADJ && MODE != kAdjPlain ? pg[j] : 0.f;
-                uu[j] = MODE == kCorrect ? pu[j] : 0.f;
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    mm[m][j] = MED ? pm[m][j] : 0.f;
-                vw[j] = MODE == kImageV ? pv[j] : 0.f;
-                vw2[j] = MODE == kImageV ? pv2[j] : 0.f;
-            }
-            if (z + 1 < z1)
-                prefetch(z + 1);
-            const int pz = z - z0;
-            if (pz > 0 && (inj_any || img_any)) {
-                // parked entry sets: the injection, and the imaging source term
-#pragma unroll
-                for (int f = 0; f < (IMG ? 2 : 1); ++f) {
-                    const int2 e = sE[f][tid];
-                    if (e.x >= 0 && e.x / PL == pz)
-                        sS[buf][f][e.x - pz * PL] = __int_as_float(e.y);
-                }
-            }
-            if (ne0 > NT)
-                overflow(std::integral_constant<bool, MODE == kPrep>{}, p.inj, eb0, ne0, oc0,
-                         p.inj_sig, p.inj_stride, pz, &sS[buf][0][0]);
-            if constexpr (IMG)
-                if (ne1 > NT)
-                    overflow(std::false_type{}, p.img, eb1, ne1, oc1, p.img_sig, p.img_stride, pz,
-                             &sS[buf][NF - 1][0]);
-            __syncthreads();
-
-            const auto rC = rsrc(p.C, z);
-            const auto rG = rsrc(ADJ && MODE != kAdjPlain ? p.G : p.C, z);
-            const auto rV = rsrc((MODE == kStepV || MED) && p.V ? p.V : p.C, z);
-            const int dzd = layer_depth(z, n0, d.nb);
-            const float ez = sp.e[0] * (float)(dzd * dzd);
-#pragma unroll
-            for (int j = 0; j < RY; ++j) {
-                if (!rin[j])
-                    continue;
-                const int ly = wy * RY + j;
-                const float* SA = S;
-                const float ctr = q[0][j][slot_c];
-                float az = 0.f, ay = 0.f, ax = 0.f;
-#pragma unroll
-                for (int qq = R; qq >= 1; --qq) {
-                    az = fmaf(cf.c[0][qq], q[0][j][(u + R + qq) % Q] + q[0][j][(u + R - qq) % Q], az);
-                    ay = fmaf(cf.c[1][qq], SA[(ly + R + qq) * LW + lx + R] + SA[(ly + R - qq) * LW + lx + R], ay);
-                    ax = fmaf(cf.c[2][qq], SA[(ly + R) * LW + lx + R + qq] + SA[(ly + R) * LW + lx + R - qq], ax);
-                }
-                float lap = fmaf(cf.c0, ctr, az + ay + ax);
-                float inj = 0.f;
-                if (inj_any) {
-                    if constexpr (kInjApart<ADJ, MODE>)
-                        inj = sS[buf][0][ly * kTileX + lx];
-                    else
-                        lap += sS[buf][0][ly * kTileX + lx];
-                    sS[buf][0][ly * kTileX + lx] = 0.f;
-                }
-                const float eta = ez + ey[j];
-                if constexpr (MED) {
-                    const float* SB = S + PLANE;
-                    float dz = 0.f, dy = 0.f, dx = 0.f, bz = 0.f, by = 0.f, bx = 0.f;
-#pragma unroll
-                    for (int qq = R; qq >= 1; --qq) {
-                        dz = fmaf(cf.d[0][qq], q[0][j][(u + R + qq) % Q] - q[0][j][(u + R - qq) % Q], dz);
-                        dy = fmaf(cf.d[1][qq], SA[(ly + R + qq) * LW + lx + R] - SA[(ly + R - qq) * LW + lx + R], dy);
-                        dx = fmaf(cf.d[2][qq], SA[(ly + R) * LW + lx + R + qq] - SA[(ly + R) * LW + lx + R - qq], dx);
-                        bz = fmaf(cf.c[0][qq], q[1][j][(u + R + qq) % Q] + q[1][j][(u + R - qq) % Q], bz);
-                        by = fmaf(cf.c[1][qq], SB[(ly + R + qq) * LW + lx + R] + SB[(ly + R - qq) * LW + lx + R], by);
-                        bx = fmaf(cf.c[2][qq], SB[(ly + R) * LW + lx + R + qq] + SB[(ly + R) * LW + lx + R - qq], bx);
-                    }
-                    const float prev = q[1][j][slot_c];
-                    const float lapb = fmaf(cf.c0, prev, bz + by + bx);
-                    const float dens = fmaf(mm[0][j], dz, fmaf(mm[1][j], dy, mm[2][j] * dx));
-                    bstore_nt(rC, rbo[j], medium_out(ctr, lap, dens, inj, lapb, prev, kk[j], mm[3][j],
-                                                     p.att_power, eta, sp.half_dt));
-                    if (p.V)   // gradient forward: the imaging factor
-                        bstore_nt(rV, rbo[j], medium_h(ctr, lap, dens, inj, lapb, prev, kk[j], mm[3][j],
-                                                       p.att_power, eta, sp.half_dt));
-                    continue;
-                }
-                const float out = step_out<ADJ, MODE>(ctr, lap, inj, uu[j], bb[j], kk[j], eta, sp.half_dt);
-                bstore_nt(rC, rbo[j], out);
-                if constexpr (MODE == kStepV)
-                    bstore_nt(rV, rbo[j], lap);
-                if constexpr (MODE == kImageV) {
-                    bstore_nt(rG, rbo[j], fmaf(ctr, vw[j], fmaf(bb[j], vw2[j], gg[j])));
-                } else if constexpr (ADJ && MODE != kAdjPlain) {
-                    const float* SU = S + (NF - 1) * PLANE;
-                    const float uc0 = q[NF - 1][j][slot_c];
-                    float uz = 0.f, uy = 0.f, ux = 0.f;
-#pragma unroll
-                    for (int qq = R; qq >= 1; --qq) {
-                        uz = fmaf(cf.c[0][qq], q[NF - 1][j][(u + R + qq) % Q] + q[NF - 1][j][(u + R - qq) % Q], uz);
-                        uy = fmaf(cf.c[1][qq], SU[(ly + R + qq) * LW + lx + R] + SU[(ly + R - qq) * LW + lx + R], uy);
-                        ux = fmaf(cf.c[2][qq], SU[(ly + R) * LW + lx + R + qq] + SU[(ly + R) * LW + lx + R - qq], ux);
-                    }
-                    float lu = fmaf(cf.c0, uc0, uz + uy + ux);
-                    if (img_any) {
-                        lu += sS[buf][NF - 1][ly * kTileX + lx];
-                        sS[buf][NF - 1][ly * kTileX + lx] = 0.f;
-                    }
-                    bstore_nt(rG, rbo[j], image_out<MODE>(ctr, uc0, lu, uu[j], kk[j], gg[j]));
-                }
-            }
-            buf ^= 1;
-            return true;
-        });
-    }
-}
+#include "step3d_body.h"
 
 // ------------------------------------------------------------ kernel entry points
 //
@@ -954,41 +555,47 @@ __global__ __launch_bounds__(64 * WAVES) void step2d_batched(Dims d, StencilCoef
     step2d_body<R, ADJ, RY, WAVES, MODE>(d, cf, st.sp, st.p, ls, blockIdx.x);
 }
 
-// Occupancy target of a single-shot 3D kernel: 4 waves per SIMD (at most 128
-// VGPRs) where that costs no spills, else left to the compiler.  (The batched
-// kernels hold their slot's parameters in registers as well; they are left to
-// the compiler, which keeps them free of spills.)
-template <bool ADJ, int RY, int WAVES, int MODE>
+// Occupancy of the single-shot 3D kernels: the leapfrog steps, the fourth-order
+// launches with one stencil field and the y = 0 medium step stay within 128
+// VGPRs (4 waves per SIMD) by themselves; the attribute holds the compiler to
+// it where the launch shapes count on it.  (The batched kernels hold their
+// slot's parameters in registers as well; they are left to the compiler, which
+// keeps them free of spills.)
+template <bool ADJ, int MODE>
 constexpr int min_waves_3d()
 {
-    return (MODE == kStep || MODE == kStepV || MODE == kImageV || MODE == kAdjPlain) &&
-                   (RY <= 2 || (!ADJ && WAVES == 8))
-               ? 4
-               : 1;
+    return MODE == kMedium || MODE == kMediumY0 || (ADJ && MODE == kCorrect) ? 1 : 4;
 }
 
-template <int R, bool ADJ, int RY, int WAVES, int MODE = kStep>
+template <int R, bool ADJ, int VX, int WAVES, int MODE, bool STREAM>
 __global__ __launch_bounds__(64 * WAVES)
-__attribute__((amdgpu_waves_per_eu(min_waves_3d<ADJ, RY, WAVES, MODE>())))
+__attribute__((amdgpu_waves_per_eu(min_waves_3d<ADJ, MODE>())))
 void step3d_kernel(Dims d, StencilCoef cf, SpongeCoef sp, StepParams p, LaunchShape ls)
 {
-    step3d_body<R, ADJ, RY, WAVES, MODE>(d, cf, sp, p, ls, blockIdx.x);
+    step3d_body<R, ADJ, VX, WAVES, MODE, STREAM>(d, cf, sp, p, ls, blockIdx.x);
 }
 
-template <int R, bool ADJ, int RY, int WAVES, int MODE>
+template <int R, bool ADJ, int VX, int WAVES, int MODE>
 __global__ __launch_bounds__(64 * WAVES) void step3d_batched(Dims d, StencilCoef cf, LaunchShape ls,
                                                              const SlotStep* table)
 {
     const SlotStep st = table[blockIdx.y];
     if (!st.active)
         return;
-    step3d_body<R, ADJ, RY, WAVES, MODE>(d, cf, st.sp, st.p, ls, blockIdx.x);
+    step3d_body<R, ADJ, VX, WAVES, MODE, true>(d, cf, st.sp, st.p, ls, blockIdx.x);
 }
 
-// Tile shapes with compiled kernels (rows per thread, waves); tile_shape()
-// returns one of these.  Without STRIDE_TILE_SWEEP: the 2D shape and the three
-// 3D shapes (forward, adjoint / two-field steps, and adjoint steps imaging
-// from v) of common.h.
+// Points per thread of a 3D step: four with one stencil field, two with two
+// (whose register queues would otherwise leave one wave per SIMD).
+template <bool ADJ, int MODE>
+constexpr int vec3d()
+{
+    constexpr bool one = MODE == kImageV || MODE == kAdjPlain;
+    return (ADJ && !one) || MODE == kMedium ? kVx3dTwo : kVx3dOne;
+}
+
+// 2D tile shapes with compiled kernels (rows per thread, waves); tile_shape()
+// returns one of these.  Without STRIDE_TILE_SWEEP: the shape of common.h.
 #ifdef STRIDE_TILE_SWEEP
 #define STRIDE_DISPATCH2D(L)                                                                      \
     do {                                                                                          \
@@ -1001,40 +608,8 @@ __global__ __launch_bounds__(64 * WAVES) void step3d_batched(Dims d, StencilCoef
         else                                                                                      \
             L(4, 4);                                                                              \
     } while (0)
-#define STRIDE_DISPATCH3D(L)                                                                      \
-    do {                                                                                          \
-        if (ls.waves == 8) {                                                                      \
-            if (ls.ry == 1)                                                                       \
-                L(1, 8);                                                                          \
-            else if (ls.ry == 2)                                                                  \
-                L(2, 8);                                                                          \
-            else                                                                                  \
-                L(4, 8);                                                                          \
-        } else {                                                                                  \
-            if (ls.ry == 2)                                                                       \
-                L(2, 4);                                                                          \
-            else                                                                                  \
-                L(4, 4);                                                                          \
-        }                                                                                         \
-    } while (0)
 #else
 #define STRIDE_DISPATCH2D(L) L(kRy2d, kWaves2d)
-#define STRIDE_DISPATCH3D(L)                                                                      \
-    do {                                                                                          \
-        if constexpr (!ADJ) {                                                                     \
-            if (ls.ry == kRy3dFwd && ls.waves == kWaves3dFwd) {                                   \
-                L(kRy3dFwd, kWaves3dFwd);                                                         \
-                break;                                                                            \
-            }                                                                                     \
-        }                                                                                         \
-        if constexpr (ADJ && (MODE == kImageV || MODE == kAdjPlain)) {                            \
-            if (ls.ry == kRy3dAdjV && ls.waves == kWaves3dAdjV) {                                 \
-                L(kRy3dAdjV, kWaves3dAdjV);                                                       \
-                break;                                                                            \
-            }                                                                                     \
-        }                                                                                         \
-        L(kRy3dAdj, kWaves3dAdj);                                                                 \
-    } while (0)
 #endif
 
 // Launch of one step kernel family: the tile blocks, then the sample blocks.
@@ -1056,14 +631,16 @@ template <int R, bool ADJ, int MODE>
 void launch3d_t(const Dims& d, const StencilCoef& cf, const SpongeCoef& sp, const LaunchShape& ls,
                 const StepParams& p, hipStream_t s)
 {
-    const int nt = 64 * ls.waves;
+    const int nt = 64 * kWaves3d;
     int smp_blocks = (p.smp.count * sample_lanes(p.smp.ntap) + nt - 1) / nt;
     dim3 grid(ls.tile_blocks_pad + smp_blocks);
-#define STRIDE_LAUNCH3D(RY_, W_)                                                                  \
-    hipLaunchKernelGGL((step3d_kernel<R, ADJ, RY_, W_, MODE>), grid, dim3(64 * (W_)), 0, s, d, cf, sp, \
-                       p, ls)
-    STRIDE_DISPATCH3D(STRIDE_LAUNCH3D);
-#undef STRIDE_LAUNCH3D
+    constexpr int VX = vec3d<ADJ, MODE>();
+    if (stream_3d(d, ADJ, MODE))
+        hipLaunchKernelGGL((step3d_kernel<R, ADJ, VX, kWaves3d, MODE, true>), grid, dim3(nt), 0, s, d,
+                           cf, sp, p, ls);
+    else
+        hipLaunchKernelGGL((step3d_kernel<R, ADJ, VX, kWaves3d, MODE, false>), grid, dim3(nt), 0, s, d,
+                           cf, sp, p, ls);
 }
 
 template <int R, bool ADJ, int MODE>
@@ -1084,18 +661,15 @@ template <int R, bool ADJ, int MODE>
 void batched3d_t(const Dims& d, const StencilCoef& cf, const LaunchShape& ls, const SlotStep* table,
                  int nslots, int max_sample_threads, hipStream_t s)
 {
-    const int nt = 64 * ls.waves;
+    const int nt = 64 * kWaves3d;
     int smp_blocks = (max_sample_threads + nt - 1) / nt;
     dim3 grid(ls.tile_blocks_pad + smp_blocks, nslots);
-#define STRIDE_LAUNCH3DB(RY_, W_)                                                                  \
-    hipLaunchKernelGGL((step3d_batched<R, ADJ, RY_, W_, MODE>), grid, dim3(64 * (W_)), 0, s, d, cf, ls, \
-                       table)
-    STRIDE_DISPATCH3D(STRIDE_LAUNCH3DB);
-#undef STRIDE_LAUNCH3DB
+    hipLaunchKernelGGL((step3d_batched<R, ADJ, vec3d<ADJ, MODE>(), kWaves3d, MODE>), grid, dim3(nt), 0,
+                       s, d, cf, ls, table);
 }
 
 // Runtime (R, mode) to template arguments for one family.  Forward modes:
-// kStep, kPrep, kCorrect, kMedium, kStepV; adjoint modes: kStep, kCorrect,
+// kStep, kPrep, kCorrect, kMedium, kMediumY0, kStepV; adjoint modes: kStep, kCorrect,
 // kImageV, kAdjPlain.
 template <bool THREE_D, bool ADJ, int R>
 void launch_mode_r(int mode, const Dims& d, const StencilCoef& cf, const SpongeCoef& sp,
@@ -1123,6 +697,7 @@ void launch_mode_r(int mode, const Dims& d, const StencilCoef& cf, const SpongeC
             STRIDE_MODE_CASE(kPrep)
             STRIDE_MODE_CASE(kCorrect)
             STRIDE_MODE_CASE(kMedium)
+            STRIDE_MODE_CASE(kMediumY0)
             STRIDE_MODE_CASE(kStepV)
         default:
             return;

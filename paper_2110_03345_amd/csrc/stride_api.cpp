@@ -82,11 +82,12 @@ bool fd1_weights(int order, double* dw)
     return false;
 }
 
-LaunchShape make_shape(const Dims& d, int zc, int ry, int waves)
+// Launch shape of tiles of 64 x ty points (2D: ry rows per thread; 3D: chunks
+// of zc planes).
+LaunchShape make_shape(const Dims& d, int ty, int zc, int ry, int waves)
 {
     LaunchShape ls{};
     int nx = d.n[d.nd - 1], ny = d.n[d.nd - 2];
-    const int ty = ry * waves;
     ls.ty = ty;
     ls.ry = ry;
     ls.waves = waves;
@@ -105,11 +106,20 @@ LaunchShape make_shape(const Dims& d, int zc, int ry, int waves)
     return ls;
 }
 
-// Planes per 3D block.  Short chunks give many independent blocks (the march
-// is latency-bound, so parallelism wins over the 2R lead-in planes each chunk
-// re-reads, which mostly hit L2).  On 316^3: 32 for the 64 x 32 forward tile,
-// 16 for the 64 x 8 adjoint tile.  (STRIDE_TILE_SWEEP builds read STRIDE_ZC.)
-int default_zc(const Dims& d, bool adjoint)
+// Planes per 3D block.  A block marches zc + 2R planes at about 1 us a plane
+// (alone on its CU) and re-reads the 2R lead-in planes, so short chunks win
+// while those come from the Infinity Cache: the shortest chunk (from kZc3dMin
+// on) whose blocks are all resident at once, `resident` of them, else the
+// shortest (one stencil field; 6 planes where a batch of such shots, which the
+// engine runs on the same shape, leaves the cache) or the longest tried (two,
+// whose two register queues make the lead-in dearer).  Beyond the cache the lead-in costs HBM
+// traffic, and kZc3dOne / kZc3dTwo planes balance it against blocks in flight.
+// Forward step, us (zc: time): 128^3 4: 9.3, 8: 12.6, 16: 20.6, 32: 37;
+// 188^3 4: 22.8, 7: 22.2, 32: 44; 252^3 4: 47.4, 6: 47.8, 8: 49.8, 16: 55.7; 284^3
+// 4: 76.3, 8: 73.7, 16: 77.7; 316^3 4: 102.7, 8: 93.6, 16: 95.3, 32: 92.9.
+// Fused adjoint: 128^3 4: 16.9, 8: 17.4, 16: 24.9; 220^3 4: 72.6, 10: 65.8,
+// 16: 69.9; 316^3 8: 196, 16: 187, 32: 185.
+int chunk_planes(const Dims& d, int ty, bool two_fields)
 {
     if (d.nd != 3)
         return 1;
@@ -118,7 +128,17 @@ int default_zc(const Dims& d, bool adjoint)
     if (want > 0)
         return want;
 #endif
-    return adjoint ? kZc3dAdj : kZc3dFwd;
+    if ((two_fields ? 5 : 3) * d.total * 4 > kCacheBytes)
+        return two_fields ? kZc3dTwo : kZc3dOne;
+    const long long tiles = (long long)((d.n[2] + kTileX - 1) / kTileX) * ((d.n[1] + ty - 1) / ty);
+    const int longest = two_fields ? 10 : 8;
+    const long long resident = two_fields ? 512 : 1024;
+    for (int zc = kZc3dMin; zc <= longest; ++zc)
+        if (tiles * ((d.n[0] + zc - 1) / zc) <= resident)
+            return zc;
+    if (two_fields)
+        return longest;
+    return 5 * d.total * 4 > kCacheBytes ? 6 : kZc3dMin;
 }
 
 int pitch_align()
@@ -943,7 +963,7 @@ struct Runner {
             p.img = P.no_inj;
             if (dwavelet)
                 p.smp = src_samples(P, dwavelet);
-            launch_step_mode(P.dims, P.R, true, image ? kImageV : kAdjPlain, P.cf, P.sp, P.ls_adjv, p,
+            launch_step_mode(P.dims, P.R, true, image ? kImageV : kAdjPlain, P.cf, P.sp, P.ls_fwd, p,
                              s);
             ++adj_steps;
             ++adj_launches;
@@ -1329,10 +1349,6 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
     return check_finite(finite_flag(ws), s, {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}});
 }
 
-// Forward solve in a heterogeneous medium: three rotating wavefields (the
-// step reads u^{n-1} as a stencil field, so u^{n+1} cannot overwrite it), the
-// medium fields prepared once, one kMedium launch per step on the two-field
-// launch shape (whose source table is src_img).
 // Views of a medium workspace: [scratch | k | u0 | u1 | u2 | gamma_a x nd | att]
 // (the gradient adds [G | traces | residual | H x (nt - 1)]).
 struct MediumWs {
@@ -1403,10 +1419,24 @@ int prepare_medium(const stride_plan& P, const float* vp, const float* rho, cons
     return STRIDE_OK;
 }
 
-// Medium forward sweep: three rotating wavefields (the step reads u^{n-1} as a
-// stencil field, so u^{n+1} cannot overwrite it), one kMedium launch per step
-// on the two-field launch shape (whose source table is src_img); with H the
-// step n also stores its imaging factor into H[n].  Returns the field of u^{nt-1}.
+// One medium step launch.  y = 2 reads u^{n-1} as a stencil field too, on the
+// two-field launch shape (whose source table is src_img); y = 0 reads it at the
+// point only and runs on the forward shape.
+void launch_medium_step(const stride_plan& P, const MediumWs& M, int att_power, StepParams& p,
+                        hipStream_t s)
+{
+    const bool y2 = att_power == 2;
+    p.inj = y2 ? P.src_img : P.src_inj;
+    for (int a = 0; a < 3; ++a)
+        p.gam[a] = M.gam[a] ? M.gam[a] : M.gam[0];
+    p.att = M.att;
+    launch_step_mode(P.dims, P.R, false, y2 ? kMedium : kMediumY0, P.cf, P.sp,
+                     y2 ? P.ls_adj : P.ls_fwd, p, s);
+}
+
+// Medium forward sweep: three rotating wavefields (the y = 2 step reads u^{n-1}
+// as a stencil field, so u^{n+1} cannot overwrite it), one launch per step;
+// with H the step n also stores its imaging factor into H[n].  Returns the field of u^{nt-1}.
 const float* medium_sweep(const stride_plan& P, const MediumWs& M, const float* wavelet,
                           int att_power, float* traces, float* const* H, hipStream_t s)
 {
@@ -1421,15 +1451,10 @@ const float* medium_sweep(const stride_plan& P, const MediumWs& M, const float* 
         p.C = M.u[next];
         p.K = M.k;
         p.step = n;
-        p.inj = P.src_img;
         p.inj_sig = wavelet;
         p.smp = rec_samples(P, traces);
-        for (int a = 0; a < 3; ++a)
-            p.gam[a] = M.gam[a] ? M.gam[a] : M.gam[0];
-        p.att = M.att;
-        p.att_power = att_power;
         p.V = H ? H[n] : nullptr;
-        launch_step_mode(P.dims, P.R, false, kMedium, P.cf, P.sp, P.ls_adj, p, s);
+        launch_medium_step(P, M, att_power, p, s);
         const int t = prev;
         prev = cur;
         cur = next;
@@ -1542,16 +1567,11 @@ int gradient_medium(const stride_plan& P, const float* vp, const float* rho, con
         p.C = C;
         p.K = M.k;
         p.step = n;
-        p.inj = P.src_img;
         p.inj_sig = wavelet;
         if (smp)
             p.smp = rec_samples(P, smp);
-        for (int a = 0; a < 3; ++a)
-            p.gam[a] = M.gam[a] ? M.gam[a] : M.gam[0];
-        p.att = M.att;
-        p.att_power = att_power;
         p.V = V;
-        launch_step_mode(P.dims, P.R, false, kMedium, P.cf, P.sp, P.ls_adj, p, s);
+        launch_medium_step(P, M, att_power, p, s);
     };
     // the field of three that is neither a nor b
     auto third = [](float* const* f3, const float* a, const float* b3) {
@@ -1928,14 +1948,16 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
         }
     }
 
-    int ryf, wf, rya, wa, ryv, wv;
-    tile_shape(P->nd, false, &ryf, &wf);
-    tile_shape(P->nd, true, &rya, &wa);
-    tile_shape_v(P->nd, &ryv, &wv);
-    P->ls_fwd = make_shape(d, default_zc(d, false), ryf, wf);
-    P->ls_adj = make_shape(d, default_zc(d, true), rya, wa);
-    P->ls_adjv = make_shape(d, default_zc(d, true), ryv, wv);
-
+    int ryf = 1, wf = kWaves3d, rya = 1, wa = kWaves3d;
+    int tyf = kVx3dOne * kWaves3d, tya = kVx3dTwo * kWaves3d;
+    if (P->nd == 2) {
+        tile_shape_2d(false, &ryf, &wf);
+        tile_shape_2d(true, &rya, &wa);
+        tyf = ryf * wf;
+        tya = rya * wa;
+    }
+    P->ls_fwd = make_shape(d, tyf, chunk_planes(d, tyf, false), ryf, wf);
+    P->ls_adj = make_shape(d, tya, chunk_planes(d, tya, true), rya, wa);
 
     TapSet st, rt;
     if ((rc = make_taps(*P, src_xyz, nsrc, st, "source")) ||
@@ -1946,7 +1968,7 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     HostTiles tsf = build_tiles(*P, st, 1.0 / P->cellvol, P->ls_fwd);
     HostTiles tsa = build_tiles(*P, st, 1.0 / P->cellvol, P->ls_adj);
     HostTiles tra = build_tiles(*P, rt, 1.0, P->ls_adj);
-    HostTiles trv = build_tiles(*P, rt, 1.0, P->ls_adjv);
+    HostTiles trv = build_tiles(*P, rt, 1.0, P->ls_fwd);
     std::vector<long long> ridx, sidx;
     std::vector<float> rw, sw;
     flatten_sample(rt, 1.0, ridx, rw);
@@ -1975,8 +1997,7 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     size_t o_trv_ptr = add(trv.ptr.data(), trv.ptr.size(), 4);
     size_t o_trv_ent = add(trv.ent.data(), trv.ent.size(), sizeof(TileEntry));
     std::vector<int> none(
-        (size_t)std::max({P->ls_fwd.tile_blocks, P->ls_adj.tile_blocks, P->ls_adjv.tile_blocks}) + 1,
-        0);
+        (size_t)std::max(P->ls_fwd.tile_blocks, P->ls_adj.tile_blocks) + 1, 0);
     size_t o_none = add(none.data(), none.size(), 4);
     std::vector<char> host(off, 0);
     for (auto& pt : parts)

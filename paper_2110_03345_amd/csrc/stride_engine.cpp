@@ -103,7 +103,6 @@ struct stride_engine {
     int R;
     StencilCoef cf;
     LaunchShape ls_fwd, ls_adj;
-    LaunchShape ls_adjv;      // adjoint steps imaging from a stored v (the single-shot shape)
     int max_slots, max_samples, tmax;
     int ntap;                 // taps per receiver of the engine's grid (linear or sinc)
     bool graphs;
@@ -363,9 +362,7 @@ void launch_chunk(stride_engine* E, int ticks, const int* gy, hipStream_t s)
             const bool adj = kGroupAdjoint[g];
             // traces are sampled by the forward step (fourth order: its kPrep row)
             const bool smp = g == kGFwd || g == kGFwdV || g == kGPrep;
-            const LaunchShape& ls = !adj                                     ? E->ls_fwd
-                                    : (g == kGAdjImage || g == kGAdjPlain) ? E->ls_adjv
-                                                                           : E->ls_adj;
+            const LaunchShape& ls = !adj || g == kGAdjImage || g == kGAdjPlain ? E->ls_fwd : E->ls_adj;
             launch_step_batched(E->dims, E->R, adj, kGroupMode[g], E->cf, ls, base + E->group_off[g],
                                 gy[g], smp ? sample_threads : 0, s);
         }
@@ -480,7 +477,6 @@ int stride_engine_create(const stride_grid_t* grid, int32_t max_slots, int32_t m
     E->cf = sp->cf;
     E->ls_fwd = sp->ls_fwd;
     E->ls_adj = sp->ls_adj;
-    E->ls_adjv = sp->ls_adjv;
     E->max_slots = max_slots;
     E->max_samples = max_receivers;
     E->ntap = sp->ntap;

@@ -26,76 +26,48 @@
 
 namespace stride {
 
-// Tile shapes the kernels use (the host sizes launch shapes with these): the
+// Tile shape of the 2D kernels (the host sizes launch shapes with it): the
 // constants of common.h.  A build with STRIDE_TILE_SWEEP compiles every shape
-// the sweeps try and reads the choice from the environment (STRIDE_RY2D[_ADJ],
-// STRIDE_WAVES2D[_ADJ], STRIDE_RY3D[_ADJ], STRIDE_WAVES3D[_ADJ]); the library
-// as shipped ignores the environment.
-void tile_shape(int nd, bool adjoint, int* ry, int* waves)
+// the sweeps try and reads the choice from the environment
+// (STRIDE_RY2D[_ADJ], STRIDE_WAVES2D[_ADJ]); the library as shipped ignores
+// the environment.
+void tile_shape_2d(bool adjoint, int* ry, int* waves)
 {
 #ifdef STRIDE_TILE_SWEEP
-    if (nd == 2) {
-        const char* er = getenv(adjoint ? "STRIDE_RY2D_ADJ" : "STRIDE_RY2D");
-        const char* ew = getenv(adjoint ? "STRIDE_WAVES2D_ADJ" : "STRIDE_WAVES2D");
-        int r = er && *er ? atoi(er) : kRy2d;
-        int w = ew && *ew ? atoi(ew) : kWaves2d;
-        if (w == 8) {
-            r = 4;
-        } else {
-            w = 4;
-            if (r != 2 && r != 8)
-                r = 4;
-        }
-        *ry = r;
-        *waves = w;
-        return;
-    }
-    const char* er = getenv(adjoint ? "STRIDE_RY3D_ADJ" : "STRIDE_RY3D");
-    const char* ew = getenv(adjoint ? "STRIDE_WAVES3D_ADJ" : "STRIDE_WAVES3D");
-    int r = er && *er ? atoi(er) : (adjoint ? kRy3dAdj : kRy3dFwd);
-    int w = ew && *ew ? atoi(ew) : (adjoint ? kWaves3dAdj : kWaves3dFwd);
-    if (w != 8)
-        w = 4;
-    if (r != 1 && r != 2)
+    const char* er = getenv(adjoint ? "STRIDE_RY2D_ADJ" : "STRIDE_RY2D");
+    const char* ew = getenv(adjoint ? "STRIDE_WAVES2D_ADJ" : "STRIDE_WAVES2D");
+    int r = er && *er ? atoi(er) : kRy2d;
+    int w = ew && *ew ? atoi(ew) : kWaves2d;
+    if (w == 8) {
         r = 4;
-    if (w == 4 && r == 1)
-        r = 2;
+    } else {
+        w = 4;
+        if (r != 2 && r != 8)
+            r = 4;
+    }
     *ry = r;
     *waves = w;
 #else
-    if (nd == 2) {
-        *ry = kRy2d;
-        *waves = kWaves2d;
-    } else {
-        *ry = adjoint ? kRy3dAdj : kRy3dFwd;
-        *waves = adjoint ? kWaves3dAdj : kWaves3dFwd;
-    }
+    (void)adjoint;
+    *ry = kRy2d;
+    *waves = kWaves2d;
 #endif
 }
 
-void tile_shape_v(int nd, int* ry, int* waves)
+// Point values are read once per step.  Loaded with the non-temporal policy
+// they do not evict the stencil field's halo, which pays beyond the Infinity
+// Cache (forward step at 316^3: 92.7 us against 103.9); while the fields a step
+// touches stay in that cache from step to step the ordinary policy finds them
+// there (252^3: 47.4 against 55.9 us, storing v 57.8 against 68.3, 188^3: 22.8
+// against 26.7).  The fields counted are those that live from step to step:
+// wavefields, k, G and the second stencil or point field.
+bool stream_3d(const Dims& d, bool adjoint, int mode)
 {
-    if (nd == 2) {
-        tile_shape(nd, true, ry, waves);
-        return;
-    }
-#ifdef STRIDE_TILE_SWEEP
-    const char* er = getenv("STRIDE_RY3D_ADJV");
-    const char* ew = getenv("STRIDE_WAVES3D_ADJV");
-    int r = er && *er ? atoi(er) : kRy3dAdjV;
-    int w = ew && *ew ? atoi(ew) : kWaves3dAdjV;
-    if (w != 8)
-        w = 4;
-    if (r != 1 && r != 2)
-        r = 4;
-    if (w == 4 && r == 1)
-        r = 2;
-    *ry = r;
-    *waves = w;
-#else
-    *ry = kRy3dAdjV;
-    *waves = kWaves3dAdjV;
-#endif
+    const bool one = mode == kImageV || mode == kAdjPlain;
+    const int fields = (adjoint && !one) || mode == kMedium || mode == kMediumY0 ? 5
+                       : mode == kCorrect || mode == kImageV                    ? 4
+                                                                                : 3;
+    return fields * d.total * 4 > kCacheBytes;
 }
 
 namespace {
