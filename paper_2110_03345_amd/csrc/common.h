@@ -136,6 +136,101 @@ void tile_shape_2d(bool adjoint, int* ry, int* waves);
 // Whether a 3D step loads its point values with the non-temporal policy.
 bool stream_3d(const Dims& d, bool adjoint, int mode);
 
+// 2D sweeps that keep the state on the chip (step2d_resident.h): one block of
+// kResidentThreads per tile of tx x ty points, tx a multiple of 4.
+constexpr int kResidentThreads = 1024;
+constexpr int kResidentItems = 2;    // quads per thread, at most
+constexpr int kResidentSide = 256;   // tile side, at most
+
+struct ResidentShape {
+    int tx, ty;
+    int tiles_x, tiles_y, tiles;
+};
+
+// Quads of a tile that neighbours take: R rows above and below, the quads of
+// R columns left and right.
+__host__ __device__ inline int resident_outer_quads(int R, const ResidentShape& rs)
+{
+    return 2 * R * (rs.tx / 4) + (rs.ty - 2 * R) * 2 * ((R + 3) / 4);
+}
+
+// Threads with items: enough for nq quads at J each and for the outer quads at
+// one each, in whole waves.
+__host__ __device__ inline int resident_compute_threads(int nq, int outer, int J)
+{
+    const int n = (nq + J - 1) / J > outer ? (nq + J - 1) / J : outer;
+    return (n + 63) / 64 * 64;
+}
+
+// Exchange words of a tile: word k of outer quad i at k * stride + i, so that
+// a wave's accesses are contiguous (four words per quad in a row cost four times
+// the transactions); stride a whole number of 64-byte lines.
+__host__ __device__ inline int resident_word_stride(int R, const ResidentShape& rs)
+{
+    return (resident_outer_quads(R, rs) + 7) / 8 * 8;
+}
+
+// Bytes of the exchange area (two buffers of words).
+__host__ __device__ inline long long resident_word_bytes(int R, const ResidentShape& rs)
+{
+    return 2ll * rs.tiles * 4 * resident_word_stride(R, rs) * 8;
+}
+
+// Row length of the LDS region of a tile (the tile and its frame of R rows and
+// R columns, in whole quads) and the region index of tile point (y, x).
+__host__ __device__ inline int resident_row(int R, const ResidentShape& rs)
+{
+    return rs.tx + 8 * ((R + 3) / 4);
+}
+__host__ __device__ inline int resident_index(int R, const ResidentShape& rs, int y, int x)
+{
+    return (y + R) * resident_row(R, rs) + 4 * ((R + 3) / 4) + x;
+}
+
+// LDS of a block: two buffers of the region, two more for injected values, and
+// k in an adjoint sweep with two quads per thread.
+__host__ __device__ inline int resident_lds_bytes(int R, const ResidentShape& rs, bool injects,
+                                                  bool adjoint)
+{
+    const bool k = adjoint && rs.tx / 4 * rs.ty > kResidentThreads;
+    return ((injects ? 4 : 2) * resident_row(R, rs) * (rs.ty + 2 * R) + (k ? rs.tx * rs.ty : 0)) * 4;
+}
+
+// Points sampled by tile b: ptr[b] .. ptr[b+1]; taps as region indices.
+struct ResidentSamples {
+    const int* ptr;
+    const int* id;         // row of `out`
+    const int* idx;        // [..][ntap]
+    const float* w;        // [..][ntap]
+    float* out;
+    int out_stride;
+    int ntap;
+};
+
+// A sweep of `count` steps (kStep, kStepV or the adjoint kImageV).
+struct ResidentParams {
+    const float* A;        // u^n and u^{n-1} at the start (NULL: both zero)
+    const float* B;
+    float* A2;             // the two states at the end (NULL: not kept)
+    float* B2;
+    const float* K;
+    float* G;              // adjoint: imaging accumulator
+    float* V;              // kStepV: v of step v_from (out); adjoint: v of the first step (in)
+    long long vstride;     // elements from one step's V to the next step's
+    int v_from;            // kStepV: first step whose v is stored
+    int step;              // signal / sample index of the first step
+    int dir;               // +1 forward, -1 adjoint
+    int count;             // steps
+    int sample_last;       // sample the final state too (at index step + dir count)
+    int injects;           // the table has entries (LDS for their values)
+    InjTable inj;          // entries per tile; `local` = region index
+    const float* inj_sig;
+    int inj_stride;
+    ResidentSamples smp;   // sampling of u^n (out NULL: none)
+    unsigned long long* words;   // exchange area, zero at the start
+    unsigned* err;
+};
+
 // What a step launch computes.  Fourth-order time runs two launches per
 // forward step and three per adjoint step (kPrep on u^m and on w^{m+1}, then
 // the adjoint kCorrect).
@@ -200,6 +295,14 @@ void launch_step(const Dims& d, int R, bool adjoint, const StencilCoef& cf, cons
 // kCorrect or kImageV.
 void launch_step_mode(const Dims& d, int R, bool adjoint, int mode, const StencilCoef& cf,
                       const SpongeCoef& sp, const LaunchShape& ls, const StepParams& p, hipStream_t s);
+
+// One sweep kept on the chip; hipSuccess, or the launch error (nothing ran).
+// The exchange words must be zero (resident_word_bytes of them).
+hipError_t launch_resident(const Dims& d, int R, int mode, const StencilCoef& cf,
+                           const SpongeCoef& sp, const ResidentShape& rs, const ResidentParams& p,
+                           hipStream_t s);
+// Fills p with NaN where *err is set (a sweep whose blocks gave up waiting).
+void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s);
 
 void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const PmlParams& pp,
                            hipStream_t s);

@@ -37,6 +37,9 @@ struct stride_plan {
     stride::InjTable rec_inj;    // receivers (adjoint injection), weights (blocks of ls_adj)
     stride::InjTable rec_inj_v;  // the same entries, blocks of ls_fwd
     stride::InjTable no_inj;     // no entries (blocks of any shape)
+    stride::ResidentShape rs;    // 2D sweeps kept on the chip (tiles 0: not for this plan)
+    stride::InjTable src_res, rec_res;           // sources / receivers by tile of rs
+    stride::ResidentSamples rec_smp, src_smp;    // sampling by tile of rs (out unset)
     const long long* rec_idx;
     const float* rec_w;          // receiver sampling
     const long long* src_idx;

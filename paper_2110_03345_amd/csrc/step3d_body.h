@@ -44,15 +44,21 @@ __device__ __forceinline__ StepVec<VX> bloadv(__amdgpu_buffer_rsrc_t r, int byte
                                   __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, AUX));
 }
 
+template <int VX, int AUX = 0>
+__device__ __forceinline__ void bstorev(__amdgpu_buffer_rsrc_t r, int byte_off, StepVec<VX> v)
+{
+    using U = unsigned __attribute__((ext_vector_type(VX)));
+    if constexpr (VX == 4)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U, v), r, byte_off, 0, AUX);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U, v), r, byte_off, 0, AUX);
+}
+
 // Non-temporal store: results are read back only in a later launch.
 template <int VX>
 __device__ __forceinline__ void bstorev_nt(__amdgpu_buffer_rsrc_t r, int byte_off, StepVec<VX> v)
 {
-    using U = unsigned __attribute__((ext_vector_type(VX)));
-    if constexpr (VX == 4)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U, v), r, byte_off, 0, 2);
-    else
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U, v), r, byte_off, 0, 2);
+    bstorev<VX, 2>(r, byte_off, v);
 }
 
 // STREAM: the point values are loaded with the non-temporal policy (grids

@@ -266,36 +266,25 @@ struct HostTiles {
     std::vector<TileEntry> ent;
 };
 
-// Injection entries of every tap with a nonzero weight, grouped by block of a
-// launch shape (2D: tile; 3D: tile and chunk of zc planes, block index
-// chunk * tiles_xy + tile), sorted by block-local point and in (point, tap)
-// order within a point.
-HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
-                      const LaunchShape& ls)
+// Injection entries of every tap with a nonzero weight, grouped by block,
+// sorted by block-local point and in (point, tap) order within a point.
+// place(c) gives the block and local index of padded coordinates c.
+template <class Place>
+HostTiles group_entries(const TapSet& taps, double scale, int blocks, Place place)
 {
     HostTiles T;
-    const int plane = ls.ty * kTileX;   // block-local points per plane
     const size_t npts = taps.T ? taps.w.size() / taps.T : 0;
-    std::vector<std::vector<TileEntry>> per(ls.tile_blocks);
+    std::vector<std::vector<TileEntry>> per(blocks);
     for (size_t p = 0; p < npts; ++p)
         for (int t = 0; t < taps.T; ++t) {
             const size_t k = p * taps.T + t;
             if (taps.w[k] == 0.0)
                 continue;
-            const int* c = &taps.coord[k * 3];
-            const int cy = c[P.nd - 2], cx = c[P.nd - 1];
-            const int ty = cy / ls.ty, tx = cx / kTileX;
-            int zci = 0, pz = 0;
-            if (P.nd == 3) {
-                zci = c[0] / ls.zc;
-                pz = c[0] - zci * ls.zc;
-            }
-            const int local = pz * plane + (cy - ty * ls.ty) * kTileX + (cx - tx * kTileX);
-            const size_t blk = (size_t)zci * ls.tiles_xy + (size_t)ty * ls.tiles_x + tx;
-            per[blk].push_back(TileEntry{local, 0, (int)p, (float)(taps.w[k] * scale)});
+            const std::pair<size_t, int> at = place(&taps.coord[k * 3]);
+            per[at.first].push_back(TileEntry{at.second, 0, (int)p, (float)(taps.w[k] * scale)});
         }
-    T.ptr.assign(ls.tile_blocks + 1, 0);
-    for (int t = 0; t < ls.tile_blocks; ++t) {
+    T.ptr.assign(blocks + 1, 0);
+    for (int t = 0; t < blocks; ++t) {
         auto& v = per[t];
         std::stable_sort(v.begin(), v.end(),
                          [](const TileEntry& a, const TileEntry& b) { return a.local < b.local; });
@@ -310,6 +299,112 @@ HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
         T.ent.insert(T.ent.end(), v.begin(), v.end());
     }
     return T;
+}
+
+// By block of a launch shape (2D: tile; 3D: tile and chunk of zc planes, block
+// index chunk * tiles_xy + tile).
+HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
+                      const LaunchShape& ls)
+{
+    const int plane = ls.ty * kTileX;   // block-local points per plane
+    return group_entries(taps, scale, ls.tile_blocks, [&](const int* c) {
+        const int cy = c[P.nd - 2], cx = c[P.nd - 1];
+        const int ty = cy / ls.ty, tx = cx / kTileX;
+        int zci = 0, pz = 0;
+        if (P.nd == 3) {
+            zci = c[0] / ls.zc;
+            pz = c[0] - zci * ls.zc;
+        }
+        return std::pair<size_t, int>((size_t)zci * ls.tiles_xy + (size_t)ty * ls.tiles_x + tx,
+                                      pz * plane + (cy - ty * ls.ty) * kTileX + (cx - tx * kTileX));
+    });
+}
+
+// By tile of the 2D sweeps kept on the chip.
+HostTiles build_resident(const stride_plan& P, const TapSet& taps, double scale)
+{
+    const ResidentShape& rs = P.rs;
+    return group_entries(taps, scale, rs.tiles, [&](const int* c) {
+        const int ty = c[0] / rs.ty, tx = c[1] / rs.tx;
+        return std::pair<size_t, int>((size_t)ty * rs.tiles_x + tx,
+                                      resident_index(P.R, rs, c[0] - ty * rs.ty, c[1] - tx * rs.tx));
+    });
+}
+
+// Points sampled by each tile of the same: a point belongs to the tile of the
+// node below it, whose region holds all its taps (at most 3 nodes before and 4
+// after that node on an axis; the frame is R >= 4 wide).
+struct HostSamples {
+    std::vector<int> ptr, id, idx;
+    std::vector<float> w;
+};
+
+HostSamples build_resident_samples(const stride_plan& P, const TapSet& taps, double scale)
+{
+    const ResidentShape& rs = P.rs;
+    const size_t npts = taps.T ? taps.w.size() / taps.T : 0;
+    const int before = P.g.interp == 1 ? kSincHalfWidth - 1 : 0;
+    std::vector<std::vector<int>> per(rs.tiles);
+    auto home = [&](size_t p, int a) { return taps.coord[p * taps.T * 3 + a] + before; };
+    for (size_t p = 0; p < npts; ++p)
+        per[(size_t)(home(p, 0) / rs.ty) * rs.tiles_x + home(p, 1) / rs.tx].push_back((int)p);
+    HostSamples S;
+    S.ptr.assign(rs.tiles + 1, 0);
+    for (int t = 0; t < rs.tiles; ++t) {
+        const int y0 = t / rs.tiles_x * rs.ty, x0 = t % rs.tiles_x * rs.tx;
+        for (int p : per[t]) {
+            S.id.push_back(p);
+            for (int k = 0; k < taps.T; ++k) {
+                const size_t q = (size_t)p * taps.T + k;
+                S.idx.push_back(resident_index(P.R, rs, taps.coord[q * 3] - y0, taps.coord[q * 3 + 1] - x0));
+                S.w.push_back((float)(taps.w[q] * scale));
+            }
+        }
+        S.ptr[t + 1] = (int)S.id.size();
+    }
+    return S;
+}
+
+// Tiles of the 2D sweeps kept on the chip: at most one block per CU, at most
+// kResidentItems quads per thread, frames and exchange words within what the
+// block and the workspace hold (the words take the two adjoint or forward
+// fields, free while the state is on the chip).  One quad per thread where that
+// fits the chip, in few, full blocks with short frames (a step is then mostly
+// the exchange, and fewer blocks wait for each other: at 240^2 1.76 us a step
+// with 80 x 48 tiles, 2.0 with 40 x 30; at 592^2 1.84 with 68 x 60, 2.6 with
+// 40 x 37); else two, in small tiles (a step is then mostly the items: at 1104^2
+// 2.35 us with 80 x 62, 2.5 with 92 x 69).
+ResidentShape choose_resident(const Dims& d, int R, int cus)
+{
+    ResidentShape best{};
+    long long best_cost = 0;
+    const int hb = (R + 3) / 4;
+    const int n0 = d.n[0], n1 = d.n[1];
+    const long long field = round_up(d.total * 4, 256);
+    for (int tiles_x = 1; tiles_x <= cus; ++tiles_x) {
+        const int tx = std::max((int)round_up((n1 + tiles_x - 1) / tiles_x, 4), std::max(16, 8 * hb));
+        if ((n1 + tx - 1) / tx != tiles_x)
+            continue;
+        for (int tiles_y = 1; tiles_x * tiles_y <= cus; ++tiles_y) {
+            const int ty = std::max((n0 + tiles_y - 1) / tiles_y, 2 * R);
+            if ((n0 + ty - 1) / ty != tiles_y || tx / 4 * ty > kResidentItems * kResidentThreads)
+                continue;
+            const ResidentShape rs{tx, ty, tiles_x, tiles_y, tiles_x * tiles_y};
+            const int nq = tx / 4 * ty;
+            const int nh = 2 * R * (tx / 4 + 2 * hb) + 2 * hb * ty;
+            if (tx > kResidentSide || ty > kResidentSide || nh > kResidentThreads || resident_outer_quads(R, rs) > kResidentThreads ||
+                resident_lds_bytes(R, rs, true, true) > 155 * 1024 ||
+                resident_word_bytes(R, rs) > 2 * field)
+                continue;
+            const long long cost = nq <= kResidentThreads ? 5 * rs.tiles + 4 * nh - 2 * nq
+                                                          : (1 << 20) + 2 * nq + 2 * nh;
+            if (!best.tiles || cost < best_cost) {
+                best = rs;
+                best_cost = cost;
+            }
+        }
+    }
+    return best;
 }
 
 void flatten_sample(const TapSet& taps, double scale, std::vector<long long>& idx,
@@ -766,7 +861,8 @@ struct OutArray {
     const char* what;
 };
 
-int check_finite(unsigned* flag, hipStream_t s, std::initializer_list<OutArray> outs)
+int check_finite(unsigned* flag, hipStream_t s, std::initializer_list<OutArray> outs,
+                 bool resident = false)
 {
     if (!g_check_finite)
         return STRIDE_OK;
@@ -779,9 +875,13 @@ int check_finite(unsigned* flag, hipStream_t s, std::initializer_list<OutArray> 
             launch_finite_scan(o.d, o.n, flag, bit, s);
         bit <<= 1;
     }
-    unsigned host = 0;
-    HIP_TRY(hipMemcpyAsync(&host, flag, sizeof(host), hipMemcpyDeviceToHost, s));
+    unsigned word[2] = {0, 0};   // the scan's bits; blocks of a resident sweep gave up
+    HIP_TRY(hipMemcpyAsync(word, flag, resident ? 8 : 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    if (word[1])
+        return fail(STRIDE_E_HIP, "the blocks of a 2D sweep were not resident together "
+                                  "(neighbour wait timed out); the outputs are NaN");
+    const unsigned host = word[0];
     if (!host)
         return STRIDE_OK;
     std::string names;
@@ -797,6 +897,48 @@ int check_finite(unsigned* flag, hipStream_t s, std::initializer_list<OutArray> 
 // Flag word of the non-finite check: word 4 of a workspace's scratch
 // (words 0-3 hold the vp and medium checks).
 unsigned* finite_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 4; }
+
+// Word 5: set when the blocks of a resident sweep gave up waiting for each other.
+unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; }
+
+// One 2D sweep kept on the chip, its exchange words in the two fields at
+// `words` (zeroed here).  False when the plan has no such sweeps, the sweep is
+// shorter than two steps (blocks then do not wait for each other, and one could
+// store its final state before a neighbour has loaded its frame) or the launch
+// is refused; the caller then runs single steps.
+bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
+                  hipStream_t s)
+{
+    if (!P.rs.tiles || p.count < 2)
+        return false;
+    launch_fill(words, resident_word_bytes(P.R, P.rs) / 4, 0.f, s);
+    p.words = reinterpret_cast<unsigned long long*>(words);
+    p.err = err;
+    p.injects = (mode == kImageV ? P.nrec : P.nsrc) > 0;
+    if (launch_resident(P.dims, P.R, mode, P.cf, P.sp, P.rs, p, s) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Parameters of a forward sweep of `count` steps from step n (traces: record
+// u^n .. , with `last` the final state too).
+ResidentParams resident_forward(const stride_plan& P, const float* K, const float* wavelet, int n,
+                                int count, float* traces, bool last)
+{
+    ResidentParams p{};
+    p.K = K;
+    p.step = n;
+    p.dir = 1;
+    p.count = count;
+    p.inj = P.src_res;
+    p.inj_sig = wavelet;
+    p.inj_stride = P.nt;
+    p.smp = P.rec_smp;
+    p.smp.out = traces;
+    p.sample_last = traces && last;
+    return p;
+}
 
 long long phys_points(const stride_plan& P)
 {
@@ -873,6 +1015,10 @@ struct Runner {
         segpath = path.kind == GradPath::kSegmented;
     }
 
+    unsigned* err() const { return resident_flag(W.flags); }
+    long long field_step() const { return W.pool[1] - W.pool[0]; }
+    bool kept_on_chip = false;   // some sweep of this solve ran resident
+
     // pool layout of the segmented path: v buffer [0, vbuf), two working
     // fields, then the start state (u^j, u^{j-1}) of segments 1 .. K-2
     float* seg_work(int i) const { return W.pool[path.vbuf + i]; }
@@ -917,11 +1063,47 @@ struct Runner {
         ++launches;
     }
 
+    // Segmented forward sweep kept on the chip: one launch up to each stored
+    // start state, the last one storing v^n over the last segment.
+    bool forward_seg_resident(float* traces)
+    {
+        const std::vector<int>& j = path.starts;
+        const int K = (int)j.size();
+        for (int k = 0; k + 1 < K; ++k) {
+            const bool end = k + 2 == K;
+            const int to = end ? P.nt - 1 : j[k + 1];
+            ResidentParams p = resident_forward(P, W.k, wavelet, j[k], to - j[k], traces, end);
+            if (k > 0) {
+                p.A = seg_state(k, 0);
+                p.B = seg_state(k, 1);
+            }
+            if (end) {
+                p.V = W.pool[0];
+                p.vstride = field_step();
+                p.v_from = j[K - 1] - j[k];
+            } else {
+                p.A2 = seg_state(k + 1, 0);
+                p.B2 = seg_state(k + 1, 1);
+            }
+            if (!run_resident(P, end ? kStepV : kStep, p, W.w[0], err(), s))
+                return false;
+            kept_on_chip = true;
+            steps += to - j[k];
+            ++launches;
+        }
+        return true;
+    }
+
     // Forward sweep of the segmented path (u rotates in the adjoint fields);
-    // returns the field of u^{nt-1}.
+    // returns the field of u^{nt-1}, or NULL when it has been sampled already.
     const float* forward_seg(float* traces)
     {
         const int last = path.starts.back();
+        if (P.torder == 2 && forward_seg_resident(traces)) {
+            launch_fill(W.pool[P.nt - 1 - last], P.dims.total, 0.f, s);     // as below
+            return nullptr;
+        }
+        steps = launches = 0;
         launch_fill(W.w[0], P.dims.total, 0.f, s);
         launch_fill(W.w[1], P.dims.total, 0.f, s);
         float *fc = W.w[0], *fp = W.w[1];
@@ -944,6 +1126,37 @@ struct Runner {
     {
         if (P.torder == 4) {
             adjoint_p(j, e, V, wa, grad_traces, dwavelet);
+            return;
+        }
+        // kept on the chip, one imaging term per step: the paired form adds the
+        // same terms in the same order
+        ResidentParams rp{};
+        rp.K = W.k;
+        rp.G = W.G;
+        rp.V = V[e - 1 - j];
+        rp.vstride = -field_step();
+        rp.step = e - 1;
+        rp.dir = -1;
+        rp.count = e - j;
+        rp.inj = P.rec_res;
+        rp.inj_sig = grad_traces;
+        rp.inj_stride = P.nt;
+        rp.smp = P.src_smp;
+        rp.smp.out = dwavelet;
+        if (e < P.nt) {
+            rp.A = W.w[wa];
+            rp.B = W.w[1 - wa];
+        }
+        if (j > 0) {
+            rp.A2 = W.w[wa];
+            rp.B2 = W.w[1 - wa];
+        }
+        // the whole sweep needs no fields of its own; a segment keeps w there
+        // and exchanges in the working pair
+        if (run_resident(P, kImageV, rp, segpath ? seg_work(0) : W.w[0], err(), s)) {
+            kept_on_chip = true;
+            adj_steps += e - j;
+            ++adj_launches;
             return;
         }
         for (int m = e - 1; m >= j; --m) {
@@ -982,15 +1195,26 @@ struct Runner {
                 // recompute v^n, n in [j_k, e), from the segment's start state
                 float* fc = k >= 1 ? seg_state(k, 0) : seg_work(0);
                 float* fp = k >= 1 ? seg_state(k, 1) : seg_work(1);
-                if (k == 0) {
-                    launch_fill(fc, P.dims.total, 0.f, s);
-                    launch_fill(fp, P.dims.total, 0.f, s);
-                }
                 const int seg = g_timer.begin(s);
                 const long long s0 = steps, l0 = launches;
-                for (int n = j[k]; n < e; ++n) {
-                    seg_step(fc, fp, fp, n, W.pool[n - j[k]], nullptr);
-                    std::swap(fc, fp);
+                ResidentParams p = resident_forward(P, W.k, wavelet, j[k], e - j[k], nullptr, false);
+                p.A = k >= 1 ? fc : nullptr;
+                p.B = k >= 1 ? fp : nullptr;
+                p.V = W.pool[0];
+                p.vstride = field_step();
+                if (P.torder == 2 && run_resident(P, kStepV, p, seg_work(0), err(), s)) {
+                    kept_on_chip = true;
+                    steps += e - j[k];
+                    ++launches;
+                } else {
+                    if (k == 0) {
+                        launch_fill(fc, P.dims.total, 0.f, s);
+                        launch_fill(fp, P.dims.total, 0.f, s);
+                    }
+                    for (int n = j[k]; n < e; ++n) {
+                        seg_step(fc, fp, fp, n, W.pool[n - j[k]], nullptr);
+                        std::swap(fc, fp);
+                    }
                 }
                 g_timer.end(seg, s, 2, steps - s0, launches - l0);
             }
@@ -1085,10 +1309,21 @@ struct Runner {
         }
     }
 
-    // Forward sweep of the full-history path; returns the field of u^{nt-1}.
+    // Forward sweep of the full-history path; returns the field of u^{nt-1}, or
+    // NULL when it has been sampled already.
     const float* forward_v(float* traces)
     {
         float* u[2] = {W.w[0], W.w[1]};
+        ResidentParams rp = resident_forward(P, W.k, wavelet, 0, P.nt - 1, traces, true);
+        rp.V = W.pool[0];
+        rp.vstride = field_step();
+        if (run_resident(P, kStepV, rp, W.w[0], err(), s)) {
+            kept_on_chip = true;
+            launch_fill(W.pool[P.nt - 1], P.dims.total, 0.f, s);    // as below
+            steps += P.nt - 1;
+            ++launches;
+            return nullptr;
+        }
         launch_fill(u[0], P.dims.total, 0.f, s);
         launch_fill(u[1], P.dims.total, 0.f, s);
         int cur = 0;
@@ -1275,6 +1510,19 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
     if (rc)
         return rc;
     launch_prep_k(P.dims, vp, P.g.dt, k, s);
+    const std::initializer_list<OutArray> outs = {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}};
+    if (P.rs.tiles) {
+        launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
+        int id = g_timer.begin(s);
+        if (run_resident(P, kStep, resident_forward(P, k, wavelet, 0, P.nt - 1, traces, true), u[0],
+                         resident_flag(ws), s)) {
+            g_timer.end(id, s, 0, P.nt - 1, 1);
+            launch_poison(resident_flag(ws), traces, (long long)P.nrec * P.nt, s);
+            HIP_TRY(hipGetLastError());
+            return check_finite(finite_flag(ws), s, outs, true);
+        }
+        g_timer.end(id, s, 0, 0, 0);
+    }
     launch_fill(u[0], P.dims.total, 0.f, s);
     launch_fill(u[1], P.dims.total, 0.f, s);
     int tid = g_timer.begin(s);
@@ -1304,7 +1552,7 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
         g_timer.end(tid, s, 0, P.nt - 1, 2LL * (P.nt - 1));
         launch_sample(rec_samples(P, traces), u[cur], P.nt - 1, s);
         HIP_TRY(hipGetLastError());
-        return check_finite(finite_flag(ws), s, {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}});
+        return check_finite(finite_flag(ws), s, outs);
     }
     PmlParams pm{};
     int ps = 0;
@@ -1346,7 +1594,7 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
     g_timer.end(tid, s, 0, P.nt - 1, (P.boundary == 1 ? 2LL : 1LL) * (P.nt - 1));
     launch_sample(rec_samples(P, traces), u[cur], P.nt - 1, s);
     HIP_TRY(hipGetLastError());
-    return check_finite(finite_flag(ws), s, {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}});
+    return check_finite(finite_flag(ws), s, outs);
 }
 
 // Views of a medium workspace: [scratch | k | u0 | u1 | u2 | gamma_a x nd | att]
@@ -1724,6 +1972,7 @@ int forward_save(const stride_plan& P, const float* vp, const float* wavelet, fl
         return rc;
     float* tr = traces ? traces : W.traces;
     launch_prep_k(P.dims, vp, P.g.dt, W.k, s);
+    launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
     TraceRange range_("forward sweep");
     Runner run(P, W, s, wavelet);
     const float* last;
@@ -1741,7 +1990,10 @@ int forward_save(const stride_plan& P, const float* vp, const float* wavelet, fl
         last = W.pool[run.cursor.cur()];
     }
     // last sample from the final state x_{nt-1}
-    launch_sample(rec_samples(P, tr), last, P.nt - 1, s);
+    if (last)
+        launch_sample(rec_samples(P, tr), last, P.nt - 1, s);
+    if (run.kept_on_chip)
+        launch_poison(resident_flag(ws), tr, (long long)P.nrec * P.nt, s);
     if (traces && traces != W.traces)
         launch_copy(W.traces, traces, (long long)P.nrec * P.nt, s);
     HIP_TRY(hipGetLastError());
@@ -1783,6 +2035,8 @@ int backward(const stride_plan& P, const float* vp, const float* wavelet, const 
         launch_time_filter3(dwavelet, P.nsrc, P.nt, s);
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, W.G, P.torder == 4 ? W.k : nullptr, vp, dvp, W.w[0], W.w[1], s);
+    if (run.kept_on_chip)
+        launch_poison(resident_flag(ws), dvp, phys_points(P), s);
     HIP_TRY(hipGetLastError());
     return STRIDE_OK;
 }
@@ -1959,6 +2213,16 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     P->ls_fwd = make_shape(d, tyf, chunk_planes(d, tyf, false), ryf, wf);
     P->ls_adj = make_shape(d, tya, chunk_planes(d, tya, true), rya, wa);
 
+    // 2D leapfrog sweeps with the sponge may keep their state on the chip
+    P->rs = ResidentShape{};
+    if (P->nd == 2 && P->torder == 2 && P->boundary == 0) {
+        int dev = 0, cus = 0, coop = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+            hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop)
+            P->rs = choose_resident(d, P->R, cus);
+    }
+
     TapSet st, rt;
     if ((rc = make_taps(*P, src_xyz, nsrc, st, "source")) ||
         (rc = make_taps(*P, rec_xyz, nrec, rt, "receiver"))) {
@@ -1969,6 +2233,14 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     HostTiles tsa = build_tiles(*P, st, 1.0 / P->cellvol, P->ls_adj);
     HostTiles tra = build_tiles(*P, rt, 1.0, P->ls_adj);
     HostTiles trv = build_tiles(*P, rt, 1.0, P->ls_fwd);
+    HostTiles tss, tsr;
+    HostSamples hrs, hss;
+    if (P->rs.tiles) {
+        tss = build_resident(*P, st, 1.0 / P->cellvol);
+        tsr = build_resident(*P, rt, 1.0);
+        hrs = build_resident_samples(*P, rt, 1.0);
+        hss = build_resident_samples(*P, st, 1.0 / P->cellvol);
+    }
     std::vector<long long> ridx, sidx;
     std::vector<float> rw, sw;
     flatten_sample(rt, 1.0, ridx, rw);
@@ -1996,6 +2268,20 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     size_t o_tra_ent = add(tra.ent.data(), tra.ent.size(), sizeof(TileEntry));
     size_t o_trv_ptr = add(trv.ptr.data(), trv.ptr.size(), 4);
     size_t o_trv_ent = add(trv.ent.data(), trv.ent.size(), sizeof(TileEntry));
+    size_t o_res[12];
+    {
+        int i = 0;
+        for (const HostTiles* t : {&tss, &tsr}) {
+            o_res[i++] = add(t->ptr.data(), t->ptr.size(), 4);
+            o_res[i++] = add(t->ent.data(), t->ent.size(), sizeof(TileEntry));
+        }
+        for (const HostSamples* h : {&hrs, &hss}) {
+            o_res[i++] = add(h->ptr.data(), h->ptr.size(), 4);
+            o_res[i++] = add(h->id.data(), h->id.size(), 4);
+            o_res[i++] = add(h->idx.data(), h->idx.size(), 4);
+            o_res[i++] = add(h->w.data(), h->w.size(), 4);
+        }
+    }
     std::vector<int> none(
         (size_t)std::max(P->ls_fwd.tile_blocks, P->ls_adj.tile_blocks) + 1, 0);
     size_t o_none = add(none.data(), none.size(), 4);
@@ -2020,6 +2306,15 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     P->rec_inj = InjTable{(const int*)(B + o_tra_ptr), (const TileEntry*)(B + o_tra_ent)};
     P->rec_inj_v = InjTable{(const int*)(B + o_trv_ptr), (const TileEntry*)(B + o_trv_ent)};
     P->no_inj = InjTable{(const int*)(B + o_none), (const TileEntry*)(B + o_tra_ent)};
+
+    P->src_res = InjTable{(const int*)(B + o_res[0]), (const TileEntry*)(B + o_res[1])};
+    P->rec_res = InjTable{(const int*)(B + o_res[2]), (const TileEntry*)(B + o_res[3])};
+    auto samples = [&](const size_t* o) {
+        return ResidentSamples{(const int*)(B + o[0]), (const int*)(B + o[1]), (const int*)(B + o[2]),
+                               (const float*)(B + o[3]), nullptr, P->nt, P->ntap};
+    };
+    P->rec_smp = samples(o_res + 4);
+    P->src_smp = samples(o_res + 8);
 
     P->rec_idx = (const long long*)(B + o_ridx);
     P->rec_w = (const float*)(B + o_rw);
@@ -2218,7 +2513,8 @@ int stride_forward_save(const stride_plan_t* plan, const float* vp, const float*
     if (rc)
         return rc;
     return check_finite(finite_flag(ws), s,
-                        {{traces ? traces : W.traces, nullptr, (long long)plan->nrec * plan->nt, "traces"}});
+                        {{traces ? traces : W.traces, nullptr, (long long)plan->nrec * plan->nt, "traces"}},
+                        true);
 }
 
 int stride_backward(const stride_plan_t* plan, const float* vp, const float* wavelet,
@@ -2235,7 +2531,8 @@ int stride_backward(const stride_plan_t* plan, const float* vp, const float* wav
         return rc;
     return check_finite(finite_flag(ws), s,
                         {{dvp, nullptr, phys_points(*plan), "dvp"},
-                         {dwavelet, nullptr, dwavelet ? (long long)plan->nsrc * plan->nt : 0, "dwavelet"}});
+                         {dwavelet, nullptr, dwavelet ? (long long)plan->nsrc * plan->nt : 0, "dwavelet"}},
+                        true);
 }
 
 int stride_plan_gradient(const stride_plan_t* plan, const float* vp, const float* wavelet,
@@ -2261,7 +2558,8 @@ int stride_plan_gradient(const stride_plan_t* plan, const float* vp, const float
     return check_finite(finite_flag(ws), s,
                         {{W.traces, nullptr, (long long)plan->nrec * plan->nt, "traces"},
                          {nullptr, misfit, 1, "misfit"},
-                         {dvp, nullptr, phys_points(*plan), "dvp"}});
+                         {dvp, nullptr, phys_points(*plan), "dvp"}},
+                        true);
 }
 
 int stride_workspace_query(const stride_grid_t* grid, int32_t nsrc, int32_t nrec, int32_t mode,

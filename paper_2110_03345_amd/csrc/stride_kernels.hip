@@ -516,6 +516,22 @@ void launch_copy(float* dst, const float* src, long long n, hipStream_t s)
     hipLaunchKernelGGL(copy_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, dst, src, n);
 }
 
+__global__ void poison_kernel(const unsigned* err, float* p, long long n)
+{
+    if (!*err)
+        return;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (long long)gridDim.x * blockDim.x)
+        p[i] = __uint_as_float(0x7fc00000u);
+}
+
+void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s)
+{
+    if (n > 0)
+        hipLaunchKernelGGL(poison_kernel, dim3(std::min(grid_for(n, 256), 256)), dim3(256), 0, s, err, p,
+                           n);
+}
+
 // flag |= bit when any of the n values is NaN or infinite.
 template <class T>
 __global__ void finite_scan_kernel(const T* p, long long n, unsigned* flag, unsigned bit)
