@@ -222,13 +222,22 @@ struct ResidentParams {
     int dir;               // +1 forward, -1 adjoint
     int count;             // steps
     int sample_last;       // sample the final state too (at index step + dir count)
+    SpongeCoef sp;
     int injects;           // the table has entries (LDS for their values)
     InjTable inj;          // entries per tile; `local` = region index
     const float* inj_sig;
     int inj_stride;
     ResidentSamples smp;   // sampling of u^n (out NULL: none)
-    unsigned long long* words;   // exchange area, zero at the start
+    unsigned long long* words;   // exchange area: no word holds a step number in
+    unsigned tag;                // (tag, tag + count], the numbers of this sweep
     unsigned* err;
+};
+
+// Sweeps of one launch, on rs.tiles blocks each.
+constexpr int kResidentSlots = 12;   // kernel arguments hold 4 KB
+struct ResidentBatch {
+    int n;
+    ResidentParams p[kResidentSlots];
 };
 
 // What a step launch computes.  Fourth-order time runs two launches per
@@ -299,8 +308,7 @@ void launch_step_mode(const Dims& d, int R, bool adjoint, int mode, const Stenci
 // One sweep kept on the chip; hipSuccess, or the launch error (nothing ran).
 // The exchange words must be zero (resident_word_bytes of them).
 hipError_t launch_resident(const Dims& d, int R, int mode, const StencilCoef& cf,
-                           const SpongeCoef& sp, const ResidentShape& rs, const ResidentParams& p,
-                           hipStream_t s);
+                           const ResidentShape& rs, const ResidentBatch& b, hipStream_t s);
 // Fills p with NaN where *err is set (a sweep whose blocks gave up waiting).
 void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s);
 

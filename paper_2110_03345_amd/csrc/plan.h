@@ -13,6 +13,19 @@
 #include "common.h"
 #include "revolve.h"
 
+namespace stride {
+
+// Tiles of a 2D sweep kept on the chip (rs.tiles 0: not for this plan), and the
+// plan's points by tile.
+struct ResidentTables {
+    ResidentShape rs;
+    int slots;                          // shared: sweeps that fit the chip together
+    InjTable src, rec;
+    ResidentSamples rec_smp, src_smp;   // (out unset)
+};
+
+}  // namespace stride
+
 struct stride_plan {
     stride_grid_t g;
     int nd, R, nb, nt;
@@ -37,9 +50,8 @@ struct stride_plan {
     stride::InjTable rec_inj;    // receivers (adjoint injection), weights (blocks of ls_adj)
     stride::InjTable rec_inj_v;  // the same entries, blocks of ls_fwd
     stride::InjTable no_inj;     // no entries (blocks of any shape)
-    stride::ResidentShape rs;    // 2D sweeps kept on the chip (tiles 0: not for this plan)
-    stride::InjTable src_res, rec_res;           // sources / receivers by tile of rs
-    stride::ResidentSamples rec_smp, src_smp;    // sampling by tile of rs (out unset)
+    stride::ResidentTables res;      // 2D sweeps kept on the chip, one at a time
+    stride::ResidentTables shared;   // the same, several shots side by side
     const long long* rec_idx;
     const float* rec_w;          // receiver sampling
     const long long* src_idx;
@@ -108,6 +120,14 @@ struct GradPath {
     int vbuf = 0;                 // segmented: v fields (the longest segment)
     long long forward_steps = 0;  // forward step launches per gradient
 };
+
+inline long long phys_points(const stride_plan& P)
+{
+    long long n = 1;
+    for (int a = 0; a < P.nd; ++a)
+        n *= P.g.shape[a];
+    return n;
+}
 
 GradPath grad_path(const stride_plan& P, long long fields, int snaps);
 

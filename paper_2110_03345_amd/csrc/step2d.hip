@@ -7,50 +7,48 @@ namespace {
 #include "step2d_resident.h"
 
 template <int R, int MODE, int J>
-hipError_t resident_t(const Dims& d, const StencilCoef& cf, const SpongeCoef& sp,
-                      const ResidentShape& rs, const ResidentParams& p, hipStream_t s)
+hipError_t resident_t(const Dims& d, const StencilCoef& cf, const ResidentShape& rs,
+                      const ResidentBatch& b, hipStream_t s)
 {
     const void* k = reinterpret_cast<const void*>(step2d_resident<R, MODE, J>);
-    const int lds = resident_lds_bytes(R, rs, p.injects, MODE == kImageV);
+    const int lds = resident_lds_bytes(R, rs, b.p[0].injects, MODE == kImageV);
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess)
         return e;
     Dims d_ = d;
     StencilCoef cf_ = cf;
-    SpongeCoef sp_ = sp;
     ResidentShape rs_ = rs;
-    ResidentParams p_ = p;
-    void* args[] = {&d_, &cf_, &sp_, &rs_, &p_};
-    return hipLaunchCooperativeKernel(k, dim3((rs.tiles + kXcds - 1) / kXcds * kXcds),
+    ResidentBatch b_ = b;
+    void* args[] = {&d_, &cf_, &rs_, &b_};
+    return hipLaunchCooperativeKernel(k, dim3((b.n * rs.tiles + kXcds - 1) / kXcds * kXcds),
                                       dim3(kResidentThreads), args, (unsigned)lds, s);
 }
 
 template <int R>
-hipError_t resident_r(int mode, const Dims& d, const StencilCoef& cf, const SpongeCoef& sp,
-                      const ResidentShape& rs, const ResidentParams& p, hipStream_t s)
+hipError_t resident_r(int mode, const Dims& d, const StencilCoef& cf, const ResidentShape& rs,
+                      const ResidentBatch& b, hipStream_t s)
 {
     const bool one = rs.tx / 4 * rs.ty <= kResidentThreads;     // quads per thread
     switch (mode) {
     case kStep:
-        return one ? resident_t<R, kStep, 1>(d, cf, sp, rs, p, s)
-                   : resident_t<R, kStep, kResidentItems>(d, cf, sp, rs, p, s);
+        return one ? resident_t<R, kStep, 1>(d, cf, rs, b, s)
+                   : resident_t<R, kStep, kResidentItems>(d, cf, rs, b, s);
     case kStepV:
-        return one ? resident_t<R, kStepV, 1>(d, cf, sp, rs, p, s)
-                   : resident_t<R, kStepV, kResidentItems>(d, cf, sp, rs, p, s);
+        return one ? resident_t<R, kStepV, 1>(d, cf, rs, b, s)
+                   : resident_t<R, kStepV, kResidentItems>(d, cf, rs, b, s);
     default:
-        return one ? resident_t<R, kImageV, 1>(d, cf, sp, rs, p, s)
-                   : resident_t<R, kImageV, kResidentItems>(d, cf, sp, rs, p, s);
+        return one ? resident_t<R, kImageV, 1>(d, cf, rs, b, s)
+                   : resident_t<R, kImageV, kResidentItems>(d, cf, rs, b, s);
     }
 }
 
 }  // namespace
 
 hipError_t launch_resident(const Dims& d, int R, int mode, const StencilCoef& cf,
-                           const SpongeCoef& sp, const ResidentShape& rs, const ResidentParams& p,
-                           hipStream_t s)
+                           const ResidentShape& rs, const ResidentBatch& b, hipStream_t s)
 {
-    return R == 4 ? resident_r<4>(mode, d, cf, sp, rs, p, s)
-                  : resident_r<5>(mode, d, cf, sp, rs, p, s);
+    return R == 4 ? resident_r<4>(mode, d, cf, rs, b, s)
+                  : resident_r<5>(mode, d, cf, rs, b, s);
 }
 
 void launch_family_2d(bool adjoint, int R, int mode, const Dims& d, const StencilCoef& cf,

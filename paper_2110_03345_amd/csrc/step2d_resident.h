@@ -35,8 +35,7 @@ constexpr long long kResidentPatience = 400000000ll;
 
 template <int R, int MODE, int J>
 __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, StencilCoef cf,
-                                                                    SpongeCoef sp, ResidentShape rs,
-                                                                    ResidentParams p)
+                                                                    ResidentShape rs, ResidentBatch batch)
 {
     using V = StepVec<4>;
     using Word = unsigned long long;
@@ -51,9 +50,12 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
     __shared__ int tr[kResidentSampled];
     __shared__ float ey[kResidentSide];
     __shared__ __align__(16) float ex[kResidentSide];
-    const int tile = xcd_logical(blockIdx.x, gridDim.x);
-    if (tile >= rs.tiles)
+    const int block = xcd_logical(blockIdx.x, gridDim.x), slot = block / rs.tiles;
+    if (slot >= batch.n)
         return;
+    const int tile = block - slot * rs.tiles;
+    const ResidentParams& p = batch.p[slot];
+    const SpongeCoef sp = p.sp;
     const int tid = threadIdx.x;
     const int txq = rs.tx / 4, ty = rs.ty;
     const int W = rs.tx + 2 * HQ;
@@ -312,7 +314,8 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
         const float* S = buf + (t & 1) * area;
         float* Sn = buf + ((t + 1) & 1) * area;
         const bool more = t + 1 < p.count;
-        const bool exchange = more || p.sample_last;
+        // (a sweep of one step: before its blocks store the state others still load)
+        const bool exchange = more || p.sample_last || p.count == 1;
         Word* const out = mine + (t & 1) * parity;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
                     __hip_atomic_store(out + k * ws,
-                                       (Word)__float_as_uint(un[k]) | ((Word)(unsigned)(t + 1) << 32),
+                                       (Word)__float_as_uint(un[k]) | ((Word)(p.tag + t + 1) << 32),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             *(V*)&Sn[li] = un;
@@ -409,7 +412,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
         }
         if (exchange && hl >= 0) {
             const Word* w = hw + (t & 1) * parity;
-            const unsigned want = (unsigned)(t + 1);
+            const unsigned want = p.tag + t + 1;
             V v;
             long long since = 0;
             for (int tries = 0;; ++tries) {

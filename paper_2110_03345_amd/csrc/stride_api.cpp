@@ -321,9 +321,9 @@ HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
 }
 
 // By tile of the 2D sweeps kept on the chip.
-HostTiles build_resident(const stride_plan& P, const TapSet& taps, double scale)
+HostTiles build_resident(const stride_plan& P, const ResidentShape& rs, const TapSet& taps,
+                         double scale)
 {
-    const ResidentShape& rs = P.rs;
     return group_entries(taps, scale, rs.tiles, [&](const int* c) {
         const int ty = c[0] / rs.ty, tx = c[1] / rs.tx;
         return std::pair<size_t, int>((size_t)ty * rs.tiles_x + tx,
@@ -339,9 +339,9 @@ struct HostSamples {
     std::vector<float> w;
 };
 
-HostSamples build_resident_samples(const stride_plan& P, const TapSet& taps, double scale)
+HostSamples build_resident_samples(const stride_plan& P, const ResidentShape& rs,
+                                   const TapSet& taps, double scale)
 {
-    const ResidentShape& rs = P.rs;
     const size_t npts = taps.T ? taps.w.size() / taps.T : 0;
     const int before = P.g.interp == 1 ? kSincHalfWidth - 1 : 0;
     std::vector<std::vector<int>> per(rs.tiles);
@@ -373,34 +373,53 @@ HostSamples build_resident_samples(const stride_plan& P, const TapSet& taps, dou
 // the exchange, and fewer blocks wait for each other: at 240^2 1.76 us a step
 // with 80 x 48 tiles, 2.0 with 40 x 30; at 592^2 1.84 with 68 x 60, 2.6 with
 // 40 x 37); else two, in small tiles (a step is then mostly the items: at 1104^2
-// 2.35 us with 80 x 62, 2.5 with 92 x 69).
-ResidentShape choose_resident(const Dims& d, int R, int cus)
+// 2.35 us with 80 x 62, 2.5 with 92 x 69).  `shared`: the most steps per time of
+// several sweeps side by side (592^2: four on 56 tiles, 2.7 us a step of all
+// four; two on 100 tiles 1.9).
+struct ResidentChoice {
+    ResidentShape one{}, shared{};
+};
+
+ResidentChoice choose_resident(const Dims& d, int R, int cus)
 {
-    ResidentShape best{};
-    long long best_cost = 0;
+    ResidentChoice best;
+    long long one_cost = 0, shared_cost = 0;
+    double shared_rate = 0.0;
     const int hb = (R + 3) / 4;
     const int n0 = d.n[0], n1 = d.n[1];
+    const int tx_min = std::max(16, 8 * hb), ty_min = 2 * R;
     const long long field = round_up(d.total * 4, 256);
-    for (int tiles_x = 1; tiles_x <= cus; ++tiles_x) {
-        const int tx = std::max((int)round_up((n1 + tiles_x - 1) / tiles_x, 4), std::max(16, 8 * hb));
-        if ((n1 + tx - 1) / tx != tiles_x)
+    for (int tiles_x = 1; tiles_x <= std::min(cus, n1 / tx_min + 1); ++tiles_x) {
+        const int tx = std::max((int)round_up((n1 + tiles_x - 1) / tiles_x, 4), tx_min);
+        if (tx > kResidentSide || (n1 + tx - 1) / tx != tiles_x)
             continue;
-        for (int tiles_y = 1; tiles_x * tiles_y <= cus; ++tiles_y) {
-            const int ty = std::max((n0 + tiles_y - 1) / tiles_y, 2 * R);
-            if ((n0 + ty - 1) / ty != tiles_y || tx / 4 * ty > kResidentItems * kResidentThreads)
+        // from the fewest rows of tiles whose quads fit the threads
+        const int ty_max = std::min(kResidentItems * kResidentThreads / (tx / 4), kResidentSide);
+        for (int tiles_y = (n0 + ty_max - 1) / ty_max;
+             tiles_x * tiles_y <= cus && tiles_y <= n0 / ty_min + 1; ++tiles_y) {
+            const int ty = std::max((n0 + tiles_y - 1) / tiles_y, ty_min);
+            if (ty > ty_max || (n0 + ty - 1) / ty != tiles_y)
                 continue;
             const ResidentShape rs{tx, ty, tiles_x, tiles_y, tiles_x * tiles_y};
             const int nq = tx / 4 * ty;
             const int nh = 2 * R * (tx / 4 + 2 * hb) + 2 * hb * ty;
-            if (tx > kResidentSide || ty > kResidentSide || nh > kResidentThreads || resident_outer_quads(R, rs) > kResidentThreads ||
+            if (nh > kResidentThreads || resident_outer_quads(R, rs) > kResidentThreads ||
                 resident_lds_bytes(R, rs, true, true) > 155 * 1024 ||
                 resident_word_bytes(R, rs) > 2 * field)
                 continue;
-            const long long cost = nq <= kResidentThreads ? 5 * rs.tiles + 4 * nh - 2 * nq
-                                                          : (1 << 20) + 2 * nq + 2 * nh;
-            if (!best.tiles || cost < best_cost) {
-                best = rs;
-                best_cost = cost;
+            const bool single = nq <= kResidentThreads;
+            const long long cost = single ? 5 * rs.tiles + 4 * nh - 2 * nq
+                                          : (1 << 20) + 2 * nq + 2 * nh;
+            if (!best.one.tiles || cost < one_cost) {
+                best.one = rs;
+                one_cost = cost;
+            }
+            // sweeps per 1.85 us (one quad per thread) or 2.4 us (two)
+            const double rate = std::min(cus / rs.tiles, kResidentSlots) / (single ? 1.85 : 2.4);
+            if (rate > shared_rate || (rate == shared_rate && cost < shared_cost)) {
+                best.shared = rs;
+                shared_rate = rate;
+                shared_cost = cost;
             }
         }
     }
@@ -909,13 +928,14 @@ unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; 
 bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
                   hipStream_t s)
 {
-    if (!P.rs.tiles || p.count < 2)
+    if (!P.res.rs.tiles || p.count < 2)
         return false;
-    launch_fill(words, resident_word_bytes(P.R, P.rs) / 4, 0.f, s);
+    launch_fill(words, resident_word_bytes(P.R, P.res.rs) / 4, 0.f, s);
     p.words = reinterpret_cast<unsigned long long*>(words);
     p.err = err;
     p.injects = (mode == kImageV ? P.nrec : P.nsrc) > 0;
-    if (launch_resident(P.dims, P.R, mode, P.cf, P.sp, P.rs, p, s) == hipSuccess)
+    p.sp = P.sp;
+    if (launch_resident(P.dims, P.R, mode, P.cf, P.res.rs, ResidentBatch{1, {p}}, s) == hipSuccess)
         return true;
     (void)hipGetLastError();
     return false;
@@ -931,21 +951,13 @@ ResidentParams resident_forward(const stride_plan& P, const float* K, const floa
     p.step = n;
     p.dir = 1;
     p.count = count;
-    p.inj = P.src_res;
+    p.inj = P.res.src;
     p.inj_sig = wavelet;
     p.inj_stride = P.nt;
-    p.smp = P.rec_smp;
+    p.smp = P.res.rec_smp;
     p.smp.out = traces;
     p.sample_last = traces && last;
     return p;
-}
-
-long long phys_points(const stride_plan& P)
-{
-    long long n = 1;
-    for (int a = 0; a < P.nd; ++a)
-        n *= P.g.shape[a];
-    return n;
 }
 
 // The fields of a plan that workspace sizes and gradient paths depend on,
@@ -1138,10 +1150,10 @@ struct Runner {
         rp.step = e - 1;
         rp.dir = -1;
         rp.count = e - j;
-        rp.inj = P.rec_res;
+        rp.inj = P.res.rec;
         rp.inj_sig = grad_traces;
         rp.inj_stride = P.nt;
-        rp.smp = P.src_smp;
+        rp.smp = P.res.src_smp;
         rp.smp.out = dwavelet;
         if (e < P.nt) {
             rp.A = W.w[wa];
@@ -1511,7 +1523,7 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
         return rc;
     launch_prep_k(P.dims, vp, P.g.dt, k, s);
     const std::initializer_list<OutArray> outs = {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}};
-    if (P.rs.tiles) {
+    if (P.res.rs.tiles) {
         launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
         int id = g_timer.begin(s);
         if (run_resident(P, kStep, resident_forward(P, k, wavelet, 0, P.nt - 1, traces, true), u[0],
@@ -2214,13 +2226,18 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     P->ls_adj = make_shape(d, tya, chunk_planes(d, tya, true), rya, wa);
 
     // 2D leapfrog sweeps with the sponge may keep their state on the chip
-    P->rs = ResidentShape{};
+    P->res = P->shared = ResidentTables{};
     if (P->nd == 2 && P->torder == 2 && P->boundary == 0) {
         int dev = 0, cus = 0, coop = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop)
-            P->rs = choose_resident(d, P->R, cus);
+            hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop) {
+            const ResidentChoice c = choose_resident(d, P->R, cus);
+            P->res.rs = c.one;
+            P->shared.rs = c.shared;
+            if (c.shared.tiles)
+                P->shared.slots = std::min(cus / c.shared.tiles, kResidentSlots);
+        }
     }
 
     TapSet st, rt;
@@ -2233,14 +2250,6 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     HostTiles tsa = build_tiles(*P, st, 1.0 / P->cellvol, P->ls_adj);
     HostTiles tra = build_tiles(*P, rt, 1.0, P->ls_adj);
     HostTiles trv = build_tiles(*P, rt, 1.0, P->ls_fwd);
-    HostTiles tss, tsr;
-    HostSamples hrs, hss;
-    if (P->rs.tiles) {
-        tss = build_resident(*P, st, 1.0 / P->cellvol);
-        tsr = build_resident(*P, rt, 1.0);
-        hrs = build_resident_samples(*P, rt, 1.0);
-        hss = build_resident_samples(*P, st, 1.0 / P->cellvol);
-    }
     std::vector<long long> ridx, sidx;
     std::vector<float> rw, sw;
     flatten_sample(rt, 1.0, ridx, rw);
@@ -2268,18 +2277,32 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     size_t o_tra_ent = add(tra.ent.data(), tra.ent.size(), sizeof(TileEntry));
     size_t o_trv_ptr = add(trv.ptr.data(), trv.ptr.size(), 4);
     size_t o_trv_ent = add(trv.ent.data(), trv.ent.size(), sizeof(TileEntry));
-    size_t o_res[12];
-    {
-        int i = 0;
-        for (const HostTiles* t : {&tss, &tsr}) {
-            o_res[i++] = add(t->ptr.data(), t->ptr.size(), 4);
-            o_res[i++] = add(t->ent.data(), t->ent.size(), sizeof(TileEntry));
+    struct ResidentHost {
+        ResidentTables* t;
+        HostTiles src, rec;
+        HostSamples rec_smp, src_smp;
+        size_t off[12];
+    };
+    std::vector<ResidentHost> resident;
+    if (P->res.rs.tiles)
+        resident.push_back({&P->res, {}, {}, {}, {}, {}});
+    if (P->shared.rs.tiles)
+        resident.push_back({&P->shared, {}, {}, {}, {}, {}});
+    for (ResidentHost& h : resident) {
+        h.src = build_resident(*P, h.t->rs, st, 1.0 / P->cellvol);
+        h.rec = build_resident(*P, h.t->rs, rt, 1.0);
+        h.rec_smp = build_resident_samples(*P, h.t->rs, rt, 1.0);
+        h.src_smp = build_resident_samples(*P, h.t->rs, st, 1.0 / P->cellvol);
+        size_t* o = h.off;
+        for (const HostTiles* t : {&h.src, &h.rec}) {
+            *o++ = add(t->ptr.data(), t->ptr.size(), 4);
+            *o++ = add(t->ent.data(), t->ent.size(), sizeof(TileEntry));
         }
-        for (const HostSamples* h : {&hrs, &hss}) {
-            o_res[i++] = add(h->ptr.data(), h->ptr.size(), 4);
-            o_res[i++] = add(h->id.data(), h->id.size(), 4);
-            o_res[i++] = add(h->idx.data(), h->idx.size(), 4);
-            o_res[i++] = add(h->w.data(), h->w.size(), 4);
+        for (const HostSamples* t : {&h.rec_smp, &h.src_smp}) {
+            *o++ = add(t->ptr.data(), t->ptr.size(), 4);
+            *o++ = add(t->id.data(), t->id.size(), 4);
+            *o++ = add(t->idx.data(), t->idx.size(), 4);
+            *o++ = add(t->w.data(), t->w.size(), 4);
         }
     }
     std::vector<int> none(
@@ -2307,14 +2330,16 @@ int stride_plan_create(const stride_grid_t* grid, int32_t nsrc, const double* sr
     P->rec_inj_v = InjTable{(const int*)(B + o_trv_ptr), (const TileEntry*)(B + o_trv_ent)};
     P->no_inj = InjTable{(const int*)(B + o_none), (const TileEntry*)(B + o_tra_ent)};
 
-    P->src_res = InjTable{(const int*)(B + o_res[0]), (const TileEntry*)(B + o_res[1])};
-    P->rec_res = InjTable{(const int*)(B + o_res[2]), (const TileEntry*)(B + o_res[3])};
     auto samples = [&](const size_t* o) {
         return ResidentSamples{(const int*)(B + o[0]), (const int*)(B + o[1]), (const int*)(B + o[2]),
                                (const float*)(B + o[3]), nullptr, P->nt, P->ntap};
     };
-    P->rec_smp = samples(o_res + 4);
-    P->src_smp = samples(o_res + 8);
+    for (const ResidentHost& h : resident) {
+        h.t->src = InjTable{(const int*)(B + h.off[0]), (const TileEntry*)(B + h.off[1])};
+        h.t->rec = InjTable{(const int*)(B + h.off[2]), (const TileEntry*)(B + h.off[3])};
+        h.t->rec_smp = samples(h.off + 4);
+        h.t->src_smp = samples(h.off + 8);
+    }
 
     P->rec_idx = (const long long*)(B + o_ridx);
     P->rec_w = (const float*)(B + o_rw);

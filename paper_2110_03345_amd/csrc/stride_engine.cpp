@@ -15,7 +15,9 @@
 // pinned staging table (double-buffered; active entries packed from row 0 so
 // launches cover only occupied rows), copies it to the device, and replays a
 // hipGraph of the chunk's launches (captured once per chunk length and launch
-// heights).  Chunks have a fixed length; a slot whose phase ends inside one
+// heights).  2D slots whose chunk is one sweep of leapfrog steps (forward
+// solves and full histories) don't tick: one launch runs the chunk's steps of
+// several such slots side by side, their states kept on the chip.  Chunks have a fixed length; a slot whose phase ends inside one
 // idles to its end.  Phase transitions run as ordinary launches at chunk
 // boundaries: the last trace sample, the residual and misfit, and the
 // gradient finalise.  A shot's arithmetic is the single-shot kernels' body,
@@ -73,6 +75,7 @@ struct SlotJob {
     int phase = 0;                       // gradient: 0 forward sweep, 1 recompute + adjoint
     int m = 0;                           // full-history / segmented adjoint: next step
     int wa = 0;                          // adjoint ping-pong
+    int imaged = 0;                      // adjoint: first step whose term a sweep kept on the chip added
     long long left = 0;                  // ticks until the current phase ends
     // segmented history: segment starts, v buffer pool[0, vbuf), working pair
     // pool[vbuf], pool[vbuf + 1], start state of segment k in pool[vbuf + 2k],
@@ -116,6 +119,9 @@ struct stride_engine {
     int stage_i = 0;
     std::map<std::array<int, kGroups + 1>, hipGraphExec_t> execs;   // (ticks, launch heights)
     long long ticks_total = 0;
+    unsigned long long* words = nullptr;   // exchange area of the sweeps kept on the chip
+    unsigned tag = 0;                      // highest step number in it
+    unsigned* late = nullptr;              // pinned: blocks of such a sweep gave up waiting
 
     int tick_rows() const { return group_off[kGroups]; }
 };
@@ -192,7 +198,7 @@ void adjoint_v_row(const stride_plan& P, TickRows& R, SlotJob& J, int m, int j, 
     c.inj_stride = P.nt;
     c.img = P.no_inj;
     c.V = J.W.pool[m - j];
-    c.V2 = m + 1 < e ? J.W.pool[m + 1 - j] : nullptr;
+    c.V2 = m + 1 < e && m + 1 != J.imaged ? J.W.pool[m + 1 - j] : nullptr;
     R.add(m % 2 == 0 ? kGAdjImage : kGAdjPlain, make_row(P, c));
     J.wa = 1 - J.wa;
 }
@@ -396,6 +402,130 @@ int get_exec(stride_engine* E, int ticks, const int* gy, hipStream_t s, hipGraph
     return STRIDE_OK;
 }
 
+// Shortest chunk worth launches of its own: at 592^2 eight steps of four slots
+// take about 35 us (launch, state in and out), as ticks 55.
+constexpr int kResidentChunk = 8;
+
+// The next `count` ticks of a slot as one sweep kept on the chip: forward solves
+// and full histories of second order in time.  False: they run as ticks.
+bool resident_sweep(const stride_engine* E, SlotJob& J, int count, int* mode, ResidentParams& p)
+{
+    const stride_plan& P = *J.P;
+    const ResidentTables& T = P.shared;
+    if (!T.rs.tiles || T.rs.tx != E->shape_plan->shared.rs.tx ||
+        T.rs.ty != E->shape_plan->shared.rs.ty || P.torder != 2 || J.seg || count < kResidentChunk)
+        return false;
+    p = ResidentParams{};
+    p.sp = P.sp;
+    p.inj_stride = P.nt;
+    p.count = count;
+    float *a, *b;
+    if (J.mode == STRIDE_MODE_FORWARD || (J.history && J.phase == 0)) {
+        const bool keep = J.mode != STRIDE_MODE_FORWARD;
+        *mode = keep ? kStepV : kStep;
+        float* const* u = keep ? J.W.w : J.F.u;
+        a = u[J.cur];
+        b = u[1 - J.cur];
+        p.K = keep ? J.W.k : J.F.k;
+        p.dir = 1;
+        p.step = J.n;
+        p.inj = T.src;
+        p.inj_sig = J.wavelet;
+        p.smp = T.rec_smp;
+        p.smp.out = keep ? J.W.traces : J.traces;
+        if (keep) {
+            p.V = J.W.pool[J.n];
+            p.vstride = J.W.pool[1] - J.W.pool[0];
+        }
+        p.injects = P.nsrc > 0;
+    } else {
+        // a pair begun by an odd step's tick ends as ticks
+        if (!J.history || (J.m % 2 == 0 && J.m != P.nt - 1 && J.imaged != J.m + 1))
+            return false;
+        *mode = kImageV;
+        a = J.W.w[J.wa];
+        b = J.W.w[1 - J.wa];
+        p.K = J.W.k;
+        p.G = J.W.G;
+        p.V = J.W.pool[J.m];
+        p.vstride = J.W.pool[0] - J.W.pool[1];
+        p.dir = -1;
+        p.step = J.m;
+        p.inj = T.rec;
+        p.inj_sig = J.W.residual;
+        p.injects = P.nrec > 0;
+    }
+    // in place: a block stores its part of the states after its neighbours have
+    // loaded their frames
+    p.A = p.A2 = a;
+    p.B = p.B2 = b;
+    return true;
+}
+
+// Runs what resident_sweep takes of the active slots' next `ticks` ticks; used[j]
+// counts the ticks it ran of slot j.
+int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStream_t s)
+{
+    if (!E->words)
+        return STRIDE_OK;
+    const ResidentShape& rs = E->shape_plan->shared.rs;
+    const long long area = resident_word_bytes(E->R, rs) / 8;
+    struct Sweep {
+        int slot;
+        ResidentParams p;
+    };
+    std::array<std::vector<Sweep>, kImageV + 1> sweeps;
+    for (int j = 0; j < E->max_slots; ++j) {
+        SlotJob& J = E->slots[j];
+        int mode;
+        Sweep w{j, {}};
+        if (J.used && !J.finished &&
+            resident_sweep(E, J, (int)std::min<long long>(ticks, J.left), &mode, w.p))
+            sweeps[mode].push_back(w);
+    }
+    for (int mode : {kStep, kStepV, kImageV}) {
+        const std::vector<Sweep>& v = sweeps[mode];
+        bool injects = false;
+        for (const Sweep& w : v)
+            injects = injects || w.p.injects;
+        const size_t per = (size_t)E->shape_plan->shared.slots;
+        const size_t launches = (v.size() + per - 1) / per;
+        for (size_t l = 0; l < launches; ++l) {
+            const size_t from = l * v.size() / launches, to = (l + 1) * v.size() / launches;
+            if (E->tag > 0x7fffffffu) {
+                launch_fill((float*)E->words, 2 * area * per, 0.f, s);
+                E->tag = 0;
+            }
+            ResidentBatch b{};
+            for (size_t i = from; i < to; ++i) {
+                ResidentParams& p = b.p[b.n];
+                p = v[i].p;
+                p.injects = injects;
+                p.words = E->words + (long long)b.n++ * area;
+                p.tag = E->tag;
+                p.err = E->late;
+            }
+            if (launch_resident(E->dims, E->R, mode, E->cf, rs, b, s) != hipSuccess) {
+                (void)hipGetLastError();
+                return STRIDE_OK;       // refused: these ticks run as ticks
+            }
+            E->tag += (unsigned)ticks;
+            for (size_t i = from; i < to; ++i) {
+                SlotJob& J = E->slots[v[i].slot];
+                const int count = v[i].p.count;
+                used[v[i].slot] = count;
+                if (mode == kImageV) {
+                    J.m -= count;
+                    J.imaged = J.m + 1;
+                } else {
+                    J.n += count;
+                }
+            }
+        }
+    }
+    return STRIDE_OK;
+}
+
 // Ticks of a gradient's second phase (recomputation and adjoint).
 long long second_phase_ticks(const SlotJob& J)
 {
@@ -408,10 +538,12 @@ long long second_phase_ticks(const SlotJob& J)
 // Work between phases, enqueued after the chunk that ended the phase.
 void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
 {
-    (void)E;
     const stride_plan& P = *J.P;
+    const long long ntraces = (long long)P.nrec * P.nt;
     if (J.mode == STRIDE_MODE_FORWARD) {
         launch_sample(rec_samples(P, J.traces), J.F.u[J.cur], P.nt - 1, s);
+        if (E->words)
+            launch_poison(E->late, J.traces, ntraces, s);
         J.finished = true;
         return;
     }
@@ -447,12 +579,19 @@ void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
             J.wa = 0;
         }
         J.phase = 1;
+        J.imaged = P.nt;
         J.left = second_phase_ticks(J);
         return;
     }
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, J.W.G, P.torder == 4 ? J.W.k : nullptr, J.vp, J.dvp, J.W.w[0],
                         J.W.w[1], s);
+    if (E->words) {
+        launch_poison(E->late, J.dvp, phys_points(P), s);
+        launch_poison(E->late, (float*)J.misfit, 2, s);
+        if (J.traces)
+            launch_poison(E->late, J.traces, ntraces, s);
+    }
     J.finished = true;
 }
 
@@ -495,6 +634,19 @@ int stride_engine_create(const stride_grid_t* grid, int32_t max_slots, int32_t m
         if (e == hipSuccess)
             e = hipEventCreateWithFlags(&E->stage_ev[i], hipEventDisableTiming);
     }
+    const ResidentTables& T = sp->shared;
+    if (e == hipSuccess && T.slots > 0) {
+        // exchange words start at zero; later sweeps number their steps on
+        const size_t area = (size_t)resident_word_bytes(E->R, T.rs) * T.slots;
+        e = hipMalloc((void**)&E->words, area);
+        if (e == hipSuccess)
+            e = hipHostMalloc((void**)&E->late, sizeof(unsigned), hipHostMallocDefault);
+        if (e == hipSuccess) {
+            *E->late = 0;
+            launch_fill((float*)E->words, (long long)area / 4, 0.f, nullptr);
+            e = hipStreamSynchronize(nullptr);
+        }
+    }
     if (e != hipSuccess) {
         stride_engine_destroy(E);
         return fail(STRIDE_E_HIP, "engine allocation: %s", hipGetErrorString(e));
@@ -518,6 +670,10 @@ int stride_engine_destroy(stride_engine_t* E)
     }
     if (E->d_table)
         (void)hipFree(E->d_table);
+    if (E->words)
+        (void)hipFree(E->words);
+    if (E->late)
+        (void)hipHostFree(E->late);
     if (E->shape_plan)
         stride_plan_destroy(E->shape_plan);
     delete E;
@@ -636,6 +792,14 @@ int stride_engine_run(stride_engine_t* E, int32_t max_ticks, void* stream, int32
     if (ticks > cap)
         ticks /= 2;
 
+    if (E->late && *(volatile unsigned*)E->late)
+        return fail(STRIDE_E_HIP, "the blocks of a 2D sweep were not resident together");
+    std::vector<long long> used_ticks(E->max_slots, 0);
+    int rc = run_sweeps(E, ticks, used_ticks, s);
+    if (rc)
+        return rc;
+    const std::vector<long long> swept = used_ticks;
+
     // per-tick slot tables, each group's active rows packed from its first
     // row, in the pinned staging buffer
     int si = E->stage_i;
@@ -646,7 +810,6 @@ int stride_engine_run(stride_engine_t* E, int32_t max_ticks, void* stream, int32
     size_t bytes = sizeof(SlotStep) * (size_t)ticks * per_tick;
     int rows[kGroups] = {};
     std::vector<int> counts((size_t)ticks * kGroups, 0);
-    std::vector<long long> used_ticks(E->max_slots, 0);
     for (int t = 0; t < ticks; ++t) {
         SlotStep* tick = H + (size_t)t * per_tick;
         TickRows R;
@@ -656,9 +819,9 @@ int stride_engine_run(stride_engine_t* E, int32_t max_ticks, void* stream, int32
         }
         for (int j = 0; j < E->max_slots; ++j) {
             SlotJob& J = E->slots[j];
-            if (!J.used || J.finished || used_ticks[j] >= J.left)
+            if (!J.used || J.finished || swept[j] || used_ticks[j] >= J.left)
                 continue;
-            int rc = fill_tick(J, R);
+            rc = fill_tick(J, R);
             if (rc)
                 return rc;
             ++used_ticks[j];
@@ -687,19 +850,21 @@ int stride_engine_run(stride_engine_t* E, int32_t max_ticks, void* stream, int32
                 std::memset((void*)(r + c), 0, sizeof(SlotStep) * (size_t)(h - c));
         }
     }
-    STRIDE_HIP_TRY(hipMemcpyAsync(E->d_table, H, bytes, hipMemcpyHostToDevice, s));
+    const bool any = *std::max_element(rows, rows + kGroups) > 0;
+    if (any)
+        STRIDE_HIP_TRY(hipMemcpyAsync(E->d_table, H, bytes, hipMemcpyHostToDevice, s));
     STRIDE_HIP_TRY(hipEventRecord(E->stage_ev[si], s));
     E->stage_used[si] = true;
     E->stage_i = 1 - si;
-
-    if (E->graphs && s != nullptr) {
-        hipGraphExec_t x = nullptr;
-        int rc = get_exec(E, ticks, gy, s, &x);
-        if (rc)
-            return rc;
-        STRIDE_HIP_TRY(hipGraphLaunch(x, s));
-    } else {
-        launch_chunk(E, ticks, gy, s);
+    if (any) {
+        if (E->graphs && s != nullptr) {
+            hipGraphExec_t x = nullptr;
+            if ((rc = get_exec(E, ticks, gy, s, &x)))
+                return rc;
+            STRIDE_HIP_TRY(hipGraphLaunch(x, s));
+        } else {
+            launch_chunk(E, ticks, gy, s);
+        }
     }
     for (int j = 0; j < E->max_slots; ++j) {
         SlotJob& J = E->slots[j];

@@ -522,7 +522,7 @@ __global__ void poison_kernel(const unsigned* err, float* p, long long n)
         return;
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x)
-        p[i] = __uint_as_float(0x7fc00000u);
+        p[i] = __uint_as_float(0x7fffffffu);   // (two of them: a double NaN)
 }
 
 void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s)

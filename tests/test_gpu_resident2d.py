@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2110_03345_amd as S
+    from paper_2110_03345_amd import _abi
 
 TOL = 1e-4
 # interior shape, layer, order, steps, interp; padded widths of every remainder by four
@@ -59,3 +60,41 @@ def test_resident_sweeps(shape, nb, order, nt, interp):
         check_traces(tr.cpu().numpy(), ref, TOL)
         check_field(dvp.cpu().numpy(), dref, TOL)
         assert rel(dwav.cpu().numpy(), wref) < TOL
+
+
+@pytest.mark.parametrize("shape,nshots", [((70, 85), 14), ((300, 333), 5), ((611, 590), 3)],
+                         ids=lambda v: str(v).replace(" ", ""))
+@pytest.mark.parametrize("ticks", [[64], [8, 1, 16, 2], [1, 64, 4]], ids=str)
+def test_engine_sweeps(shape, nshots, ticks):
+    """Slots whose chunks run as sweeps, as ticks and as both, more of them than
+    one launch takes: the bits of the single-shot solves."""
+    nt, rng = 75, np.random.default_rng(nshots)
+    w = W.tiny_2d(n=shape, nt=nt, nb=6, nrec=40)
+    eng = _abi.stride_engine_create(S.make_grid(**w.grid_kwargs()), nshots, 64, 64, True)
+    stream = torch.cuda.Stream()
+    jobs = []
+    for i in range(nshots):
+        w.src_xyz = rng.uniform(0.2, 0.8, (2, 2)) * [(n - 1) * w.spacing for n in shape]
+        plan = S.Plan.from_workload(w)
+        vp, wav = dev(w.vp), dev(rng.standard_normal((2, nt)))
+        obs, tr = dev(rng.standard_normal((40, nt))), torch.empty((40, nt), device="cuda")
+        mis, dvp = torch.zeros(1, dtype=torch.float64, device="cuda"), torch.empty_like(vp)
+        mode = S.STRIDE_MODE_FORWARD if i % 3 == 1 else S.STRIDE_MODE_GRADIENT
+        ws = plan.workspace(mode)
+        torch.cuda.synchronize()
+        _abi.stride_engine_attach(eng, plan.handle, mode, vp, float(w.vp.max()), wav, obs, tr, mis,
+                                  dvp, ws, stream)
+        jobs.append((plan, mode, vp, wav, obs, tr, mis, dvp, ws))
+    done, k = 0, 0
+    while done < nshots:
+        done += len(_abi.stride_engine_run(eng, ticks[k % len(ticks)], nshots, stream)[1])
+        k += 1
+    stream.synchronize()
+    _abi.stride_engine_destroy(eng)
+    for plan, mode, vp, wav, obs, tr, mis, dvp, _ in jobs:
+        if mode == S.STRIDE_MODE_FORWARD:
+            assert torch.equal(plan.forward(vp, wav), tr)
+            continue
+        t1 = torch.empty_like(tr)
+        m1, d1 = plan.gradient(vp, wav, obs, traces=t1)
+        assert torch.equal(t1, tr) and torch.equal(m1, mis) and torch.equal(d1, dvp)
