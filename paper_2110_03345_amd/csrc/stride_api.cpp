@@ -273,30 +273,42 @@ template <class Place>
 HostTiles group_entries(const TapSet& taps, double scale, int blocks, Place place)
 {
     HostTiles T;
-    const size_t npts = taps.T ? taps.w.size() / taps.T : 0;
-    std::vector<std::vector<TileEntry>> per(blocks);
-    for (size_t p = 0; p < npts; ++p)
-        for (int t = 0; t < taps.T; ++t) {
-            const size_t k = p * taps.T + t;
-            if (taps.w[k] == 0.0)
-                continue;
-            const std::pair<size_t, int> at = place(&taps.coord[k * 3]);
-            per[at.first].push_back(TileEntry{at.second, 0, (int)p, (float)(taps.w[k] * scale)});
-        }
+    const size_t n = taps.w.size();
+    std::vector<TileEntry> all;
+    std::vector<int> block;
+    all.reserve(n);
+    block.reserve(n);
     T.ptr.assign(blocks + 1, 0);
+    for (size_t k = 0; k < n; ++k) {
+        if (taps.w[k] == 0.0)
+            continue;
+        const std::pair<size_t, int> at = place(&taps.coord[k * 3]);
+        all.push_back(TileEntry{at.second, 0, (int)(k / taps.T), (float)(taps.w[k] * scale)});
+        block.push_back((int)at.first);
+        ++T.ptr[at.first + 1];
+    }
+    for (int t = 0; t < blocks; ++t)
+        T.ptr[t + 1] += T.ptr[t];
+    T.ent.resize(all.size());
+    std::vector<int> next(T.ptr.begin(), T.ptr.end() - 1);
+    for (size_t i = 0; i < all.size(); ++i)
+        T.ent[next[block[i]]++] = all[i];
     for (int t = 0; t < blocks; ++t) {
-        auto& v = per[t];
-        std::stable_sort(v.begin(), v.end(),
-                         [](const TileEntry& a, const TileEntry& b) { return a.local < b.local; });
-        for (size_t i = 0; i < v.size();) {
-            size_t j = i;
-            while (j < v.size() && v[j].local == v[i].local)
+        TileEntry* v = T.ent.data() + T.ptr[t];
+        const int m = T.ptr[t + 1] - T.ptr[t];
+        if (m > 1 && !std::is_sorted(v, v + m, [](const TileEntry& a, const TileEntry& b) {
+                return a.local < b.local;
+            }))
+            std::stable_sort(v, v + m, [](const TileEntry& a, const TileEntry& b) {
+                return a.local < b.local;
+            });
+        for (int i = 0; i < m;) {
+            int j = i;
+            while (j < m && v[j].local == v[i].local)
                 ++j;
-            v[i].run = (int)(j - i);
+            v[i].run = j - i;
             i = j;
         }
-        T.ptr[t + 1] = T.ptr[t] + (int)v.size();
-        T.ent.insert(T.ent.end(), v.begin(), v.end());
     }
     return T;
 }
@@ -344,23 +356,29 @@ HostSamples build_resident_samples(const stride_plan& P, const ResidentShape& rs
 {
     const size_t npts = taps.T ? taps.w.size() / taps.T : 0;
     const int before = P.g.interp == 1 ? kSincHalfWidth - 1 : 0;
-    std::vector<std::vector<int>> per(rs.tiles);
     auto home = [&](size_t p, int a) { return taps.coord[p * taps.T * 3 + a] + before; };
-    for (size_t p = 0; p < npts; ++p)
-        per[(size_t)(home(p, 0) / rs.ty) * rs.tiles_x + home(p, 1) / rs.tx].push_back((int)p);
+    std::vector<int> tile(npts);
     HostSamples S;
     S.ptr.assign(rs.tiles + 1, 0);
-    for (int t = 0; t < rs.tiles; ++t) {
+    for (size_t p = 0; p < npts; ++p) {
+        tile[p] = home(p, 0) / rs.ty * rs.tiles_x + home(p, 1) / rs.tx;
+        ++S.ptr[tile[p] + 1];
+    }
+    for (int t = 0; t < rs.tiles; ++t)
+        S.ptr[t + 1] += S.ptr[t];
+    S.id.resize(npts);
+    S.idx.resize(npts * taps.T);
+    S.w.resize(npts * taps.T);
+    std::vector<int> next(S.ptr.begin(), S.ptr.end() - 1);
+    for (size_t p = 0; p < npts; ++p) {
+        const int t = tile[p], i = next[t]++;
         const int y0 = t / rs.tiles_x * rs.ty, x0 = t % rs.tiles_x * rs.tx;
-        for (int p : per[t]) {
-            S.id.push_back(p);
-            for (int k = 0; k < taps.T; ++k) {
-                const size_t q = (size_t)p * taps.T + k;
-                S.idx.push_back(resident_index(P.R, rs, taps.coord[q * 3] - y0, taps.coord[q * 3 + 1] - x0));
-                S.w.push_back((float)(taps.w[q] * scale));
-            }
+        S.id[i] = (int)p;
+        for (int k = 0; k < taps.T; ++k) {
+            const size_t q = p * taps.T + k, o = (size_t)i * taps.T + k;
+            S.idx[o] = resident_index(P.R, rs, taps.coord[q * 3] - y0, taps.coord[q * 3 + 1] - x0);
+            S.w[o] = (float)(taps.w[q] * scale);
         }
-        S.ptr[t + 1] = (int)S.id.size();
     }
     return S;
 }

@@ -119,7 +119,7 @@ struct stride_engine {
     int stage_i = 0;
     std::map<std::array<int, kGroups + 1>, hipGraphExec_t> execs;   // (ticks, launch heights)
     long long ticks_total = 0;
-    unsigned long long* words = nullptr;   // exchange area of the sweeps kept on the chip
+    unsigned long long* words = nullptr;   // exchange area of the sweeps kept on the chip (or none)
     unsigned tag = 0;                      // highest step number in it
     unsigned* late = nullptr;              // pinned: blocks of such a sweep gave up waiting
 
@@ -627,25 +627,24 @@ int stride_engine_create(const stride_grid_t* grid, int32_t max_slots, int32_t m
     E->slots.resize(max_slots);
     for (int g = 0; g < kGroups; ++g)
         E->group_off[g + 1] = E->group_off[g] + group_rows(g, max_slots);
-    size_t bytes = sizeof(SlotStep) * (size_t)E->tmax * E->tick_rows();
-    hipError_t e = hipMalloc((void**)&E->d_table, bytes);
+    // behind the tables: the exchange area on the device (zero at the start; later
+    // sweeps number their steps on) and the late flag in pinned memory
+    const ResidentTables& T = sp->shared;
+    const size_t bytes = sizeof(SlotStep) * (size_t)E->tmax * E->tick_rows();
+    const size_t table = (bytes + 255) / 256 * 256;
+    const size_t area = T.slots > 0 ? (size_t)resident_word_bytes(E->R, T.rs) * T.slots : 0;
+    hipError_t e = hipMalloc((void**)&E->d_table, table + area);
     for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-        e = hipHostMalloc((void**)&E->h_stage[i], bytes, hipHostMallocDefault);
+        e = hipHostMalloc((void**)&E->h_stage[i], table + 64, hipHostMallocDefault);
         if (e == hipSuccess)
             e = hipEventCreateWithFlags(&E->stage_ev[i], hipEventDisableTiming);
     }
-    const ResidentTables& T = sp->shared;
-    if (e == hipSuccess && T.slots > 0) {
-        // exchange words start at zero; later sweeps number their steps on
-        const size_t area = (size_t)resident_word_bytes(E->R, T.rs) * T.slots;
-        e = hipMalloc((void**)&E->words, area);
-        if (e == hipSuccess)
-            e = hipHostMalloc((void**)&E->late, sizeof(unsigned), hipHostMallocDefault);
-        if (e == hipSuccess) {
-            *E->late = 0;
-            launch_fill((float*)E->words, (long long)area / 4, 0.f, nullptr);
-            e = hipStreamSynchronize(nullptr);
-        }
+    if (e == hipSuccess && area) {
+        E->words = (unsigned long long*)((char*)E->d_table + table);
+        E->late = (unsigned*)((char*)E->h_stage[0] + table);
+        *E->late = 0;
+        launch_fill((float*)E->words, (long long)area / 4, 0.f, nullptr);
+        e = hipStreamSynchronize(nullptr);
     }
     if (e != hipSuccess) {
         stride_engine_destroy(E);
@@ -670,10 +669,6 @@ int stride_engine_destroy(stride_engine_t* E)
     }
     if (E->d_table)
         (void)hipFree(E->d_table);
-    if (E->words)
-        (void)hipFree(E->words);
-    if (E->late)
-        (void)hipHostFree(E->late);
     if (E->shape_plan)
         stride_plan_destroy(E->shape_plan);
     delete E;
