@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
     bool damped[J];
     auto place_of = [&](int rq) { return ((rq >> 16) + R) * W + HQ + 4 * (rq & 0xffff); };
     auto field_of = [&](int rq) {
-        return rq < 0 ? -1 : ((y0 + (rq >> 16)) * s0 + x0 + 4 * (rq & 0xffff)) * 4;
+        return rq < 0 ? kNoByte : ((y0 + (rq >> 16)) * s0 + x0 + 4 * (rq & 0xffff)) * 4;
     };
     auto place = [&](int j) { return LEAN ? place_of(rq[j]) : li_[j]; };
     auto field = [&](int j) { return LEAN ? field_of(rq[j]) : bo_[j]; };

@@ -32,6 +32,11 @@
 template <int VX>
 using StepVec = float __attribute__((ext_vector_type(VX)));
 
+// Byte offset of a vector outside any field or plane (their sizes are multiples
+// of 64 below 2^31).  Not -1: the compiler narrows a load of which only some
+// values are used, and -1 plus their offset wraps round into the field.
+constexpr int kNoByte = 0x7ffffff0;
+
 template <int VX, int AUX>
 __device__ __forceinline__ StepVec<VX> bloadv(__amdgpu_buffer_rsrc_t r, int byte_off)
 {
@@ -117,7 +122,7 @@ __device__ __forceinline__ void step3d_body(const Dims& d, const StencilCoef& cf
 
     // plane-independent geometry: byte offsets within a plane (-1 = outside)
     const int plane_bytes = (int)(s0 * 4);
-    const int bo = gx < n2 && gy < n1 ? (gy * s1 + gx) * 4 : -1;
+    const int bo = gx < n2 && gy < n1 ? (gy * s1 + gx) * 4 : kNoByte;
     const int lo = (row + R) * LW + col + HQ;       // own points in the LDS tile
     float ey[VX];
     {
@@ -135,7 +140,7 @@ __device__ __forceinline__ void step3d_body(const Dims& d, const StencilCoef& cf
     for (int h = 0; h < HL; ++h) {
         const int i = tid + h * NT;
         hl[h] = -1;
-        ho[h] = -1;
+        ho[h] = kNoByte;
         hx[h] = 0;
         if (i < NH) {
             int ly, lx;

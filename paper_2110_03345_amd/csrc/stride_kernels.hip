@@ -560,14 +560,16 @@ void launch_finite_scan(const double* p, long long n, unsigned* flag, unsigned b
 // Perfectly matched layer.  Per axis a whose layer holds a point (zeta_a > 0):
 //   chi_a = E chi_a + (1 - E) (D2_a u - D_a psi_a),  psi_a' = E psi_a + (1 - E) D_a u,
 // and u^{n+1} += k sum_a (-D_a psi_a - chi_a), the axes taken in order 0, 1, 2.
-// Neighbours beyond the padded array read 0.  One thread per point of the
-// layer, over three launches of 64-lane rows (no index division): the planes
-// of axis 0 in its layer (3D), then within the physical planes the rows of
-// axis 1 in its layer, then within the physical rows the points of axis 2 in
-// its layer.  Blocks are 4 rows; in the first launch the rows of a block are 4
-// consecutive planes and consecutive blocks continue along axis 0, so the 2R
-// axis-0 neighbours a point reads come from the same or a neighbouring block
-// (L2) rather than from a plane's distance away in the launch.
+// Neighbours beyond the padded array read 0.  A thread corrects four points of a
+// row, in one launch over three ranges of blocks: the planes of axis 0 in its
+// layer (3D), then within the physical planes the rows of axis 1 in its layer,
+// then within the physical rows the quads that touch axis 2's layer.  The waves
+// of a block are consecutive planes (first range) or rows (second) of the same
+// columns, which keeps most neighbours in L1.  At 220^3 with a layer of 30: 88 us
+// a step (110 with a thread per point and a launch per range); L1 then waits on
+// lines still on their way to it for 40% of the time, the vector units are busy
+// for 30%, and two to sixteen waves to a block or fewer loads in flight make no
+// difference.
 struct PmlGeom {
     int nn[3];        // 3D-ised padded extents (axis 0 of a 2D grid has extent 1)
     int st[3];        // strides in floats (pitched rows)
@@ -577,101 +579,211 @@ struct PmlGeom {
     int three;
 };
 
-template <int R>
+using PmlVec = StepVec<4>;
+
+// A quad of a layer: its plane (uniform over the wave), row, first column and
+// byte offset in the plane.
+struct PmlAt {
+    long long plane;     // element offset of the plane
+    int plane_bytes;
+    int i0, i1, i2;
+    int off;
+};
+
+__device__ __forceinline__ int pml_depth(const PmlGeom& g, int ax, int i)
+{
+    const int b = ax == 0 ? g.b0 : g.b, hi = b + g.pl[ax] - 1;
+    return i < b ? b - i : (i > hi ? i - hi : 0);
+}
+
+__device__ __forceinline__ float pml_decay(const PmlGeom& g, const PmlParams& pp, int ax, int depth)
+{
+    const float frac = (float)depth / (float)(ax == 0 ? g.b0 : g.b);
+    const float zeta = pp.zmax[g.three ? ax : ax - 1] * frac * frac;
+    return __expf(-zeta * pp.dt);   // hardware exp2: a few ulp, far inside the tolerance
+}
+
+// Term of axis AX at four points, of which those with on[k] are in its layer (the
+// others keep their memory variables and get no term); corr: the sum so far.
+// Neighbours are read with buffer loads, whose range check gives the zeros
+// beyond the array: one select per load instead of one per value.
+template <int R, int AX>
 __device__ __forceinline__ void pml_axis_term(const StencilCoef& cf, const PmlParams& pp,
-                                              const PmlGeom& g, long long p, const int* ii, int ax,
-                                              float& corr)
+                                              const PmlGeom& g, const PmlAt& at, const bool* on,
+                                              PmlVec& corr)
 {
-    const int a = g.three ? ax : ax - 1;        // axis of the solver's Dims / coefficients
-    const int i = ii[ax];
-    const int b = ax == 0 ? g.b0 : g.b;
-    const int hi = b + g.pl[ax] - 1;
-    const int depth = i < b ? b - i : (i > hi ? i - hi : 0);
-    if (depth == 0)
-        return;
-    const float frac = (float)depth / (float)b;
-    const float zeta = pp.zmax[a] * frac * frac;
-    const float E = __expf(-zeta * pp.dt);   // hardware exp2: a few ulp, far inside the tolerance
-    const float* u = pp.u + p;
-    const float* psi = pp.psi[a] + p;
-    const int s = g.st[ax];
-    float d2 = pp.c0[a] * u[0], d1u = 0.f, d1p = 0.f;
+    const int a = g.three ? AX : AX - 1;        // axis of the solver's Dims / coefficients
+    const auto ru = plane_rsrc(pp.u + at.plane, at.plane_bytes);
+    const auto rp = plane_rsrc(pp.psi[a] + at.plane, at.plane_bytes);
+    const auto rc = plane_rsrc(pp.chi[a] + at.plane, at.plane_bytes);
+    const PmlVec u0 = bloadv<4, 0>(ru, at.off), p0 = bloadv<4, 0>(rp, at.off);
+    PmlVec chi = bloadv<4, 0>(rc, at.off);
+    PmlVec d2, d1u = PmlVec(0.f), d1p = PmlVec(0.f);
 #pragma unroll
-    for (int j = 1; j <= R; ++j) {
-        const bool in_p = i + j < g.nn[ax], in_m = i - j >= 0;
-        const float up = in_p ? u[j * s] : 0.f;
-        const float um = in_m ? u[-j * s] : 0.f;
-        const float qp = in_p ? psi[j * s] : 0.f;
-        const float qm = in_m ? psi[-j * s] : 0.f;
-        d2 = fmaf(cf.c[a][j], up + um, d2);
-        d1u = fmaf(cf.d[a][j], up - um, d1u);
-        d1p = fmaf(cf.d[a][j], qp - qm, d1p);
+    for (int k = 0; k < 4; ++k)
+        d2[k] = pp.c0[a] * u0[k];
+    if constexpr (AX == 2) {
+        constexpr int H = (R + 3) / 4 * 4;
+        float ur[4 + 2 * H], pr[4 + 2 * H];
+#pragma unroll
+        for (int q = 0; q < 4 + 2 * H; q += 4) {
+            const int x = at.i2 + q - H;
+            const int off = x >= 0 && x < g.nn[2] ? at.off + (q - H) * 4 : kNoByte;
+            const PmlVec uv = q == H ? u0 : bloadv<4, 0>(ru, off);
+            const PmlVec pv = q == H ? p0 : bloadv<4, 0>(rp, off);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ur[q + k] = uv[k];
+                pr[q + k] = pv[k];
+            }
+        }
+        if (g.nn[2] % 4 != 0)       // rows ending inside a quad
+#pragma unroll
+            for (int q = 0; q < 4 + 2 * H; ++q) {
+                const bool in = at.i2 + q - H < g.nn[2];
+                ur[q] = in ? ur[q] : 0.f;
+                pr[q] = in ? pr[q] : 0.f;
+            }
+#pragma unroll
+        for (int j = 1; j <= R; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                d2[k] = fmaf(cf.c[a][j], ur[H + k + j] + ur[H + k - j], d2[k]);
+                d1u[k] = fmaf(cf.d[a][j], ur[H + k + j] - ur[H + k - j], d1u[k]);
+                d1p[k] = fmaf(cf.d[a][j], pr[H + k + j] - pr[H + k - j], d1p[k]);
+            }
+    } else {
+#pragma unroll
+        for (int j = 1; j <= R; ++j) {
+            PmlVec up, um, qp, qm;
+            if constexpr (AX == 0) {
+                const long long s = (long long)j * g.st[0];
+                const int bp = at.i0 + j < g.nn[0] ? at.plane_bytes : 0;
+                const int bm = at.i0 - j >= 0 ? at.plane_bytes : 0;
+                const long long lp = at.plane + (bp ? s : 0), lm = at.plane - (bm ? s : 0);
+                up = bloadv<4, 0>(plane_rsrc(pp.u + lp, bp), at.off);
+                um = bloadv<4, 0>(plane_rsrc(pp.u + lm, bm), at.off);
+                qp = bloadv<4, 0>(plane_rsrc(pp.psi[a] + lp, bp), at.off);
+                qm = bloadv<4, 0>(plane_rsrc(pp.psi[a] + lm, bm), at.off);
+            } else {
+                const int s = j * g.st[1] * 4;
+                const int op = at.i1 + j < g.nn[1] ? at.off + s : kNoByte;
+                const int om = at.i1 - j >= 0 ? at.off - s : kNoByte;
+                up = bloadv<4, 0>(ru, op);
+                um = bloadv<4, 0>(ru, om);
+                qp = bloadv<4, 0>(rp, op);
+                qm = bloadv<4, 0>(rp, om);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                d2[k] = fmaf(cf.c[a][j], up[k] + um[k], d2[k]);
+                d1u[k] = fmaf(cf.d[a][j], up[k] - um[k], d1u[k]);
+                d1p[k] = fmaf(cf.d[a][j], qp[k] - qm[k], d1p[k]);
+            }
+        }
     }
-    const float chi = fmaf(E, pp.chi[a][p], (1.f - E) * (d2 - d1p));
-    pp.chi[a][p] = chi;
-    pp.psin[a][p] = fmaf(E, psi[0], (1.f - E) * d1u);
-    corr -= d1p + chi;
+    PmlVec next;
+    float E = 0.f;
+    if constexpr (AX < 2)
+        E = pml_decay(g, pp, AX, pml_depth(g, AX, AX == 0 ? at.i0 : at.i1));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (AX == 2)
+            E = pml_decay(g, pp, AX, pml_depth(g, AX, at.i2 + k));
+        const float c = fmaf(E, chi[k], (1.f - E) * (d2[k] - d1p[k]));
+        const float n = fmaf(E, p0[k], (1.f - E) * d1u[k]);
+        chi[k] = on[k] ? c : chi[k];
+        next[k] = on[k] ? n : p0[k];
+        corr[k] = on[k] ? corr[k] - (d1p[k] + c) : corr[k];
+    }
+    bstorev<4>(rc, at.off, chi);
+    bstorev<4>(plane_rsrc(pp.psin[a] + at.plane, at.plane_bytes), at.off, next);
 }
 
+// The correction of points (i0, i1, 4 q ..), i0 uniform over the wave.  Rows are
+// pitched to whole quads; points past the end of a row keep what they hold.
 template <int R>
-__device__ __forceinline__ void pml_point(const StencilCoef& cf, const PmlParams& pp, const PmlGeom& g,
-                                          int i0, int i1, int i2)
+__device__ __forceinline__ void pml_quad(const StencilCoef& cf, const PmlParams& pp, const PmlGeom& g,
+                                         int i0, int i1, int q)
 {
-    const int ii[3] = {i0, i1, i2};
-    const long long p = (long long)i0 * g.st[0] + (long long)i1 * g.st[1] + i2;
-    float corr = 0.f;
-    for (int ax = g.three ? 0 : 1; ax < 3; ++ax)
-        pml_axis_term<R>(cf, pp, g, p, ii, ax, corr);
-    pp.un[p] = fmaf(pp.k[p], corr, pp.un[p]);
+    PmlAt at;
+    at.i0 = i0;
+    at.i1 = i1;
+    at.i2 = 4 * q;
+    at.plane = (long long)i0 * g.st[0];
+    at.plane_bytes = g.st[1] * g.nn[1] * 4;
+    at.off = (i1 * g.st[1] + at.i2) * 4;
+    PmlVec corr = PmlVec(0.f);
+    bool live[4], x[4], any = false, on[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        live[k] = at.i2 + k < g.nn[2];
+        x[k] = live[k] && pml_depth(g, 2, at.i2 + k) != 0;
+        any = any || x[k];
+    }
+    const bool z = g.three && pml_depth(g, 0, i0) != 0, y = pml_depth(g, 1, i1) != 0;
+    const auto rn = plane_rsrc(pp.un + at.plane, at.plane_bytes);
+    PmlVec un = bloadv<4, 0>(rn, at.off);
+    const PmlVec kv = bloadv<4, 0>(plane_rsrc(pp.k + at.plane, at.plane_bytes), at.off);
+    if (z)
+        pml_axis_term<R, 0>(cf, pp, g, at, live, corr);
+    if (y)
+        pml_axis_term<R, 1>(cf, pp, g, at, live, corr);
+    if (any)
+        pml_axis_term<R, 2>(cf, pp, g, at, x, corr);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        on[k] = x[k] || (live[k] && (z || y));
+        un[k] = on[k] ? fmaf(kv[k], corr[k], un[k]) : un[k];
+    }
+    bstorev<4>(rn, at.off, un);
 }
 
-// Planes of axis 0 in its layer: grid (2 ceil(b0/4), column chunks, rows);
-// blockIdx.x = side x plane group (fastest), wave = plane within the group.
-template <int R>
-__global__ __launch_bounds__(256) void pml_layer0_kernel(Dims d, StencilCoef cf, PmlParams pp,
-                                                         PmlGeom g)
-{
-    const int groups = (g.b0 + 3) / 4;
-    const int side = (int)blockIdx.x >= groups;
-    const int zl = ((int)blockIdx.x - side * groups) * 4 + ((int)threadIdx.x >> 6);
-    const int i2 = (int)blockIdx.y * 64 + ((int)threadIdx.x & 63);
-    if (zl >= g.b0 || i2 >= g.nn[2])
-        return;
-    const int i0 = side == 0 ? zl : g.b0 + g.pl[0] + zl;
-    pml_point<R>(cf, pp, g, i0, (int)blockIdx.z, i2);
-}
+// Ranges of a correction launch: blocks of kPmlWaves waves (one per plane or row
+// of a group), 64 quads of a plane's or row's list each.
+struct PmlRanges {
+    int nq;                  // quads of a row
+    int ql, qr;              // axis 2's layer: quads [0, ql) and [qr, nq)
+    int cols0, cols1, cols2; // blocks per group of planes / rows
+    int end0, end1, end2;    // last block of each range, exclusive
+};
 
-// Rows of axis 1 in its layer, in the physical planes: grid (column chunks,
-// ceil(2b/4), physical planes).
-template <int R>
-__global__ __launch_bounds__(256) void pml_layer1_kernel(Dims d, StencilCoef cf, PmlParams pp,
-                                                         PmlGeom g)
-{
-    const int rl = (int)blockIdx.y * 4 + ((int)threadIdx.x >> 6);
-    const int i2 = (int)blockIdx.x * 64 + ((int)threadIdx.x & 63);
-    if (rl >= 2 * g.b || i2 >= g.nn[2])
-        return;
-    const int i1 = rl < g.b ? rl : g.b + g.pl[1] + (rl - g.b);
-    pml_point<R>(cf, pp, g, g.b0 + (int)blockIdx.z, i1, i2);
-}
+constexpr int kPmlWaves = 4;
 
-// Points of axis 2 in its layer, in the physical rows of the physical planes:
-// one 64-lane row per (plane, row) with lanes 0 .. 2b-1 on the layer's points
-// (b <= 32; wider layers take several lane groups); grid (lane groups x
-// ceil(rows/4), physical planes).
 template <int R>
-__global__ __launch_bounds__(256) void pml_layer2_kernel(Dims d, StencilCoef cf, PmlParams pp,
-                                                         PmlGeom g)
+__global__ __launch_bounds__(64 * kPmlWaves) void pml_layer_kernel(StencilCoef cf, PmlParams pp, PmlGeom g,
+                                                        PmlRanges r)
 {
-    const int lanes = (2 * g.b + 63) / 64;      // 64-lane groups per row
-    const int rg = (int)blockIdx.x / lanes;
-    const int lg = (int)blockIdx.x - rg * lanes;
-    const int yi = rg * 4 + ((int)threadIdx.x >> 6);
-    const int xl = lg * 64 + ((int)threadIdx.x & 63);
-    if (yi >= g.pl[1] || xl >= 2 * g.b)
-        return;
-    const int i2 = xl < g.b ? xl : g.b + g.pl[2] + (xl - g.b);
-    pml_point<R>(cf, pp, g, g.b0 + (int)blockIdx.y, g.b + yi, i2);
+    const int b = xcd_logical(blockIdx.x, gridDim.x);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63;
+    if (b < r.end0) {
+        // column block fastest but for the plane group: neighbouring groups of
+        // planes run next to each other
+        const int groups = (g.b0 + kPmlWaves - 1) / kPmlWaves;
+        const int col = b / (2 * groups), gr = b - col * 2 * groups;
+        const int side = gr >= groups;
+        const int zl = (gr - side * groups) * kPmlWaves + wave, t = col * 64 + lane;
+        if (zl >= g.b0 || t >= g.nn[1] * r.nq)
+            return;
+        const int i1 = t / r.nq;
+        pml_quad<R>(cf, pp, g, side ? g.b0 + g.pl[0] + zl : zl, i1, t - i1 * r.nq);
+    } else if (b < r.end1) {
+        const int groups = (2 * g.b + kPmlWaves - 1) / kPmlWaves;
+        const int e = b - r.end0, plane = e / (groups * r.cols1), f = e - plane * groups * r.cols1;
+        const int col = f / groups;
+        const int rl = (f - col * groups) * kPmlWaves + wave, q = col * 64 + lane;
+        if (rl >= 2 * g.b || q >= r.nq)
+            return;
+        pml_quad<R>(cf, pp, g, g.b0 + plane, rl < g.b ? rl : g.pl[1] + rl, q);
+    } else if (b < r.end2) {
+        const int nl = r.ql + r.nq - r.qr;
+        const int e = b - r.end1, plane = e / r.cols2;
+        const int t = (e - plane * r.cols2) * (64 * kPmlWaves) + (int)threadIdx.x, i1 = t / nl, ql = t - i1 * nl;
+        if (i1 >= g.pl[1])
+            return;
+        pml_quad<R>(cf, pp, g, g.b0 + plane, g.b + i1, ql < r.ql ? ql : r.qr + ql - r.ql);
+    }
 }
 
 void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const PmlParams& pp,
@@ -693,22 +805,21 @@ void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const Pm
     g.b0 = three ? d.nb : 0;
     if (g.b <= 0)
         return;
-    const unsigned cch = (unsigned)((g.nn[2] + 63) / 64);
-    const unsigned lanes = (unsigned)((2 * g.b + 63) / 64);
-    const dim3 g0(2 * ((g.b0 + 3) / 4), cch, g.nn[1]);
-    const dim3 g1(cch, (2 * g.b + 3) / 4, g.pl[0]);
-    const dim3 g2(lanes * ((g.pl[1] + 3) / 4), g.pl[0]);
-    if (R == 4) {
-        if (g.b0 > 0)
-            hipLaunchKernelGGL(pml_layer0_kernel<4>, g0, dim3(256), 0, s, d, cf, pp, g);
-        hipLaunchKernelGGL(pml_layer1_kernel<4>, g1, dim3(256), 0, s, d, cf, pp, g);
-        hipLaunchKernelGGL(pml_layer2_kernel<4>, g2, dim3(256), 0, s, d, cf, pp, g);
-    } else {
-        if (g.b0 > 0)
-            hipLaunchKernelGGL(pml_layer0_kernel<5>, g0, dim3(256), 0, s, d, cf, pp, g);
-        hipLaunchKernelGGL(pml_layer1_kernel<5>, g1, dim3(256), 0, s, d, cf, pp, g);
-        hipLaunchKernelGGL(pml_layer2_kernel<5>, g2, dim3(256), 0, s, d, cf, pp, g);
-    }
+    PmlRanges r{};
+    r.nq = (g.nn[2] + 3) / 4;
+    r.ql = std::min((g.b + 3) / 4, r.nq);
+    r.qr = std::max((g.b + g.pl[2]) / 4, r.ql);
+    r.cols0 = (g.nn[1] * r.nq + 63) / 64;
+    r.cols1 = (r.nq + 63) / 64;
+    r.cols2 = (g.pl[1] * (r.ql + r.nq - r.qr) + 64 * kPmlWaves - 1) / (64 * kPmlWaves);
+    r.end0 = 2 * ((g.b0 + kPmlWaves - 1) / kPmlWaves) * r.cols0;
+    r.end1 = r.end0 + (2 * g.b + kPmlWaves - 1) / kPmlWaves * r.cols1 * g.pl[0];
+    r.end2 = r.end1 + r.cols2 * g.pl[0];
+    const dim3 grid((unsigned)((r.end2 + kXcds - 1) / kXcds * kXcds));
+    if (R == 4)
+        hipLaunchKernelGGL(pml_layer_kernel<4>, grid, dim3(64 * kPmlWaves), 0, s, cf, pp, g, r);
+    else
+        hipLaunchKernelGGL(pml_layer_kernel<5>, grid, dim3(64 * kPmlWaves), 0, s, cf, pp, g, r);
 }
 
 // Padded coordinates of linear index t over the padded grid (no pitch) and the
