@@ -315,7 +315,7 @@ void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s);
 void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const PmlParams& pp,
                            hipStream_t s);
 void launch_medium_adjoint(const Dims& d, int R, const StencilCoef& cf, const SpongeCoef& sp,
-                           const MediumAdjParams& mp, hipStream_t s);
+                           const LaunchShape& ls, const MediumAdjParams& mp, hipStream_t s);
 // out[p] += a(p) k(p) (sum of the signals injected at p), for every point of an
 // injection table built for the launch shape ls; a(p) the damping factor of
 // the sponge and (att_power 0) the attenuation field att.
@@ -344,10 +344,11 @@ struct Fd1 {
 
 // Medium fields on the padded grid: gam[a] = -D_a ln rho_pad (rho NULL: zero;
 // ln rho repeats its edge value beyond the array) and att (alpha0 NULL: zero;
-// att_power 0: 2 alpha0 vp, 2: 2 alpha0 vp / dt), computed in FP64, rounded once.
+// att_power 0: 2 alpha0 vp, 2: 2 alpha0 vp / dt), computed in FP64, rounded once;
+// lr: scratch, a double per physical point.
 void launch_prep_medium(const Dims& d, const Fd1& fd, const float* vp, const float* rho,
                         const float* alpha0, int att_power, double dt, float* const gam[3],
-                        float* att, hipStream_t s);
+                        float* att, double* lr, hipStream_t s);
 // flags[2] = 1 if rho has a non-positive or non-finite value or alpha0 a negative
 // or non-finite one; flags[3] = max over points of vp^2 (1 + 2 beta) as float bits
 // (beta = 2 alpha0 vp / dt for att_power 2, else 0).

@@ -1693,7 +1693,9 @@ int prepare_medium(const stride_plan& P, const float* vp, const float* rho, cons
         return rc;
     float* gam[3] = {M.gam[0], M.gam[1], M.gam[2]};
     launch_prep_k(P.dims, vp, P.g.dt, M.k, s);
-    launch_prep_medium(P.dims, P.fd1, vp, rho, alpha0, att_power, P.g.dt, gam, M.att, s);
+    // (scratch in the first two wavefields, which hold nothing yet)
+    launch_prep_medium(P.dims, P.fd1, vp, rho, alpha0, att_power, P.g.dt, gam, M.att,
+                       reinterpret_cast<double*>(M.u[0]), s);
     return STRIDE_OK;
 }
 
@@ -1923,7 +1925,7 @@ int gradient_medium(const stride_plan& P, const float* vp, const float* rho, con
         mp.att_power = att_power;
         mp.H = Hm;    // w^{nt} = 0: step nt-1 images nothing
         mp.G = G;
-        launch_medium_adjoint(P.dims, P.R, P.cf, P.sp, mp, s);
+        launch_medium_adjoint(P.dims, P.R, P.cf, P.sp, P.ls_adj, mp, s);
         if (m == 0)
             return;   // w^0 is not needed; the launch above added the last imaging term
         launch_inject_table(P.dims, P.ls_adj, P.rec_inj, residual, P.nt, m, M.k, M.att, att_power,

@@ -136,7 +136,17 @@ __device__ __forceinline__ long long phys_index(const Dims& d, const int c[3])
     return src;
 }
 
-__global__ void prep_medium_kernel(Dims d, Fd1 fd, const float* vp, const float* rho,
+// ln rho over the physical grid, in FP64.
+__global__ void ln_kernel(const float* rho, long long n, double* out)
+{
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        out[i] = log((double)rho[i]);
+}
+
+// One logarithm per point, kept (lr; NULL: constant density), instead of one per
+// tap: 0.4 ms at 252^3, order 10, against 1.6.
+__global__ void prep_medium_kernel(Dims d, Fd1 fd, const float* vp, const double* lr,
                                    const float* alpha0, int att_power, double dt, float* g0,
                                    float* g1, float* g2, float* att)
 {
@@ -157,13 +167,12 @@ __global__ void prep_medium_kernel(Dims d, Fd1 fd, const float* vp, const float*
         const long long src = phys_index(d, c);
         for (int a = 0; a < d.nd; ++a) {
             double sum = 0.0;
-            if (rho) {
+            if (lr) {
                 for (int j = 1; j <= fd.r; ++j) {
                     int cp[3] = {c[0], c[1], c[2]}, cm[3] = {c[0], c[1], c[2]};
                     cp[a] += j;
                     cm[a] -= j;
-                    sum += fd.d[j] * (log((double)rho[phys_index(d, cp)]) -
-                                      log((double)rho[phys_index(d, cm)]));
+                    sum += fd.d[j] * (lr[phys_index(d, cp)] - lr[phys_index(d, cm)]);
                 }
             }
             gam[a][dst] = (float)(-sum * fd.inv_dx[a]);
@@ -849,32 +858,26 @@ __device__ __forceinline__ float sponge_eta(const Dims& d, const SpongeCoef& sp,
     return eta;
 }
 
-// One thread per padded point of a 64 x 8 tile of the plane spanned by the
-// last two axes (the row axis ay and the contiguous axis ax), one plane per
-// block (3D: blockIdx.z), two rows per thread.  The block first stages in LDS
-// the stencil operand y over the tile and its R-wide halo, and the density
-// products gamma_ay w^{m+1} (tile and row halo) and gamma_ax w^{m+1} (tile and
-// column halo); the in-plane taps then come from LDS and, in 3D, those of
-// axis 0 from global memory (through the caches).  Neighbours beyond the
-// padded array read 0.  The sums run in the same order as the point-wise
-// definition: centre, then per axis the taps j = 1..R.
+// 2D: one thread per padded point of a 64 x 8 tile, two rows per thread.  The
+// block first stages in LDS the stencil operand y over the tile and its R-wide
+// halo, and the density products gamma_0 w^{m+1} (tile and row halo) and gamma_1
+// w^{m+1} (tile and column halo).  Neighbours beyond the padded array read 0.
+// The sums run in the same order as the point-wise definition: centre, then per
+// axis the taps j = 1..R.
 constexpr int kMadjRows = 8;
 
-template <int R, int ND, bool Y2>
+template <int R, bool Y2>
 __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef cf, SpongeCoef sp,
                                                              MediumAdjParams mp)
 {
-    constexpr int ay = ND - 2, ax = ND - 1;
     constexpr int TW = kTileX + 2 * R, TH = kMadjRows + 2 * R;
     __shared__ float Yt[TH][TW];
     __shared__ float Zy[TH][kTileX];
     __shared__ float Zx[kMadjRows][TW];
     const int tid = (int)threadIdx.x;
     const int x0 = (int)blockIdx.x * kTileX, y0 = (int)blockIdx.y * kMadjRows;
-    const int z = ND == 3 ? (int)blockIdx.z : 0;
-    const int ny = d.n[ay], nx = d.n[ax];
-    const long long base = ND == 3 ? (long long)z * d.st[0] : 0;
-    const long long sty = d.st[ay];
+    const int ny = d.n[0], nx = d.n[1];
+    const long long sty = d.st[0];
     auto yv = [&](long long q) {
         if constexpr (Y2)
             return fmaf(mp.att[q], mp.w1[q] - mp.w2[q], mp.w1[q]);
@@ -886,7 +889,7 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
         const int gy = y0 + ly - R, gx = x0 + lx - R;
         float v = 0.f;
         if (gy >= 0 && gy < ny && gx >= 0 && gx < nx)
-            v = yv(base + gy * sty + gx);
+            v = yv(gy * sty + gx);
         Yt[ly][lx] = v;
     }
     for (int e = tid; e < TH * kTileX; e += 256) {
@@ -894,8 +897,8 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
         const int gy = y0 + ly - R, gx = x0 + lx;
         float v = 0.f;
         if (gy >= 0 && gy < ny && gx < nx) {
-            const long long q = base + gy * sty + gx;
-            v = mp.gam[ay][q] * mp.w1[q];
+            const long long q = gy * sty + gx;
+            v = mp.gam[0][q] * mp.w1[q];
         }
         Zy[ly][lx] = v;
     }
@@ -904,8 +907,8 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
         const int gy = y0 + ly, gx = x0 + lx - R;
         float v = 0.f;
         if (gy < ny && gx >= 0 && gx < nx) {
-            const long long q = base + gy * sty + gx;
-            v = mp.gam[ax][q] * mp.w1[q];
+            const long long q = gy * sty + gx;
+            v = mp.gam[1][q] * mp.w1[q];
         }
         Zx[ly][lx] = v;
     }
@@ -917,45 +920,27 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
         const int gy = y0 + ly, gx = x0 + lx;
         if (gy >= ny || gx >= nx)
             continue;
-        int c[3];
-        if constexpr (ND == 3) {
-            c[0] = z;
-            c[1] = gy;
-            c[2] = gx;
-        } else {
-            c[0] = gy;
-            c[1] = gx;
-            c[2] = 0;
-        }
-        const long long p = base + gy * sty + gx;
+        const int c[3] = {gy, gx, 0};
+        const long long p = gy * sty + gx;
         const float w1 = mp.w1[p];
         float lap_y = cf.c0 * Yt[ly + R][lx + R];
         float dens = 0.f;
 #pragma unroll
-        for (int a = 0; a < ND; ++a) {
+        for (int a = 0; a < 2; ++a) {
             float sy = 0.f, sz = 0.f;
 #pragma unroll
             for (int jj = 1; jj <= R; ++jj) {
                 float yp, ym, zp, zm;
-                if (a == ay) {
+                if (a == 0) {
                     yp = Yt[ly + R + jj][lx + R];
                     ym = Yt[ly + R - jj][lx + R];
                     zp = Zy[ly + R + jj][lx];
                     zm = Zy[ly + R - jj][lx];
-                } else if (a == ax) {
+                } else {
                     yp = Yt[ly + R][lx + R + jj];
                     ym = Yt[ly + R][lx + R - jj];
                     zp = Zx[ly][lx + R + jj];
                     zm = Zx[ly][lx + R - jj];
-                } else {
-                    // axis 0 of a 3D grid: the neighbouring planes
-                    const long long st = d.st[0];
-                    const bool in_p = c[0] + jj < d.n[0], in_m = c[0] - jj >= 0;
-                    const long long qp = p + jj * st, qm = p - jj * st;
-                    yp = in_p ? yv(qp) : 0.f;
-                    ym = in_m ? yv(qm) : 0.f;
-                    zp = in_p ? mp.gam[0][qp] * mp.w1[qp] : 0.f;
-                    zm = in_m ? mp.gam[0][qm] * mp.w1[qm] : 0.f;
                 }
                 sy = fmaf(cf.c[a][jj], yp + ym, sy);
                 sz = fmaf(cf.d[a][jj], zp - zm, sz);
@@ -972,161 +957,290 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
     }
 }
 
-// 3D form of the kernel above with one row per thread (512 threads, the same
-// 64 x 8 tile): the axis-0 taps of a thread's point are loaded first, into
-// registers, so that their loads are in flight together with the tile loads
-// instead of starting after the block's barrier.
+// 3D form: the march of the 3D steps.  A block takes a 64 x 8 tile and zc planes,
+// a thread two points of a row; the taps along axis 0 of y and of z = gam_0 w^{m+1}
+// come from register queues, those in the plane from LDS (y over the tile and
+// its whole frame, gam_1 w^{m+1} over the rows of the frame, gam_2 w^{m+1} over its
+// columns; two buffers, one barrier per plane).  Bound by memory: eleven fields
+// pass once per step.  At 252^3, order 10: 168 us a step (4.2 TB/s of needed
+// bytes); 337 with a thread per point and every tap along axis 0 loaded again.
 template <int R, bool Y2>
-__global__ __launch_bounds__(512) void medium_adjoint_kernel3(Dims d, StencilCoef cf, SpongeCoef sp,
-                                                              MediumAdjParams mp)
+__global__ __launch_bounds__(256) void medium_adjoint3d_kernel(Dims d, StencilCoef cf, SpongeCoef sp,
+                                                               LaunchShape ls, MediumAdjParams mp)
 {
-    constexpr int TW = kTileX + 2 * R, TH = kMadjRows + 2 * R;
-    __shared__ float Yt[TH][TW];
-    __shared__ float Zy[TH][kTileX];
-    __shared__ float Zx[kMadjRows][TW];
-    const int tid = (int)threadIdx.x;
-    const int x0 = (int)blockIdx.x * kTileX, y0 = (int)blockIdx.y * kMadjRows;
-    const int z = (int)blockIdx.z;
-    const int n0 = d.n[0], ny = d.n[1], nx = d.n[2];
-    const long long st0 = d.st[0], sty = d.st[1];
-    const long long base = (long long)z * st0;
-    const int lx = tid & 63, ly = tid >> 6;
-    const int gy = y0 + ly, gx = x0 + lx;
-    const bool inside = gy < ny && gx < nx;
-    const long long p = base + gy * sty + gx;
-    // axis-0 taps: raw values (the operand is formed after the barrier)
-    float w1p[R], w1m[R], gp[R], gm[R], w2p[R], w2m[R], ap[R], am[R];
-#pragma unroll
-    for (int jj = 1; jj <= R; ++jj) {
-        const bool in_p = inside && z + jj < n0, in_m = inside && z - jj >= 0;
-        const long long qp = p + jj * st0, qm = p - jj * st0;
-        w1p[jj - 1] = in_p ? mp.w1[qp] : 0.f;
-        w1m[jj - 1] = in_m ? mp.w1[qm] : 0.f;
-        gp[jj - 1] = in_p ? mp.gam[0][qp] : 0.f;
-        gm[jj - 1] = in_m ? mp.gam[0][qm] : 0.f;
-        if constexpr (Y2) {
-            w2p[jj - 1] = in_p ? mp.w2[qp] : 0.f;
-            w2m[jj - 1] = in_m ? mp.w2[qm] : 0.f;
-            ap[jj - 1] = in_p ? mp.att[qp] : 0.f;
-            am[jj - 1] = in_m ? mp.att[qm] : 0.f;
-        }
-    }
-    auto yv = [&](long long q) {
-        if constexpr (Y2)
-            return fmaf(mp.att[q], mp.w1[q] - mp.w2[q], mp.w1[q]);
-        else
-            return mp.w1[q];
-    };
-    for (int e = tid; e < TH * TW; e += 512) {
-        const int ty = e / TW, tx = e - ty * TW;
-        const int yy = y0 + ty - R, xx = x0 + tx - R;
-        float v = 0.f;
-        if (yy >= 0 && yy < ny && xx >= 0 && xx < nx)
-            v = yv(base + yy * sty + xx);
-        Yt[ty][tx] = v;
-    }
-    for (int e = tid; e < TH * kTileX; e += 512) {
-        const int ty = e / kTileX, tx = e - ty * kTileX;
-        const int yy = y0 + ty - R, xx = x0 + tx;
-        float v = 0.f;
-        if (yy >= 0 && yy < ny && xx < nx) {
-            const long long q = base + yy * sty + xx;
-            v = mp.gam[1][q] * mp.w1[q];
-        }
-        Zy[ty][tx] = v;
-    }
-    for (int e = tid; e < kMadjRows * TW; e += 512) {
-        const int ty = e / TW, tx = e - ty * TW;
-        const int yy = y0 + ty, xx = x0 + tx - R;
-        float v = 0.f;
-        if (yy < ny && xx >= 0 && xx < nx) {
-            const long long q = base + yy * sty + xx;
-            v = mp.gam[2][q] * mp.w1[q];
-        }
-        Zx[ty][tx] = v;
-    }
-    __syncthreads();
-    if (!inside)
+    constexpr int VX = kVx3dTwo, NT = 64 * kWaves3d;
+    using V = StepVec<VX>;
+    constexpr int LPR = kTileX / VX, TY = kWaves3d * VX;
+    constexpr int HQ = (R + VX - 1) / VX * VX;
+    constexpr int LW = kTileX + 2 * HQ, LH = TY + 2 * R;
+    constexpr int Q = 2 * R + 1;
+    constexpr int NYH = 2 * R * LPR, XPR = 2 * HQ / VX, NH = NYH + XPR * TY;
+    constexpr int HL = (NH + NT - 1) / NT;
+    __shared__ __align__(16) float sY[2][LH * LW], sZ1[2][LH * kTileX], sZ2[2][TY * LW];
+
+    const int lb = xcd_logical(blockIdx.x, ls.tile_blocks_pad);
+    if (lb >= ls.tile_blocks)
         return;
-    const int c[3] = {z, gy, gx};
-    const float w1 = mp.w1[p];
-    float lap_y = cf.c0 * Yt[ly + R][lx + R];
-    float dens = 0.f;
-    {
-        float sy = 0.f, sz = 0.f;
+    const int zci = lb / ls.tiles_xy, tile = lb - zci * ls.tiles_xy;
+    const int y0 = tile / ls.tiles_x * TY, x0 = tile % ls.tiles_x * kTileX;
+    const int n0 = d.n[0], n1 = d.n[1], n2 = d.n[2];
+    const int z0 = zci * ls.zc, z1 = min(z0 + ls.zc, n0);
+    const long long s0 = d.st[0];
+    const int s1 = (int)d.st[1], plane_bytes = (int)(s0 * 4);
+    const int tid = (int)threadIdx.x, row = tid / LPR, col = tid % LPR * VX;
+    const int gx = x0 + col, gy = y0 + row;
+    const int bo = gx < n2 && gy < n1 ? (gy * s1 + gx) * 4 : kNoByte;
+    const int lo = (row + R) * LW + col + HQ;
+    const bool ragged = n2 % VX != 0 && x0 + kTileX + HQ > n2;
+    const int dyd = layer_depth(gy, n1, d.nb);
+    const float dy2 = (float)(dyd * dyd);
+    float dx2[VX];
 #pragma unroll
-        for (int jj = 1; jj <= R; ++jj) {
-            float yp = w1p[jj - 1], ym = w1m[jj - 1];
-            if constexpr (Y2) {
-                // a point outside the grid loaded 0 for w1, w2 and att: 0 here too
-                yp = fmaf(ap[jj - 1], w1p[jj - 1] - w2p[jj - 1], w1p[jj - 1]);
-                ym = fmaf(am[jj - 1], w1m[jj - 1] - w2m[jj - 1], w1m[jj - 1]);
+    for (int k = 0; k < VX; ++k) {
+        const int dxd = layer_depth(gx + k, n2, d.nb);
+        dx2[k] = (float)(dxd * dxd);
+    }
+    // frame vectors of this thread: places in y and in z_1 or z_2, byte offset
+    int hl[HL], hz[HL], ho[HL], hx[HL];
+    bool rows[HL];
+#pragma unroll
+    for (int h = 0; h < HL; ++h) {
+        const int i = tid + h * NT;
+        hl[h] = -1;
+        hz[h] = hx[h] = 0;
+        ho[h] = kNoByte;
+        rows[h] = i < NYH;
+        if (i < NH) {
+            int ly, lx;
+            if (i < NYH) {
+                const int hr = i / LPR;
+                ly = hr < R ? hr - R : TY + hr - R;
+                lx = i % LPR * VX;
+                hz[h] = (ly + R) * kTileX + lx;
+            } else {
+                const int c = (i - NYH) % XPR;
+                ly = (i - NYH) / XPR;
+                lx = c < XPR / 2 ? c * VX - HQ : kTileX + (c - XPR / 2) * VX;
+                hz[h] = ly * LW + lx + HQ;
             }
-            const float zp = gp[jj - 1] * w1p[jj - 1], zm = gm[jj - 1] * w1m[jj - 1];
-            sy = fmaf(cf.c[0][jj], yp + ym, sy);
-            sz = fmaf(cf.d[0][jj], zp - zm, sz);
+            const int g = x0 + lx, y = y0 + ly;
+            hl[h] = (ly + R) * LW + lx + HQ;
+            hx[h] = g;
+            if (y >= 0 && y < n1 && g >= 0 && g < n2)
+                ho[h] = (y * s1 + g) * 4;
         }
-        lap_y += sy;
-        dens += sz;
     }
-    {
-        float sy = 0.f, sz = 0.f;
+    auto rsrc_in = [&](const float* f, int z) { return plane_rsrc(f + z * s0, plane_bytes); };
+    auto rsrc = [&](const float* f, int z) {
+        const bool in = z >= 0 && z < n0;
+        return plane_rsrc(f + (in ? z : 0) * s0, in ? plane_bytes : 0);
+    };
+    auto operand = [&](const V& w1, const V& w2, const V& at) {
+        if constexpr (!Y2)
+            return w1;
+        V y;
 #pragma unroll
-        for (int jj = 1; jj <= R; ++jj) {
-            sy = fmaf(cf.c[1][jj], Yt[ly + R + jj][lx + R] + Yt[ly + R - jj][lx + R], sy);
-            sz = fmaf(cf.d[1][jj], Zy[ly + R + jj][lx] - Zy[ly + R - jj][lx], sz);
-        }
-        lap_y += sy;
-        dens += sz;
-    }
-    {
-        float sy = 0.f, sz = 0.f;
+        for (int k = 0; k < VX; ++k)
+            y[k] = fmaf(at[k], w1[k] - w2[k], w1[k]);
+        return y;
+    };
+    auto product = [&](const V& g, const V& w) {
+        V z;
 #pragma unroll
-        for (int jj = 1; jj <= R; ++jj) {
-            sy = fmaf(cf.c[2][jj], Yt[ly + R][lx + R + jj] + Yt[ly + R][lx + R - jj], sy);
-            sz = fmaf(cf.d[2][jj], Zx[ly][lx + R + jj] - Zx[ly][lx + R - jj], sz);
+        for (int k = 0; k < VX; ++k)
+            z[k] = g[k] * w[k];
+        return z;
+    };
+    // raw values of vectors on their way: lead plane, frame, point values
+    V lw1, lw2, lat, lg0, fw1[HL], fw2[HL], fat[HL], fg[HL];
+    V pw1, pw2, pk, pat, pH, pG, pg1, pg2;
+    auto prefetch_lead = [&](int z) {
+        lw1 = bloadv<VX, 0>(rsrc(mp.w1, z), bo);
+        lg0 = bloadv<VX, 0>(rsrc(mp.gam[0], z), bo);
+        if constexpr (Y2) {
+            lw2 = bloadv<VX, 0>(rsrc(mp.w2, z), bo);
+            lat = bloadv<VX, 0>(rsrc(mp.att, z), bo);
         }
-        lap_y += sy;
-        dens += sz;
+    };
+    auto prefetch_frame = [&](int z) {
+#pragma unroll
+        for (int h = 0; h < HL; ++h) {
+            fw1[h] = bloadv<VX, 0>(rsrc_in(mp.w1, z), ho[h]);
+            // (the rows of the frame: whole waves)
+            fg[h] = rows[h] ? bloadv<VX, 0>(rsrc_in(mp.gam[1], z), ho[h])
+                            : bloadv<VX, 0>(rsrc_in(mp.gam[2], z), ho[h]);
+            if constexpr (Y2) {
+                fw2[h] = bloadv<VX, 0>(rsrc_in(mp.w2, z), ho[h]);
+                fat[h] = bloadv<VX, 0>(rsrc_in(mp.att, z), ho[h]);
+            }
+        }
+        pg1 = bloadv<VX, 0>(rsrc_in(mp.gam[1], z), bo);
+        pg2 = bloadv<VX, 0>(rsrc_in(mp.gam[2], z), bo);
+        if constexpr (Y2)
+            pw1 = bloadv<VX, 0>(rsrc_in(mp.w1, z), bo);
+    };
+    auto prefetch_points = [&](int z) {
+        pw2 = bloadv<VX, 0>(rsrc_in(mp.w2, z), bo);
+        pk = bloadv<VX, 0>(rsrc_in(mp.k, z), bo);
+        if constexpr (!Y2)      // (no attenuation: an empty descriptor, loads of 0)
+            pat = bloadv<VX, 0>(mp.att ? rsrc_in(mp.att, z) : plane_rsrc(mp.k, 0), bo);
+        pH = bloadv<VX, STRIDE_STREAM_AUX>(mp.H ? rsrc_in(mp.H, z) : plane_rsrc(mp.k, 0), bo);
+        pG = bloadv<VX, 0>(rsrc_in(mp.G, z), bo);
+    };
+
+    // queue slot (i + t) % Q holds plane z0 + i + t - R at march iteration i
+    V qy[Q], qz[Q];
+#pragma unroll
+    for (int t = 0; t < 2 * R; ++t) {
+        prefetch_lead(z0 - R + t);
+        qy[t] = operand(lw1, lw2, lat);
+        qz[t] = product(lg0, lw1);
     }
-    float eta = sponge_eta(d, sp, c);
-    if (mp.att && mp.att_power == 0)
-        eta += mp.att[p];
-    mp.w0[p] = leapfrog(w1, mp.w2[p], mp.k[p], lap_y - dens, eta, sp.half_dt);
-    if (mp.H)
-        mp.G[p] = fmaf(w1, mp.H[p], mp.G[p]);
+    prefetch_lead(z0 + R);
+    prefetch_frame(z0);
+    prefetch_points(z0);
+
+    int buf = 0;
+    for (int zb = z0; zb < z1; zb += Q)
+        unrolled_while<Q>([&](auto uc) {
+            constexpr int u = decltype(uc)::value;
+            constexpr int slot_lead = (u + 2 * R) % Q, slot_c = (u + R) % Q;
+            const int z = zb + u;
+            if (z >= z1)
+                return false;
+            qy[slot_lead] = operand(lw1, lw2, lat);
+            qz[slot_lead] = product(lg0, lw1);
+            const V w1 = Y2 ? pw1 : qy[slot_c];
+            float *Y = sY[buf], *Z1 = sZ1[buf], *Z2 = sZ2[buf];
+            *(V*)&Y[lo] = qy[slot_c];
+            *(V*)&Z1[(row + R) * kTileX + col] = product(pg1, w1);
+            *(V*)&Z2[row * LW + col + HQ] = product(pg2, w1);
+#pragma unroll
+            for (int h = 0; h < HL; ++h)
+                if (hl[h] >= 0) {
+                    *(V*)&Y[hl[h]] = operand(fw1[h], fw2[h], fat[h]);
+                    *(V*)&(rows[h] ? Z1 : Z2)[hz[h]] = product(fg[h], fw1[h]);
+                }
+            if (ragged) {
+#pragma unroll
+                for (int k = 1; k < VX; ++k) {
+                    if (gx + k >= n2)
+                        Y[lo + k] = Z2[row * LW + col + HQ + k] = 0.f;
+#pragma unroll
+                    for (int h = 0; h < HL; ++h)
+                        if (hl[h] >= 0 && hx[h] + k >= n2) {
+                            Y[hl[h] + k] = 0.f;
+                            if (!rows[h])
+                                Z2[hz[h] + k] = 0.f;
+                        }
+                }
+            }
+            if (z + 1 < z1) {
+                prefetch_lead(z + 1 + R);
+                prefetch_frame(z + 1);
+            }
+            __syncthreads();
+
+            // centre, then per axis the taps j = 1 .. R
+            V lap, dens = V(0.f), sy = V(0.f), sz = V(0.f);
+#pragma unroll
+            for (int k = 0; k < VX; ++k)
+                lap[k] = cf.c0 * qy[slot_c][k];
+            auto add = [&]() {
+#pragma unroll
+                for (int k = 0; k < VX; ++k) {
+                    lap[k] += sy[k];
+                    dens[k] += sz[k];
+                }
+                sy = sz = V(0.f);
+            };
+            auto tap = [&](int a, int j, const V& yp, const V& ym, const V& zp, const V& zm) {
+#pragma unroll
+                for (int k = 0; k < VX; ++k) {
+                    sy[k] = fmaf(cf.c[a][j], yp[k] + ym[k], sy[k]);
+                    sz[k] = fmaf(cf.d[a][j], zp[k] - zm[k], sz[k]);
+                }
+            };
+#pragma unroll
+            for (int j = 1; j <= R; ++j)
+                tap(0, j, qy[(u + R + j) % Q], qy[(u + R - j + Q) % Q], qz[(u + R + j) % Q],
+                    qz[(u + R - j + Q) % Q]);
+            add();
+            const float* Zc = Z1 + (row + R) * kTileX + col;
+#pragma unroll
+            for (int j = 1; j <= R; ++j)
+                tap(1, j, *(const V*)(Y + lo + j * LW), *(const V*)(Y + lo - j * LW),
+                    *(const V*)(Zc + j * kTileX), *(const V*)(Zc - j * kTileX));
+            add();
+            __builtin_amdgcn_sched_barrier(0);      // bounds the LDS vectors in flight
+            {
+                float xs[VX + 2 * HQ], zs[VX + 2 * HQ];
+#pragma unroll
+                for (int i = 0; i < VX + 2 * HQ; i += VX) {
+                    const V a = *(const V*)(Y + lo - HQ + i);
+                    const V c = *(const V*)(Z2 + row * LW + col + i);
+#pragma unroll
+                    for (int k = 0; k < VX; ++k) {
+                        xs[i + k] = a[k];
+                        zs[i + k] = c[k];
+                    }
+                }
+#pragma unroll
+                for (int j = 1; j <= R; ++j)
+#pragma unroll
+                    for (int k = 0; k < VX; ++k) {
+                        sy[k] = fmaf(cf.c[2][j], xs[HQ + k + j] + xs[HQ + k - j], sy[k]);
+                        sz[k] = fmaf(cf.d[2][j], zs[HQ + k + j] - zs[HQ + k - j], sz[k]);
+                    }
+            }
+            add();
+            const int dzd = layer_depth(z, n0, d.nb);
+            const float e0 = fmaf(sp.e[0], (float)(dzd * dzd), 0.f);
+            V out, G;
+#pragma unroll
+            for (int k = 0; k < VX; ++k) {
+                float eta = fmaf(sp.e[2], dx2[k], fmaf(sp.e[1], dy2, e0));
+                if constexpr (!Y2)
+                    eta = mp.att ? eta + pat[k] : eta;
+                out[k] = leapfrog(w1[k], pw2[k], pk[k], lap[k] - dens[k], eta, sp.half_dt);
+                G[k] = fmaf(w1[k], pH[k], pG[k]);
+            }
+            bstorev<VX>(rsrc_in(mp.w0, z), bo, out);
+            if (mp.H)
+                bstorev<VX>(rsrc_in(mp.G, z), bo, G);
+            if (z + 1 < z1)
+                prefetch_points(z + 1);
+            buf ^= 1;
+            return true;
+        });
 }
 
-template <int R, int ND>
-void launch_medium_adjoint_t(const Dims& d, const StencilCoef& cf, const SpongeCoef& sp,
-                             const MediumAdjParams& mp, hipStream_t s)
+template <int R>
+void launch_medium_adjoint_r(const Dims& d, const StencilCoef& cf, const SpongeCoef& sp,
+                             const LaunchShape& ls, const MediumAdjParams& mp, hipStream_t s)
 {
-    if constexpr (ND == 3) {
-        const dim3 g((unsigned)((d.n[2] + kTileX - 1) / kTileX),
-                     (unsigned)((d.n[1] + kMadjRows - 1) / kMadjRows), (unsigned)d.n[0]);
-        if (mp.att && mp.att_power == 2)
-            hipLaunchKernelGGL((medium_adjoint_kernel3<R, true>), g, dim3(512), 0, s, d, cf, sp, mp);
+    const bool y2 = mp.att && mp.att_power == 2;
+    if (d.nd == 3) {
+        const dim3 g((unsigned)ls.tile_blocks_pad), b(64 * kWaves3d);
+        if (y2)
+            hipLaunchKernelGGL((medium_adjoint3d_kernel<R, true>), g, b, 0, s, d, cf, sp, ls, mp);
         else
-            hipLaunchKernelGGL((medium_adjoint_kernel3<R, false>), g, dim3(512), 0, s, d, cf, sp, mp);
+            hipLaunchKernelGGL((medium_adjoint3d_kernel<R, false>), g, b, 0, s, d, cf, sp, ls, mp);
         return;
     }
-    const dim3 g((unsigned)((d.n[ND - 1] + kTileX - 1) / kTileX),
-                 (unsigned)((d.n[ND - 2] + kMadjRows - 1) / kMadjRows), ND == 3 ? (unsigned)d.n[0] : 1u);
-    if (mp.att && mp.att_power == 2)
-        hipLaunchKernelGGL((medium_adjoint_kernel<R, ND, true>), g, dim3(256), 0, s, d, cf, sp, mp);
+    const dim3 g((unsigned)((d.n[1] + kTileX - 1) / kTileX),
+                 (unsigned)((d.n[0] + kMadjRows - 1) / kMadjRows));
+    if (y2)
+        hipLaunchKernelGGL((medium_adjoint_kernel<R, true>), g, dim3(256), 0, s, d, cf, sp, mp);
     else
-        hipLaunchKernelGGL((medium_adjoint_kernel<R, ND, false>), g, dim3(256), 0, s, d, cf, sp, mp);
+        hipLaunchKernelGGL((medium_adjoint_kernel<R, false>), g, dim3(256), 0, s, d, cf, sp, mp);
 }
 
 void launch_medium_adjoint(const Dims& d, int R, const StencilCoef& cf, const SpongeCoef& sp,
-                           const MediumAdjParams& mp, hipStream_t s)
+                           const LaunchShape& ls, const MediumAdjParams& mp, hipStream_t s)
 {
-    if (R == 4)
-        d.nd == 3 ? launch_medium_adjoint_t<4, 3>(d, cf, sp, mp, s)
-                  : launch_medium_adjoint_t<4, 2>(d, cf, sp, mp, s);
-    else
-        d.nd == 3 ? launch_medium_adjoint_t<5, 3>(d, cf, sp, mp, s)
-                  : launch_medium_adjoint_t<5, 2>(d, cf, sp, mp, s);
+    R == 4 ? launch_medium_adjoint_r<4>(d, cf, sp, ls, mp, s)
+           : launch_medium_adjoint_r<5>(d, cf, sp, ls, mp, s);
 }
 
 // One block per step-kernel block of the table's launch shape; each thread
@@ -1190,11 +1304,14 @@ void launch_vp_check(const float* vp, long long n, unsigned* flags, hipStream_t 
 
 void launch_prep_medium(const Dims& d, const Fd1& fd, const float* vp, const float* rho,
                         const float* alpha0, int att_power, double dt, float* const gam[3],
-                        float* att, hipStream_t s)
+                        float* att, double* lr, hipStream_t s)
 {
     long long n = (long long)d.n[0] * d.n[1] * d.n[2];
-    hipLaunchKernelGGL(prep_medium_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, d, fd, vp, rho,
-                       alpha0, att_power, dt, gam[0], gam[1], d.nd == 3 ? gam[2] : gam[1], att);
+    const long long np = (long long)d.phys[0] * d.phys[1] * d.phys[2];
+    if (rho)
+        hipLaunchKernelGGL(ln_kernel, dim3(grid_for(np, 256)), dim3(256), 0, s, rho, np, lr);
+    hipLaunchKernelGGL(prep_medium_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, d, fd, vp,
+                       rho ? lr : nullptr, alpha0, att_power, dt, gam[0], gam[1], d.nd == 3 ? gam[2] : gam[1], att);
 }
 
 void launch_medium_check(const float* vp, const float* rho, const float* alpha0, long long n,
