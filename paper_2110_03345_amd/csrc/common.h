@@ -140,31 +140,66 @@ bool stream_3d(const Dims& d, bool adjoint, int mode);
 // kResidentThreads per tile of tx x ty points, tx a multiple of 4.
 constexpr int kResidentThreads = 1024;
 constexpr int kResidentItems = 2;    // quads per thread, at most
-constexpr int kResidentSide = 256;   // tile side, at most
+constexpr unsigned kResidentSteps = (1u << 21) - 1;   // highest step number of a sweep
+constexpr int kResidentSide = 256;   // side of a tile with its ring, at most
 
 struct ResidentShape {
     int tx, ty;
     int tiles_x, tiles_y, tiles;
+    int t;               // steps per exchange, 1 or 2
 };
 
-// Quads of a tile that neighbours take: R rows above and below, the quads of
-// R columns left and right.
-__host__ __device__ inline int resident_outer_quads(int R, const ResidentShape& rs)
+// The frame a block takes from its neighbours: t R rows above and below, the
+// quads of t R columns left and right.  With two steps per exchange the first is
+// computed on the tile and a ring of R rows and the quads of R columns as well.
+__host__ __device__ inline int resident_frame_rows(int R, const ResidentShape& rs)
 {
-    return 2 * R * (rs.tx / 4) + (rs.ty - 2 * R) * 2 * ((R + 3) / 4);
+    return rs.t * R;
+}
+__host__ __device__ inline int resident_frame_quads(int R, const ResidentShape& rs)
+{
+    return (rs.t * R + 3) / 4;
+}
+__host__ __device__ inline int resident_ring_rows(int R, const ResidentShape& rs)
+{
+    return (rs.t - 1) * R;
+}
+__host__ __device__ inline int resident_ring_quads(int R, const ResidentShape& rs)
+{
+    return (rs.t - 1) * ((R + 3) / 4);
 }
 
-// Threads with items: enough for nq quads at J each and for the outer quads at
-// one each, in whole waves.
-__host__ __device__ inline int resident_compute_threads(int nq, int outer, int J)
+// Quads computed by a block: the tile's and the ring's.
+__host__ __device__ inline int resident_items(int R, const ResidentShape& rs)
 {
-    const int n = (nq + J - 1) / J > outer ? (nq + J - 1) / J : outer;
+    return (rs.tx / 4 + 2 * resident_ring_quads(R, rs)) * (rs.ty + 2 * resident_ring_rows(R, rs));
+}
+
+// Quads of a tile that neighbours take.
+__host__ __device__ inline int resident_outer_quads(int R, const ResidentShape& rs)
+{
+    const int fr = resident_frame_rows(R, rs);
+    return 2 * fr * (rs.tx / 4) + (rs.ty - 2 * fr) * 2 * resident_frame_quads(R, rs);
+}
+
+// Quads of the frame.
+__host__ __device__ inline int resident_frame(int R, const ResidentShape& rs)
+{
+    const int fb = resident_frame_quads(R, rs);
+    return 2 * resident_frame_rows(R, rs) * (rs.tx / 4 + 2 * fb) + 2 * fb * rs.ty;
+}
+
+// Threads with items: enough for the items at J each and for the outer quads at
+// one each, in whole waves.
+__host__ __device__ inline int resident_compute_threads(int items, int outer, int J)
+{
+    const int n = (items + J - 1) / J > outer ? (items + J - 1) / J : outer;
     return (n + 63) / 64 * 64;
 }
 
-// Exchange words of a tile: word k of outer quad i at k * stride + i, so that
-// a wave's accesses are contiguous (four words per quad in a row cost four times
-// the transactions); stride a whole number of 64-byte lines.
+// Exchange words of a tile, three per quad: word k of outer quad i at k * stride
+// + i, so that a wave's accesses are contiguous (the words of a quad in a row cost
+// as many times the transactions); stride a whole number of 64-byte lines.
 __host__ __device__ inline int resident_word_stride(int R, const ResidentShape& rs)
 {
     return (resident_outer_quads(R, rs) + 7) / 8 * 8;
@@ -173,18 +208,19 @@ __host__ __device__ inline int resident_word_stride(int R, const ResidentShape& 
 // Bytes of the exchange area (two buffers of words).
 __host__ __device__ inline long long resident_word_bytes(int R, const ResidentShape& rs)
 {
-    return 2ll * rs.tiles * 4 * resident_word_stride(R, rs) * 8;
+    return 2ll * rs.tiles * 3 * resident_word_stride(R, rs) * 8;
 }
 
-// Row length of the LDS region of a tile (the tile and its frame of R rows and
-// R columns, in whole quads) and the region index of tile point (y, x).
+// Row length of the LDS region of a tile (the tile and its frame) and the region
+// index of tile point (y, x).
 __host__ __device__ inline int resident_row(int R, const ResidentShape& rs)
 {
-    return rs.tx + 8 * ((R + 3) / 4);
+    return rs.tx + 8 * resident_frame_quads(R, rs);
 }
 __host__ __device__ inline int resident_index(int R, const ResidentShape& rs, int y, int x)
 {
-    return (y + R) * resident_row(R, rs) + 4 * ((R + 3) / 4) + x;
+    return (y + resident_frame_rows(R, rs)) * resident_row(R, rs) +
+           4 * resident_frame_quads(R, rs) + x;
 }
 
 // LDS of a block: two buffers of the region, two more for injected values, and
@@ -192,8 +228,10 @@ __host__ __device__ inline int resident_index(int R, const ResidentShape& rs, in
 __host__ __device__ inline int resident_lds_bytes(int R, const ResidentShape& rs, bool injects,
                                                   bool adjoint)
 {
-    const bool k = adjoint && rs.tx / 4 * rs.ty > kResidentThreads;
-    return ((injects ? 4 : 2) * resident_row(R, rs) * (rs.ty + 2 * R) + (k ? rs.tx * rs.ty : 0)) * 4;
+    const int items = resident_items(R, rs);
+    const bool k = adjoint && items > kResidentThreads;
+    return ((injects ? 4 : 2) * resident_row(R, rs) * (rs.ty + 2 * resident_frame_rows(R, rs)) +
+            (k ? 4 * items : 0)) * 4;
 }
 
 // Points sampled by tile b: ptr[b] .. ptr[b+1]; taps as region indices.
@@ -229,7 +267,7 @@ struct ResidentParams {
     int inj_stride;
     ResidentSamples smp;   // sampling of u^n (out NULL: none)
     unsigned long long* words;   // exchange area: no word holds a step number in
-    unsigned tag;                // (tag, tag + count], the numbers of this sweep
+    unsigned tag;                // (tag, tag + count], the numbers of this sweep (21 bits)
     unsigned* err;
 };
 

@@ -6,11 +6,11 @@ namespace stride {
 namespace {
 #include "step2d_resident.h"
 
-template <int R, int MODE, int J>
+template <int R, int MODE, int J, int T>
 hipError_t resident_t(const Dims& d, const StencilCoef& cf, const ResidentShape& rs,
                       const ResidentBatch& b, hipStream_t s)
 {
-    const void* k = reinterpret_cast<const void*>(step2d_resident<R, MODE, J>);
+    const void* k = reinterpret_cast<const void*>(step2d_resident<R, MODE, J, T>);
     const int lds = resident_lds_bytes(R, rs, b.p[0].injects, MODE == kImageV);
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess)
@@ -24,22 +24,27 @@ hipError_t resident_t(const Dims& d, const StencilCoef& cf, const ResidentShape&
                                       dim3(kResidentThreads), args, (unsigned)lds, s);
 }
 
+template <int R, int MODE>
+hipError_t resident_m(const Dims& d, const StencilCoef& cf, const ResidentShape& rs,
+                      const ResidentBatch& b, hipStream_t s)
+{
+    constexpr int J = kResidentItems;
+    const bool one = resident_items(R, rs) <= kResidentThreads;     // quads per thread
+    if (rs.t == 1)
+        return one ? resident_t<R, MODE, 1, 1>(d, cf, rs, b, s) : resident_t<R, MODE, J, 1>(d, cf, rs, b, s);
+    if constexpr (R == 4)       // (two steps per exchange: order 8, one quad)
+        if (one)
+            return resident_t<R, MODE, 1, 2>(d, cf, rs, b, s);
+    return hipErrorInvalidValue;
+}
+
 template <int R>
 hipError_t resident_r(int mode, const Dims& d, const StencilCoef& cf, const ResidentShape& rs,
                       const ResidentBatch& b, hipStream_t s)
 {
-    const bool one = rs.tx / 4 * rs.ty <= kResidentThreads;     // quads per thread
-    switch (mode) {
-    case kStep:
-        return one ? resident_t<R, kStep, 1>(d, cf, rs, b, s)
-                   : resident_t<R, kStep, kResidentItems>(d, cf, rs, b, s);
-    case kStepV:
-        return one ? resident_t<R, kStepV, 1>(d, cf, rs, b, s)
-                   : resident_t<R, kStepV, kResidentItems>(d, cf, rs, b, s);
-    default:
-        return one ? resident_t<R, kImageV, 1>(d, cf, rs, b, s)
-                   : resident_t<R, kImageV, kResidentItems>(d, cf, rs, b, s);
-    }
+    return mode == kStep    ? resident_m<R, kStep>(d, cf, rs, b, s)
+           : mode == kStepV ? resident_m<R, kStepV>(d, cf, rs, b, s)
+                            : resident_m<R, kImageV>(d, cf, rs, b, s);
 }
 
 }  // namespace

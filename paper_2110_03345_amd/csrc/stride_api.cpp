@@ -268,7 +268,8 @@ struct HostTiles {
 
 // Injection entries of every tap with a nonzero weight, grouped by block,
 // sorted by block-local point and in (point, tap) order within a point.
-// place(c) gives the block and local index of padded coordinates c.
+// place(c, at) calls at(block, local index) for every block with a point of its
+// own at padded coordinates c.
 template <class Place>
 HostTiles group_entries(const TapSet& taps, double scale, int blocks, Place place)
 {
@@ -282,10 +283,11 @@ HostTiles group_entries(const TapSet& taps, double scale, int blocks, Place plac
     for (size_t k = 0; k < n; ++k) {
         if (taps.w[k] == 0.0)
             continue;
-        const std::pair<size_t, int> at = place(&taps.coord[k * 3]);
-        all.push_back(TileEntry{at.second, 0, (int)(k / taps.T), (float)(taps.w[k] * scale)});
-        block.push_back((int)at.first);
-        ++T.ptr[at.first + 1];
+        place(&taps.coord[k * 3], [&](size_t at, int local) {
+            all.push_back(TileEntry{local, 0, (int)(k / taps.T), (float)(taps.w[k] * scale)});
+            block.push_back((int)at);
+            ++T.ptr[at + 1];
+        });
     }
     for (int t = 0; t < blocks; ++t)
         T.ptr[t + 1] += T.ptr[t];
@@ -319,7 +321,7 @@ HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
                       const LaunchShape& ls)
 {
     const int plane = ls.ty * kTileX;   // block-local points per plane
-    return group_entries(taps, scale, ls.tile_blocks, [&](const int* c) {
+    return group_entries(taps, scale, ls.tile_blocks, [&](const int* c, auto at) {
         const int cy = c[P.nd - 2], cx = c[P.nd - 1];
         const int ty = cy / ls.ty, tx = cx / kTileX;
         int zci = 0, pz = 0;
@@ -327,19 +329,27 @@ HostTiles build_tiles(const stride_plan& P, const TapSet& taps, double scale,
             zci = c[0] / ls.zc;
             pz = c[0] - zci * ls.zc;
         }
-        return std::pair<size_t, int>((size_t)zci * ls.tiles_xy + (size_t)ty * ls.tiles_x + tx,
-                                      pz * plane + (cy - ty * ls.ty) * kTileX + (cx - tx * kTileX));
+        at((size_t)zci * ls.tiles_xy + (size_t)ty * ls.tiles_x + tx,
+           pz * plane + (cy - ty * ls.ty) * kTileX + (cx - tx * kTileX));
     });
 }
 
-// By tile of the 2D sweeps kept on the chip.
+// By tile of the 2D sweeps kept on the chip, its ring included.
 HostTiles build_resident(const stride_plan& P, const ResidentShape& rs, const TapSet& taps,
                          double scale)
 {
-    return group_entries(taps, scale, rs.tiles, [&](const int* c) {
+    const int er = resident_ring_rows(P.R, rs), ec = 4 * resident_ring_quads(P.R, rs);
+    return group_entries(taps, scale, rs.tiles, [&](const int* c, auto at) {
+        // the tile of the point, and neighbours whose ring holds it (rings are
+        // narrower than tiles)
         const int ty = c[0] / rs.ty, tx = c[1] / rs.tx;
-        return std::pair<size_t, int>((size_t)ty * rs.tiles_x + tx,
-                                      resident_index(P.R, rs, c[0] - ty * rs.ty, c[1] - tx * rs.tx));
+        const int y0 = ty - (ty > 0 && c[0] - ty * rs.ty < er), x0 = tx - (tx > 0 && c[1] - tx * rs.tx < ec);
+        const int y1 = ty + (ty + 1 < rs.tiles_y && c[0] + er >= (ty + 1) * rs.ty);
+        const int x1 = tx + (tx + 1 < rs.tiles_x && c[1] + ec >= (tx + 1) * rs.tx);
+        for (int y = y0; y <= y1; ++y)
+            for (int x = x0; x <= x1; ++x)
+                at((size_t)y * rs.tiles_x + x,
+                   resident_index(P.R, rs, c[0] - y * rs.ty, c[1] - x * rs.tx));
     });
 }
 
@@ -384,60 +394,77 @@ HostSamples build_resident_samples(const stride_plan& P, const ResidentShape& rs
 }
 
 // Tiles of the 2D sweeps kept on the chip: at most one block per CU, at most
-// kResidentItems quads per thread, frames and exchange words within what the
-// block and the workspace hold (the words take the two adjoint or forward
-// fields, free while the state is on the chip).  One quad per thread where that
-// fits the chip, in few, full blocks with short frames (a step is then mostly
-// the exchange, and fewer blocks wait for each other: at 240^2 1.76 us a step
-// with 80 x 48 tiles, 2.0 with 40 x 30; at 592^2 1.84 with 68 x 60, 2.6 with
-// 40 x 37); else two, in small tiles (a step is then mostly the items: at 1104^2
-// 2.35 us with 80 x 62, 2.5 with 92 x 69).  `shared`: the most steps per time of
-// several sweeps side by side (592^2: four on 56 tiles, 2.7 us a step of all
-// four; two on 100 tiles 1.9).
+// kResidentItems quads per thread, frames and LDS within what a block holds; for a
+// single sweep, exchange words within the two adjoint or forward fields (free
+// while the state is on the chip).  In order of preference, with the mean of the
+// three sweeps' steps (forward, with v stored, adjoint) measured:
+//  - two steps per exchange, in the smallest tiles, up to kRingItems quads: a step
+//    is mostly the exchange.  240^2: 1.55 us with 40 x 40 tiles (one step per
+//    exchange: 2.0); 592^2: 1.87 (2.26).  Beyond, the ring's quads and the frames
+//    eat the gain (760^2 with 64 x 38 tiles, 828 quads: 2.28, the same).  Order 8
+//    only: at order 10 the words of frames of ten cells don't fit two fields;
+//  - one quad per thread in few, full blocks with short frames (fewer blocks wait
+//    for each other: at 592^2 2.26 with 68 x 60, 2.7 with 40 x 37);
+//  - two quads per thread in small tiles (a step is mostly the items: at 1104^2
+//    2.4 us with 92 x 53, 2.5 with 92 x 69; two steps per exchange 2.5).
+// `shared`: the most steps per time of several sweeps side by side (592^2: four on
+// 56 tiles, 2.7 us a step of all four; two on 90 tiles 2.1).
 struct ResidentChoice {
     ResidentShape one{}, shared{};
 };
+
+constexpr int kRingItems = 768;
 
 ResidentChoice choose_resident(const Dims& d, int R, int cus)
 {
     ResidentChoice best;
     long long one_cost = 0, shared_cost = 0;
     double shared_rate = 0.0;
-    const int hb = (R + 3) / 4;
     const int n0 = d.n[0], n1 = d.n[1];
-    const int tx_min = std::max(16, 8 * hb), ty_min = 2 * R;
     const long long field = round_up(d.total * 4, 256);
-    for (int tiles_x = 1; tiles_x <= std::min(cus, n1 / tx_min + 1); ++tiles_x) {
-        const int tx = std::max((int)round_up((n1 + tiles_x - 1) / tiles_x, 4), tx_min);
-        if (tx > kResidentSide || (n1 + tx - 1) / tx != tiles_x)
-            continue;
-        // from the fewest rows of tiles whose quads fit the threads
-        const int ty_max = std::min(kResidentItems * kResidentThreads / (tx / 4), kResidentSide);
-        for (int tiles_y = (n0 + ty_max - 1) / ty_max;
-             tiles_x * tiles_y <= cus && tiles_y <= n0 / ty_min + 1; ++tiles_y) {
-            const int ty = std::max((n0 + tiles_y - 1) / tiles_y, ty_min);
-            if (ty > ty_max || (n0 + ty - 1) / ty != tiles_y)
+    for (int t = 1; t <= (R == 4 ? 2 : 1); ++t) {
+        ResidentShape rs{};
+        rs.t = t;
+        const int er = resident_ring_rows(R, rs), eb = resident_ring_quads(R, rs);
+        const int most = t == 1 ? kResidentItems * kResidentThreads : kRingItems;
+        const int tx_min = std::max(16, 8 * resident_frame_quads(R, rs));
+        const int ty_min = 2 * resident_frame_rows(R, rs);
+        for (rs.tiles_x = 1; rs.tiles_x <= std::min(cus, n1 / tx_min + 1); ++rs.tiles_x) {
+            rs.tx = std::max((int)round_up((n1 + rs.tiles_x - 1) / rs.tiles_x, 4), tx_min);
+            if (rs.tx + 8 * eb > kResidentSide || (n1 + rs.tx - 1) / rs.tx != rs.tiles_x)
                 continue;
-            const ResidentShape rs{tx, ty, tiles_x, tiles_y, tiles_x * tiles_y};
-            const int nq = tx / 4 * ty;
-            const int nh = 2 * R * (tx / 4 + 2 * hb) + 2 * hb * ty;
-            if (nh > kResidentThreads || resident_outer_quads(R, rs) > kResidentThreads ||
-                resident_lds_bytes(R, rs, true, true) > 155 * 1024 ||
-                resident_word_bytes(R, rs) > 2 * field)
+            // from the fewest rows of tiles whose quads fit the threads
+            const int ty_max = std::min(most / (rs.tx / 4 + 2 * eb), kResidentSide) - 2 * er;
+            if (ty_max < ty_min)
                 continue;
-            const bool single = nq <= kResidentThreads;
-            const long long cost = single ? 5 * rs.tiles + 4 * nh - 2 * nq
-                                          : (1 << 20) + 2 * nq + 2 * nh;
-            if (!best.one.tiles || cost < one_cost) {
-                best.one = rs;
-                one_cost = cost;
-            }
-            // sweeps per 1.85 us (one quad per thread) or 2.4 us (two)
-            const double rate = std::min(cus / rs.tiles, kResidentSlots) / (single ? 1.85 : 2.4);
-            if (rate > shared_rate || (rate == shared_rate && cost < shared_cost)) {
-                best.shared = rs;
-                shared_rate = rate;
-                shared_cost = cost;
+            for (rs.tiles_y = (n0 + ty_max - 1) / ty_max;
+                 rs.tiles_x * rs.tiles_y <= cus && rs.tiles_y <= n0 / ty_min + 1; ++rs.tiles_y) {
+                rs.ty = std::max((n0 + rs.tiles_y - 1) / rs.tiles_y, ty_min);
+                rs.tiles = rs.tiles_x * rs.tiles_y;
+                if (rs.ty > ty_max || (n0 + rs.ty - 1) / rs.ty != rs.tiles_y)
+                    continue;
+                const int nq = resident_items(R, rs), nh = resident_frame(R, rs);
+                if (nh > kResidentThreads || resident_outer_quads(R, rs) > kResidentThreads ||
+                    resident_lds_bytes(R, rs, true, true) > 155 * 1024)
+                    continue;
+                const bool single = nq <= kResidentThreads;
+                const long long cost = t == 2   ? nq - (1 << 20)
+                                       : single ? 5 * rs.tiles + 4 * nh - 2 * nq
+                                                : (1 << 20) + 2 * nq + 2 * nh;
+                if (resident_word_bytes(R, rs) <= 2 * field &&
+                    (!best.one.tiles || cost < one_cost)) {
+                    best.one = rs;
+                    one_cost = cost;
+                }
+                if (t == 2)
+                    continue;
+                // sweeps per 2.1 us (one quad per thread) or 2.6 us (two)
+                const double rate = std::min(cus / rs.tiles, kResidentSlots) / (single ? 2.1 : 2.6);
+                if (rate > shared_rate || (rate == shared_rate && cost < shared_cost)) {
+                    best.shared = rs;
+                    shared_rate = rate;
+                    shared_cost = cost;
+                }
             }
         }
     }
@@ -946,7 +973,7 @@ unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; 
 bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
                   hipStream_t s)
 {
-    if (!P.res.rs.tiles || p.count < 2)
+    if (!P.res.rs.tiles || p.count < 2 || p.count > (int)kResidentSteps)
         return false;
     launch_fill(words, resident_word_bytes(P.R, P.res.rs) / 4, 0.f, s);
     p.words = reinterpret_cast<unsigned long long*>(words);

@@ -492,7 +492,7 @@ int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStr
         const size_t launches = (v.size() + per - 1) / per;
         for (size_t l = 0; l < launches; ++l) {
             const size_t from = l * v.size() / launches, to = (l + 1) * v.size() / launches;
-            if (E->tag > 0x7fffffffu) {
+            if (E->tag + (unsigned)ticks > kResidentSteps) {
                 launch_fill((float*)E->words, 2 * area * per, 0.f, s);
                 E->tag = 0;
             }
