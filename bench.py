@@ -49,7 +49,7 @@ HBM_PEAK_GBS = 8000.0
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, averaged over the kernel's
 # dispatches) scaled by what the same counters read for a 1 GiB device copy.
 # Valid only for the kernel source they were taken with: the sha256 of the
-# kernel file and its header; any change makes `traffic` null until the
+# kernel bodies and their header; any change makes `traffic` null until the
 # counters are taken again.
 MEASURED_TRAFFIC = {
     # keyed by workload and the adjoint kernel: "pair" = the adjoint imaging
@@ -75,7 +75,7 @@ MEASURED_TRAFFIC = {
 def kernel_source_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ("csrc/step_kernels.h", "csrc/common.h"):
+    for f in ("csrc/step_kernels.h", "csrc/common.h", "csrc/step3d_body.h", "csrc/step2d_resident.h"):
         with open(os.path.join(ROOT, "paper_2110_03345_amd", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -528,7 +528,10 @@ def measure(name, args, dev, headline, built=None, checkpointing=0, forward=True
         "gradient_path": path_name,
         "traffic_key": f"{name}/{'pair' if from_v else 'fused'}",
         "adjoint": {
-            "kernel": ("adjoint leapfrog steps, imaging from the stored v two terms per even step "
+            "kernel": ("adjoint leapfrog steps, imaging from the stored v, a sweep of %.0f steps "
+                       "per launch kept on the chip (step2d_resident<R, 5, ., .>)" % adj_spl)
+                      if from_v and adj_spl > 1 else
+                      ("adjoint leapfrog steps, imaging from the stored v two terms per even step "
                        "(step%dd_kernel<R, true, ., ., 6> and <..., 5> in turn; per-launch figures "
                        "average the pair)" % w.ndim) if from_v else
                       "adjoint leapfrog step + imaging (step%dd_kernel<R, true, ., ., 0>)" % w.ndim,
@@ -554,7 +557,8 @@ def measure(name, args, dev, headline, built=None, checkpointing=0, forward=True
             lambda _: plan.forward(vp_m, wav, traces=traces, ws=fws), steps)
         f_step = ff_ms * 1e-3 / max(ff_n, 1)
         out["forward"] = {
-            "kernel": "forward leapfrog step (step%dd_kernel<R, false, ., ., 0>)" % w.ndim,
+            "kernel": ("forward leapfrog step (step%dd_kernel<R, false, ., ., 0>)" % w.ndim
+                       if ff_n <= ff_l else "forward leapfrog sweep (step2d_resident<R, 0, ., .>)"),
             "updates_per_s": npad * (w.nt - 1) * steps / el_f,
             "ms_per_solve": 1e3 * el_f / steps,
             "bytes_per_point": FWD_BYTES,
