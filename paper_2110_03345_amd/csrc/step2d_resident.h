@@ -2,7 +2,7 @@
 // adjoint steps imaging from a stored v), included by step2d.hip.
 //
 // A single 2D step is bound by its launch and one load phase (6.1 us at 1104^2,
-// 4.1 us at 240^2), while u^n, u^{n-1} and k of a grid of up to about three
+// 4.1 us at 240^2), while u^n, u^{n-1} and k of a grid of up to about two
 // million points fit the registers of the 256 CUs.  So one launch runs a whole
 // sweep: each block owns one tile, keeps u^{n-1}, u^n and k of its points in
 // registers and u^n of the tile and its frame in LDS, and per step exchanges
