@@ -385,6 +385,21 @@ int stride_accumulate(float* dst, const float* src, int64_t n, void* stream);
  * on = 0 turns the scan and its wait off.  Always returns STRIDE_OK. */
 int stride_check_finite(int32_t on);
 
+/* 2D sweeps kept on the chip.  Second-order 2D solves with the sponge, on grids
+ * of up to about two million points, run each sweep as one cooperative launch
+ * whose blocks wait for each other at every step or two; all other solves, and
+ * these where such a launch is refused, launch every step.  The results are the
+ * same bits.  polls bounds the calling thread's waits from here on, in polls of
+ * about 1 us of a block's running time; polls < 0: the default, 2^26 (about a
+ * minute), which only blocks that cannot run together reach (another kernel
+ * holding part of the GPU throughout).  polls = 0: no such sweeps on this thread
+ * -- for a GPU that several processes use at once, where the runtime runs the
+ * cooperative launches of different processes in long turns (two processes with
+ * gradients on 1024^2 grids: 156 ms a call against 20 with single steps).
+ * An engine follows the thread that calls stride_engine_run.  Always returns
+ * STRIDE_OK. */
+int stride_sweep_wait(int64_t polls);
+
 /* Tracing of the time loops.  While enabled on the calling thread, every solve
  * records HIP event pairs on its stream around its forward time loop, its
  * adjoint time loop and each recomputation segment inside the adjoint loop.

@@ -38,6 +38,7 @@ from ._abi import (  # noqa: F401
     stride_plan_gradient_medium,
     stride_plan_padded_shape,
     stride_schedule_info,
+    stride_sweep_wait,
     stride_timing_enable,
     stride_timing_read,
     stride_workspace_bytes,

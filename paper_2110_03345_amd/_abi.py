@@ -35,7 +35,7 @@ EXPORTS = (
     "stride_forward_save", "stride_backward",
     "stride_plan_gradient", "stride_forward", "stride_gradient", "stride_workspace_query",
     "stride_schedule_info", "stride_gradient_path", "stride_last_error", "stride_error_string",
-    "stride_timing_enable", "stride_timing_read", "stride_check_finite",
+    "stride_timing_enable", "stride_timing_read", "stride_check_finite", "stride_sweep_wait",
     "stride_engine_create", "stride_engine_destroy", "stride_engine_attach", "stride_engine_run",
     "stride_engine_detach", "stride_engine_slot_ticks", "stride_accumulate",
 )
@@ -103,6 +103,7 @@ def lib():
                                            ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(i32)]
         L.stride_timing_enable.argtypes = [i32]
         L.stride_check_finite.argtypes = [i32]
+        L.stride_sweep_wait.argtypes = [ctypes.c_int64]
         L.stride_timing_read.argtypes = [dp, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64),
                                          dp, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64)]
         L.stride_engine_create.argtypes = [gp, i32, i32, i32, i32, ctypes.POINTER(vp_)]
@@ -247,6 +248,12 @@ def stride_timing_enable(on: bool) -> None:
 def stride_check_finite(on: bool) -> None:
     """Scan solve outputs for NaN/Inf (STRIDE_E_NONFINITE) on this thread."""
     _check(lib().stride_check_finite(1 if on else 0))
+
+
+def stride_sweep_wait(polls: int) -> None:
+    """Bound, in polls, on the waits of this thread's 2D sweeps kept on the chip
+    (< 0: the default; 0: single steps instead of such sweeps)."""
+    _check(lib().stride_sweep_wait(int(polls)))
 
 
 def stride_timing_read():

@@ -142,6 +142,9 @@ constexpr int kResidentThreads = 1024;
 constexpr int kResidentItems = 2;    // quads per thread, at most
 constexpr unsigned kResidentSteps = (1u << 21) - 1;   // highest step number of a sweep
 constexpr int kResidentSide = 256;   // side of a tile with its ring, at most
+// Polls after which a block gives up waiting for its neighbours' words: a poll
+// takes about 1 us, so about a minute of the block's own running.
+constexpr int kResidentPatience = 1 << 26;
 
 struct ResidentShape {
     int tx, ty;
@@ -268,7 +271,8 @@ struct ResidentParams {
     ResidentSamples smp;   // sampling of u^n (out NULL: none)
     unsigned long long* words;   // exchange area: no word holds a step number in
     unsigned tag;                // (tag, tag + count], the numbers of this sweep (21 bits)
-    unsigned* err;
+    unsigned* err;               // set by a block that gave up waiting
+    int patience;                // polls after which a block gives up
 };
 
 // Sweeps of one launch, on rs.tiles blocks each.

@@ -129,6 +129,9 @@ inline long long phys_points(const stride_plan& P)
     return n;
 }
 
+// Polls the calling thread's 2D sweeps wait for (stride_sweep_wait); 0: no such sweeps.
+int sweep_wait();
+
 GradPath grad_path(const stride_plan& P, long long fields, int snaps);
 
 // Segment starts (0 first) and buffer length of a segmented history for nt

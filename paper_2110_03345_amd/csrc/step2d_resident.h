@@ -28,15 +28,13 @@
 //
 // Every block must be resident at once: the launch is cooperative, and every
 // wait is bounded; a block that waits too long sets p.err, which ends the
-// waits of all others.  Steps compute the operations of the single-step kernel
+// waits of all others.  The bound counts polls, not time: a process whose queues
+// are set aside for another's does not poll meanwhile.  Steps compute the operations of the single-step kernel
 // in the same order: the same bits.
 #pragma once
 
 // Points of a tile whose bilinear taps are kept in LDS.
 constexpr int kResidentSampled = 64;
-
-// Neighbour waits give up after this long (100 MHz ticks: 4 s).
-constexpr long long kResidentPatience = 400000000ll;
 
 // J: quads per thread; T: steps per exchange (2: order 8, one quad)
 template <int R, int MODE, int J, int T>
@@ -476,8 +474,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
             const Word* w = hw + (t0 / T & 1) * parity;
             const unsigned want = (p.tag + t + 1) << 11;
             V v;
-            long long since = 0;
-            for (int tries = 0;; ++tries) {
+            for (int tries = 1;; ++tries) {
                 unsigned hi[3];
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
@@ -489,17 +486,13 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
                     v[3] = __uint_as_float(hi[0] | hi[1] << 11 | hi[2] << 22);
                     break;
                 }
-                if ((tries & 1023) == 1023) {
-                    const long long now = wall_clock64();
-                    if (!since)
-                        since = now;
-                    const bool late = now - since > kResidentPatience;
-                    if (late)
-                        __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (late || __hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                        bad = 1;
-                        break;
-                    }
+                const bool late = tries >= p.patience;
+                if (late)
+                    __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (late || ((tries & 1023) == 0 &&
+                             __hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                    bad = 1;
+                    break;
                 }
             }
             *(V*)&Sn[hl] = v;

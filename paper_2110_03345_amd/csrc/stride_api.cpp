@@ -3,6 +3,7 @@
 // forward and adjoint time loops, binomial checkpointing over a pool of
 // wavefields, and the exported C ABI (include/stride_hip.h).
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -965,19 +966,23 @@ unsigned* finite_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 4; }
 // Word 5: set when the blocks of a resident sweep gave up waiting for each other.
 unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; }
 
+// Polls a 2D sweep of the calling thread waits for (stride_sweep_wait).
+thread_local int g_sweep_wait = kResidentPatience;
+
 // One 2D sweep kept on the chip, its exchange words in the two fields at
-// `words` (zeroed here).  False when the plan has no such sweeps, the sweep is
-// shorter than two steps (blocks then do not wait for each other, and one could
-// store its final state before a neighbour has loaded its frame) or the launch
-// is refused; the caller then runs single steps.
+// `words` (zeroed here).  False when the plan or the calling thread has no such
+// sweeps, the sweep is shorter than two steps (blocks then do not wait for each
+// other, and one could store its final state before a neighbour has loaded its
+// frame) or the launch is refused; the caller then runs single steps.
 bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
                   hipStream_t s)
 {
-    if (!P.res.rs.tiles || p.count < 2 || p.count > (int)kResidentSteps)
+    if (!P.res.rs.tiles || !g_sweep_wait || p.count < 2 || p.count > (int)kResidentSteps)
         return false;
     launch_fill(words, resident_word_bytes(P.R, P.res.rs) / 4, 0.f, s);
     p.words = reinterpret_cast<unsigned long long*>(words);
     p.err = err;
+    p.patience = g_sweep_wait;
     p.injects = (mode == kImageV ? P.nrec : P.nsrc) > 0;
     p.sp = P.sp;
     if (launch_resident(P.dims, P.R, mode, P.cf, P.res.rs, ResidentBatch{1, {p}}, s) == hipSuccess)
@@ -2141,6 +2146,8 @@ int static_workspace(void** out)
 
 }  // namespace
 
+int stride::sweep_wait() { return g_sweep_wait; }
+
 // ============================================================== C ABI
 
 extern "C" {
@@ -2691,6 +2698,12 @@ int stride_gradient(const stride_grid_t* grid, const float* vp, const float* wav
 int stride_check_finite(int32_t on)
 {
     g_check_finite = on != 0;
+    return STRIDE_OK;
+}
+
+int stride_sweep_wait(int64_t polls)
+{
+    g_sweep_wait = polls < 0 ? kResidentPatience : (int)std::min<int64_t>(polls, INT_MAX);
     return STRIDE_OK;
 }
 

@@ -466,7 +466,7 @@ bool resident_sweep(const stride_engine* E, SlotJob& J, int count, int* mode, Re
 // counts the ticks it ran of slot j.
 int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStream_t s)
 {
-    if (!E->words)
+    if (!E->words || !sweep_wait())
         return STRIDE_OK;
     const ResidentShape& rs = E->shape_plan->shared.rs;
     const long long area = resident_word_bytes(E->R, rs) / 8;
@@ -504,6 +504,7 @@ int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStr
                 p.words = E->words + (long long)b.n++ * area;
                 p.tag = E->tag;
                 p.err = E->late;
+                p.patience = sweep_wait();
             }
             if (launch_resident(E->dims, E->R, mode, E->cf, rs, b, s) != hipSuccess) {
                 (void)hipGetLastError();
