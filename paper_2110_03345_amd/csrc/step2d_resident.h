@@ -52,6 +52,8 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
     // takes them from the frame) in LDS
     constexpr bool CEN = T == 1;
     extern __shared__ __align__(16) float lds[];
+    // one past the step in which the block gave up, 0: none.  (Not a flag: a wave may
+    // reach the next step's wait before another has looked at this step's)
     __shared__ int bad;
     __shared__ int ti[4 * kResidentSampled];         // bilinear taps of the tile's points
     __shared__ float tw[4 * kResidentSampled];
@@ -255,6 +257,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
     }
     Word* const mine = p.words + (long long)tile * 3 * ws + tid;
     const long long parity = (long long)rs.tiles * 3 * ws;
+    const int look = p.patience < 1024 ? 0 : 1023;   // polls between looks at p.err
 
     // the order in which threads take entries and points: from the last before
     // the polling waves down (past `skip`), those waves at the end
@@ -486,13 +489,14 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
                     v[3] = __uint_as_float(hi[0] | hi[1] << 11 | hi[2] << 22);
                     break;
                 }
-                const bool late = tries >= p.patience;
-                if (late)
-                    __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (late || ((tries & 1023) == 0 &&
-                             __hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-                    bad = 1;
-                    break;
+                if ((tries & look) == 0) {
+                    const bool late = tries >= p.patience;
+                    if (late)
+                        __hip_atomic_store(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (late || __hip_atomic_load(p.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                        bad = t + 1;
+                        break;
+                    }
                 }
             }
             *(V*)&Sn[hl] = v;
@@ -515,7 +519,7 @@ __global__ __launch_bounds__(kResidentThreads) void step2d_resident(Dims d, Sten
                     load_v(v2, t + 2);
             }
         __syncthreads();
-        return more && !bad;
+        return more && bad != t + 1;
     };
     for (int t = 0;; t += T) {
         if (!step(std::integral_constant<int, 0>{}, t))

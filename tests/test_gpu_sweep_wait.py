@@ -72,3 +72,32 @@ def test_a_thread_can_choose_single_steps():
     assert other == [(59, 1, 0, 0)]
     _abi.stride_sweep_wait(-1)
     assert launches(x.gradient) == (59, 1, 60, 1)
+
+
+# two steps per exchange; one, with one quad per thread; one, with two
+GIVE_UP = [dict(), dict(space_order=10), dict(shape=(1010, 1037), nt=24)]
+
+
+@pytest.mark.parametrize("kw", GIVE_UP, ids=["two_steps", "one_quad", "two_quads"])
+def test_blocks_that_give_up_leave_together(kw):
+    """A bound of one poll, which blocks reach at once: every wave of a block leaves
+    in the same step, the call reports it and the outputs are NaN; the same plan
+    and workspace then solve again."""
+    x = Shot(**kw)
+    ws = x.plan.workspace(S.STRIDE_MODE_GRADIENT)
+    ref = x.gradient(ws)
+    for _ in range(3):
+        _abi.stride_sweep_wait(1)
+        with pytest.raises(S.StrideError) as e:
+            x.forward()
+        assert e.value.code == _abi.STRIDE_E_HIP
+        out = [torch.zeros_like(t) for t in ref]
+        with pytest.raises(S.StrideError) as e:
+            _abi.stride_plan_gradient(x.plan.handle, x.vp, x.wav, x.data, *out, ws)
+        assert e.value.code == _abi.STRIDE_E_HIP
+        assert all(t.isnan().all() for t in out)
+        _abi.stride_check_finite(False)
+        assert x.forward().isnan().all()
+        _abi.stride_check_finite(True)
+        _abi.stride_sweep_wait(-1)
+        assert all(torch.equal(a, b) for a, b in zip(x.gradient(ws), ref))
