@@ -351,8 +351,13 @@ void launch_step_mode(const Dims& d, int R, bool adjoint, int mode, const Stenci
 // The exchange words must be zero (resident_word_bytes of them).
 hipError_t launch_resident(const Dims& d, int R, int mode, const StencilCoef& cf,
                            const ResidentShape& rs, const ResidentBatch& b, hipStream_t s);
-// Fills p with NaN where *err is set (a sweep whose blocks gave up waiting).
-void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s);
+// Outputs of a solve (p NULL: none).
+struct Outputs {
+    float* p[3];
+    long long n[3];
+};
+// Fills them with NaN where *err is set (a sweep whose blocks gave up waiting).
+void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s);
 
 void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const PmlParams& pp,
                            hipStream_t s);

@@ -1579,7 +1579,7 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
         if (run_resident(P, kStep, resident_forward(P, k, wavelet, 0, P.nt - 1, traces, true), u[0],
                          resident_flag(ws), s)) {
             g_timer.end(id, s, 0, P.nt - 1, 1);
-            launch_poison(resident_flag(ws), traces, (long long)P.nrec * P.nt, s);
+            launch_poison(resident_flag(ws), {{traces}, {(long long)P.nrec * P.nt}}, s);
             HIP_TRY(hipGetLastError());
             return check_finite(finite_flag(ws), s, outs, true);
         }
@@ -2057,7 +2057,7 @@ int forward_save(const stride_plan& P, const float* vp, const float* wavelet, fl
     if (last)
         launch_sample(rec_samples(P, tr), last, P.nt - 1, s);
     if (run.kept_on_chip)
-        launch_poison(resident_flag(ws), tr, (long long)P.nrec * P.nt, s);
+        launch_poison(resident_flag(ws), {{tr}, {(long long)P.nrec * P.nt}}, s);
     if (traces && traces != W.traces)
         launch_copy(W.traces, traces, (long long)P.nrec * P.nt, s);
     HIP_TRY(hipGetLastError());
@@ -2099,8 +2099,9 @@ int backward(const stride_plan& P, const float* vp, const float* wavelet, const 
         launch_time_filter3(dwavelet, P.nsrc, P.nt, s);
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, W.G, P.torder == 4 ? W.k : nullptr, vp, dvp, W.w[0], W.w[1], s);
-    if (run.kept_on_chip)
-        launch_poison(resident_flag(ws), dvp, phys_points(P), s);
+    // (also where only the forward's sweeps were kept on the chip)
+    if (P.res.rs.tiles)
+        launch_poison(resident_flag(ws), {{dvp, dwavelet}, {phys_points(P), (long long)P.nsrc * P.nt}}, s);
     HIP_TRY(hipGetLastError());
     return STRIDE_OK;
 }

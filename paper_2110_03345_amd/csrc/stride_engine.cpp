@@ -544,7 +544,7 @@ void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
     if (J.mode == STRIDE_MODE_FORWARD) {
         launch_sample(rec_samples(P, J.traces), J.F.u[J.cur], P.nt - 1, s);
         if (E->words)
-            launch_poison(E->late, J.traces, ntraces, s);
+            launch_poison(E->late, {{J.traces}, {ntraces}}, s);
         J.finished = true;
         return;
     }
@@ -587,12 +587,8 @@ void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, J.W.G, P.torder == 4 ? J.W.k : nullptr, J.vp, J.dvp, J.W.w[0],
                         J.W.w[1], s);
-    if (E->words) {
-        launch_poison(E->late, J.dvp, phys_points(P), s);
-        launch_poison(E->late, (float*)J.misfit, 2, s);
-        if (J.traces)
-            launch_poison(E->late, J.traces, ntraces, s);
-    }
+    if (E->words)
+        launch_poison(E->late, {{J.dvp, (float*)J.misfit, J.traces}, {phys_points(P), 2, ntraces}}, s);
     J.finished = true;
 }
 

@@ -529,20 +529,21 @@ void launch_copy(float* dst, const float* src, long long n, hipStream_t s)
     hipLaunchKernelGGL(copy_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, dst, src, n);
 }
 
-__global__ void poison_kernel(const unsigned* err, float* p, long long n)
+__global__ void poison_kernel(const unsigned* err, Outputs out)
 {
     if (!*err)
         return;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x)
-        p[i] = __uint_as_float(0x7fffffffu);   // (two of them: a double NaN)
+    for (int a = 0; a < 3; ++a)
+        for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; out.p[a] && i < out.n[a];
+             i += (long long)gridDim.x * blockDim.x)
+            out.p[a][i] = __uint_as_float(0x7fffffffu);   // (two of them: a double NaN)
 }
 
-void launch_poison(const unsigned* err, float* p, long long n, hipStream_t s)
+void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s)
 {
+    const long long n = std::max({out.n[0], out.n[1], out.n[2]});
     if (n > 0)
-        hipLaunchKernelGGL(poison_kernel, dim3(std::min(grid_for(n, 256), 256)), dim3(256), 0, s, err, p,
-                           n);
+        hipLaunchKernelGGL(poison_kernel, dim3(std::min(grid_for(n, 256), 256)), dim3(256), 0, s, err, out);
 }
 
 // flag |= bit when any of the n values is NaN or infinite.

@@ -101,3 +101,20 @@ def test_blocks_that_give_up_leave_together(kw):
         _abi.stride_check_finite(True)
         _abi.stride_sweep_wait(-1)
         assert all(torch.equal(a, b) for a, b in zip(x.gradient(ws), ref))
+
+
+@pytest.mark.parametrize("stopped", ["forward", "backward"])
+def test_every_output_of_a_stopped_sweep_is_nan(stopped):
+    """With the finite check off the NaN outputs are the only sign: the model and
+    the wavelet gradient, when the adjoint's sweep stopped and when the forward's
+    did, the adjoint then running as single steps."""
+    x = Shot()
+    ws = x.plan.workspace(S.STRIDE_MODE_GRADIENT)
+    _abi.stride_check_finite(False)
+    _abi.stride_sweep_wait(1 if stopped == "forward" else -1)
+    tr = x.plan.forward_save(x.vp, x.wav, ws)
+    assert bool(tr.isnan().all()) == (stopped == "forward")
+    _abi.stride_sweep_wait(0 if stopped == "forward" else 1)
+    dvp, dwav = torch.zeros_like(x.vp), torch.zeros_like(x.wav)
+    _abi.stride_backward(x.plan.handle, x.vp, x.wav, x.data, dvp, dwav, ws)
+    assert dvp.isnan().all() and dwav.isnan().all()
