@@ -362,9 +362,18 @@ int stride_engine_attach(stride_engine_t* engine, const stride_plan_t* plan, int
  * the chunk idles to its end) and the phase-end work of slots that reach it.  *ticks_run is the
  * number of ticks enqueued (0 when no slot is active); finished[slot] is set
  * to 1 (array of max_slots, may be NULL) for slots whose outputs are complete
- * once the stream reaches this point. */
+ * once the stream reaches this point (stride_engine_check then says whether
+ * sweeps of theirs failed). */
 int stride_engine_run(stride_engine_t* engine, int32_t max_ticks, void* stream,
                       int32_t* ticks_run, int32_t* finished);
+
+/* Whether finished shots are to be trusted: STRIDE_E_HIP when the blocks of a 2D
+ * sweep kept on the chip gave up waiting (stride_sweep_wait) for some shot that
+ * has completed on the stream since the last such return; the outputs of that
+ * shot are NaN, those of all others are right.  Call it after waiting for the
+ * stream (or an event) behind the shots whose outputs are taken; the engine's
+ * slots tick, without such sweeps, until it has been called.  Does not wait. */
+int stride_engine_check(stride_engine_t* engine);
 
 /* Frees a slot (after it finished, or to abandon it). */
 int stride_engine_detach(stride_engine_t* engine, int32_t slot);

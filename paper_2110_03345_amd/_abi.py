@@ -37,7 +37,7 @@ EXPORTS = (
     "stride_schedule_info", "stride_gradient_path", "stride_last_error", "stride_error_string",
     "stride_timing_enable", "stride_timing_read", "stride_check_finite", "stride_sweep_wait",
     "stride_engine_create", "stride_engine_destroy", "stride_engine_attach", "stride_engine_run",
-    "stride_engine_detach", "stride_engine_slot_ticks", "stride_accumulate",
+    "stride_engine_detach", "stride_engine_slot_ticks", "stride_engine_check", "stride_accumulate",
 )
 
 
@@ -112,6 +112,7 @@ def lib():
                                            vp_, sz, vp_, ctypes.POINTER(i32)]
         L.stride_engine_run.argtypes = [vp_, i32, vp_, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.stride_engine_detach.argtypes = [vp_, i32]
+        L.stride_engine_check.argtypes = [vp_]
         L.stride_engine_slot_ticks.argtypes = [vp_, i32, ctypes.POINTER(ctypes.c_int64)]
         L.stride_accumulate.argtypes = [vp_, vp_, ctypes.c_int64, vp_]
         L.stride_last_error.restype = ctypes.c_char_p
@@ -383,6 +384,12 @@ def stride_engine_run(engine, max_ticks: int, max_slots: int, stream=None):
 
 def stride_engine_detach(engine, slot: int) -> None:
     _check(lib().stride_engine_detach(engine, slot))
+
+
+def stride_engine_check(engine) -> None:
+    """Raises when a 2D sweep of a shot that has completed since the last raise
+    gave up waiting (its outputs are NaN)."""
+    _check(lib().stride_engine_check(engine))
 
 
 def stride_engine_slot_ticks(engine, slot: int) -> int:

@@ -356,8 +356,9 @@ struct Outputs {
     float* p[3];
     long long n[3];
 };
-// Fills them with NaN where *err is set (a sweep whose blocks gave up waiting).
-void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s);
+// Fills them with NaN where *err is set (a sweep whose blocks gave up waiting), and
+// sets *report (pinned; NULL: none).
+void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s, unsigned* report = nullptr);
 
 void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const PmlParams& pp,
                            hipStream_t s);

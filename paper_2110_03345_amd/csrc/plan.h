@@ -129,6 +129,11 @@ inline long long phys_points(const stride_plan& P)
     return n;
 }
 
+// Word 5 of a workspace's scratch: set when the blocks of a 2D sweep kept on the
+// chip gave up waiting for each other (words 0-3 hold the vp and medium checks,
+// word 4 the scan of the outputs).
+inline unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; }
+
 // Polls the calling thread's 2D sweeps wait for (stride_sweep_wait); 0: no such sweeps.
 int sweep_wait();
 

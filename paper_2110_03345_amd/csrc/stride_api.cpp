@@ -963,9 +963,6 @@ int check_finite(unsigned* flag, hipStream_t s, std::initializer_list<OutArray> 
 // (words 0-3 hold the vp and medium checks).
 unsigned* finite_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 4; }
 
-// Word 5: set when the blocks of a resident sweep gave up waiting for each other.
-unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; }
-
 // Polls a 2D sweep of the calling thread waits for (stride_sweep_wait).
 thread_local int g_sweep_wait = kResidentPatience;
 

@@ -76,6 +76,8 @@ struct SlotJob {
     int m = 0;                           // full-history / segmented adjoint: next step
     int wa = 0;                          // adjoint ping-pong
     int imaged = 0;                      // adjoint: first step whose term a sweep kept on the chip added
+    unsigned* err = nullptr;             // set when blocks of such a sweep of this shot gave up waiting
+    bool swept = false;                  // the shot has run such sweeps
     long long left = 0;                  // ticks until the current phase ends
     // segmented history: segment starts, v buffer pool[0, vbuf), working pair
     // pool[vbuf], pool[vbuf + 1], start state of segment k in pool[vbuf + 2k],
@@ -121,7 +123,7 @@ struct stride_engine {
     long long ticks_total = 0;
     unsigned long long* words = nullptr;   // exchange area of the sweeps kept on the chip (or none)
     unsigned tag = 0;                      // highest step number in it
-    unsigned* late = nullptr;              // pinned: blocks of such a sweep gave up waiting
+    unsigned* late = nullptr;              // pinned: outputs of a shot are NaN, its blocks gave up waiting
 
     int tick_rows() const { return group_off[kGroups]; }
 };
@@ -466,7 +468,8 @@ bool resident_sweep(const stride_engine* E, SlotJob& J, int count, int* mode, Re
 // counts the ticks it ran of slot j.
 int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStream_t s)
 {
-    if (!E->words || !sweep_wait())
+    // (after blocks have given up, not until the caller has heard of it)
+    if (!E->words || !sweep_wait() || *(volatile unsigned*)E->late)
         return STRIDE_OK;
     const ResidentShape& rs = E->shape_plan->shared.rs;
     const long long area = resident_word_bytes(E->R, rs) / 8;
@@ -503,7 +506,7 @@ int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStr
                 p.injects = injects;
                 p.words = E->words + (long long)b.n++ * area;
                 p.tag = E->tag;
-                p.err = E->late;
+                p.err = E->slots[v[i].slot].err;
                 p.patience = sweep_wait();
             }
             if (launch_resident(E->dims, E->R, mode, E->cf, rs, b, s) != hipSuccess) {
@@ -513,6 +516,7 @@ int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStr
             E->tag += (unsigned)ticks;
             for (size_t i = from; i < to; ++i) {
                 SlotJob& J = E->slots[v[i].slot];
+                J.swept = true;
                 const int count = v[i].p.count;
                 used[v[i].slot] = count;
                 if (mode == kImageV) {
@@ -543,8 +547,8 @@ void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
     const long long ntraces = (long long)P.nrec * P.nt;
     if (J.mode == STRIDE_MODE_FORWARD) {
         launch_sample(rec_samples(P, J.traces), J.F.u[J.cur], P.nt - 1, s);
-        if (E->words)
-            launch_poison(E->late, {{J.traces}, {ntraces}}, s);
+        if (J.swept)
+            launch_poison(J.err, {{J.traces}, {ntraces}}, s, E->late);
         J.finished = true;
         return;
     }
@@ -587,8 +591,8 @@ void end_phase(stride_engine* E, SlotJob& J, hipStream_t s)
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, J.W.G, P.torder == 4 ? J.W.k : nullptr, J.vp, J.dvp, J.W.w[0],
                         J.W.w[1], s);
-    if (E->words)
-        launch_poison(E->late, {{J.dvp, (float*)J.misfit, J.traces}, {phys_points(P), 2, ntraces}}, s);
+    if (J.swept)
+        launch_poison(J.err, {{J.dvp, (float*)J.misfit, J.traces}, {phys_points(P), 2, ntraces}}, s, E->late);
     J.finished = true;
 }
 
@@ -751,6 +755,10 @@ int stride_engine_attach(stride_engine_t* E, const stride_plan_t* plan, int32_t 
     } else {
         return fail(STRIDE_E_INVALID_ARG, "mode must be FORWARD or GRADIENT");
     }
+    if (E->words) {
+        J.err = resident_flag(ws);
+        launch_fill(reinterpret_cast<float*>(J.err), 1, 0.f, s);
+    }
     STRIDE_HIP_TRY(hipGetLastError());
     J.used = true;
     E->slots[free_slot] = std::move(J);
@@ -784,8 +792,6 @@ int stride_engine_run(stride_engine_t* E, int32_t max_ticks, void* stream, int32
     if (ticks > cap)
         ticks /= 2;
 
-    if (E->late && *(volatile unsigned*)E->late)
-        return fail(STRIDE_E_HIP, "the blocks of a 2D sweep were not resident together");
     std::vector<long long> used_ticks(E->max_slots, 0);
     int rc = run_sweeps(E, ticks, used_ticks, s);
     if (rc)
@@ -879,6 +885,16 @@ int stride_engine_detach(stride_engine_t* E, int32_t slot)
     if (!E || slot < 0 || slot >= E->max_slots || !E->slots[slot].used)
         return fail(STRIDE_E_INVALID_ARG, "bad slot");
     E->slots[slot] = SlotJob();
+    return STRIDE_OK;
+}
+
+int stride_engine_check(stride_engine_t* E)
+{
+    if (!E)
+        return fail(STRIDE_E_INVALID_ARG, "NULL engine");
+    if (E->late && __atomic_exchange_n(E->late, 0u, __ATOMIC_ACQ_REL))
+        return fail(STRIDE_E_HIP, "the blocks of a 2D sweep were not resident together (neighbour wait "
+                                  "timed out); the outputs of its shots are NaN");
     return STRIDE_OK;
 }
 

@@ -529,21 +529,24 @@ void launch_copy(float* dst, const float* src, long long n, hipStream_t s)
     hipLaunchKernelGGL(copy_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, dst, src, n);
 }
 
-__global__ void poison_kernel(const unsigned* err, Outputs out)
+__global__ void poison_kernel(const unsigned* err, Outputs out, unsigned* report)
 {
     if (!*err)
         return;
+    if (report && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(report, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     for (int a = 0; a < 3; ++a)
         for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; out.p[a] && i < out.n[a];
              i += (long long)gridDim.x * blockDim.x)
             out.p[a][i] = __uint_as_float(0x7fffffffu);   // (two of them: a double NaN)
 }
 
-void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s)
+void launch_poison(const unsigned* err, const Outputs& out, hipStream_t s, unsigned* report)
 {
     const long long n = std::max({out.n[0], out.n[1], out.n[2]});
     if (n > 0)
-        hipLaunchKernelGGL(poison_kernel, dim3(std::min(grid_for(n, 256), 256)), dim3(256), 0, s, err, out);
+        hipLaunchKernelGGL(poison_kernel, dim3(std::min(grid_for(n, 256), 256)), dim3(256), 0, s, err, out,
+                           report);
 }
 
 // flag |= bit when any of the n values is NaN or infinite.

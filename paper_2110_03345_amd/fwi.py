@@ -163,6 +163,7 @@ class BatchGradient:
                     results[i] = (self.dvp[k].clone(), self.misfit[k].clone())
                 free.append(k)
         s.synchronize()
+        _abi.stride_engine_check(self.engine)
         J = 0.0
         with torch.cuda.stream(s):
             for i in sorted(results):

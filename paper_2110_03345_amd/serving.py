@@ -337,6 +337,8 @@ class Server:
             for b in self.buckets.values():
                 while b.inflight and b.inflight[0][0].query():
                     _, shots = b.inflight.popleft()
+                    if shots:
+                        _abi.stride_engine_check(b.handle)
                     for sh in shots:
                         self._shot_done(sh)
                         r = sh.req

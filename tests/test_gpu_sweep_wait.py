@@ -118,3 +118,98 @@ def test_every_output_of_a_stopped_sweep_is_nan(stopped):
     dvp, dwav = torch.zeros_like(x.vp), torch.zeros_like(x.wav)
     _abi.stride_backward(x.plan.handle, x.vp, x.wav, x.data, dvp, dwav, ws)
     assert dvp.isnan().all() and dwav.isnan().all()
+
+
+def _run(eng, stream, chunks):
+    """Runs the engine to its end, chunk k with the bound chunks[k] (the last one on)."""
+    k, done = 0, []
+    while True:
+        _abi.stride_sweep_wait(chunks[min(k, len(chunks) - 1)])
+        n, fin = _abi.stride_engine_run(eng, 16, 4, stream)
+        done += fin
+        k += 1
+        if n == 0:
+            stream.synchronize()
+            return done
+
+
+def _attach(eng, x, mode, stream):
+    out = [torch.zeros_like(x.data), torch.zeros(1, dtype=torch.float64, device="cuda"),
+           torch.zeros_like(x.vp)]
+    ws = x.plan.workspace(mode)
+    torch.cuda.synchronize()
+    _abi.stride_engine_attach(eng, x.plan.handle, mode, x.vp, float(x.w.vp.max()), x.wav, x.data, *out,
+                              ws, stream)
+    return (out if mode == S.STRIDE_MODE_GRADIENT else out[:1]), ws
+
+
+def test_engine_tells_of_stopped_sweeps_and_goes_on():
+    """A stopped sweep, in the last chunk as in an earlier one, makes the outputs of
+    its own shot NaN and no other's, and is told once; then the engine's shots
+    sweep again."""
+    x, y = Shot(seed=1), Shot(seed=2)
+    grad, fwd = S.STRIDE_MODE_GRADIENT, S.STRIDE_MODE_FORWARD
+    ref = {(id(a), grad): a.gradient() for a in (x, y)}
+    ref.update({(id(a), fwd): (a.forward(),) for a in (x, y)})
+    eng = _abi.stride_engine_create(S.make_grid(**x.w.grid_kwargs()), 4, 16, 16, False)
+    stream = torch.cuda.Stream()
+    try:
+        for mode, bad in ((fwd, [-1, -1, -1, 1]), (grad, [1, -1]), (grad, [-1] * 7 + [1]), (grad, [1])):
+            # x meets the bounds of `bad`; y comes in its last chunks or after them
+            out, ws = _attach(eng, x, mode, stream)
+            for k in range(len(bad)):
+                _abi.stride_sweep_wait(bad[k])
+                _abi.stride_engine_run(eng, 16, 4, stream)
+            other, wy = _attach(eng, y, mode, stream)
+            _run(eng, stream, [-1])
+            assert all(t.isnan().all() for t in out), (mode, bad)
+            assert all(torch.equal(a, b) for a, b in zip(other, ref[id(y), mode])), (mode, bad)
+            with pytest.raises(S.StrideError) as e:
+                _abi.stride_engine_check(eng)
+            assert e.value.code == _abi.STRIDE_E_HIP
+            _abi.stride_engine_check(eng)
+            for slot in (0, 1):
+                _abi.stride_engine_detach(eng, slot)
+            out, ws = _attach(eng, x, mode, stream)
+            _run(eng, stream, [-1])
+            _abi.stride_engine_check(eng)
+            assert all(torch.equal(a, b) for a, b in zip(out, ref[id(x), mode]))
+            _abi.stride_engine_detach(eng, 0)
+    finally:
+        _abi.stride_engine_destroy(eng)
+
+
+def test_inversion_and_server_refuse_stopped_sweeps():
+    """Their callers get an error, not NaN gradients (of which a descent step would
+    make a model at its lower bound)."""
+    from paper_2110_03345_amd import fwi
+    from paper_2110_03345_amd.serving import Server
+    from workloads.serving_mix import materialise, request_stream
+    x = Shot(nrec=12)
+    w = x.w
+    sv = fwi.Survey(w.shape, w.spacing, w.space_order, w.nb, w.vref, w.dt, w.nt, w.src_xyz, w.rec_xyz,
+                    x.wav[0], x.data.expand(2, -1, -1).contiguous())
+    batch = fwi.BatchGradient(sv, 2)
+    try:
+        ref = batch(x.vp, sv.wavelet, sv.observed, [0, 1])
+        _abi.stride_sweep_wait(1)
+        with pytest.raises(S.StrideError) as e:
+            batch(x.vp, sv.wavelet, sv.observed, [0, 1])
+        assert e.value.code == _abi.STRIDE_E_HIP
+        _abi.stride_sweep_wait(-1)
+        J, g = batch(x.vp, sv.wavelet, sv.observed, [0, 1])
+        assert J == ref[0] and torch.equal(g, ref[1])
+    finally:
+        batch.close()
+    specs = [materialise(s, nrec_2d=24, nrec_3d=32)
+             for s in request_stream(3, 5, rate_hz=200.0, nt_range=(60, 90), shots_range=(1, 2),
+                                     classes_2d=(150,), classes_3d=())]
+    srv = Server(hbm_budget=1 << 30, max_slots=4, max_chunk=16)
+    try:
+        _abi.stride_sweep_wait(1)
+        with pytest.raises(S.StrideError) as e:
+            srv.run(specs, realtime=False)
+        assert e.value.code == _abi.STRIDE_E_HIP
+        torch.cuda.synchronize()
+    finally:
+        srv.close()
