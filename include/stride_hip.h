@@ -390,23 +390,27 @@ int stride_accumulate(float* dst, const float* src, int64_t n, void* stream);
  * forms) scans what it wrote -- traces, misfit, dvp, dwavelet -- on its stream
  * with a small kernel, waits for the result, and returns STRIDE_E_NONFINITE,
  * naming the outputs, if any value is NaN or infinite (for example from a
- * wavelet or observed data holding one).  The outputs are left as computed.
+ * wavelet or observed data holding one), or STRIDE_E_HIP if a 2D sweep gave up
+ * (stride_sweep_wait).  The outputs are left as computed.
  * on = 0 turns the scan and its wait off.  Always returns STRIDE_OK. */
 int stride_check_finite(int32_t on);
 
 /* 2D sweeps kept on the chip.  Second-order 2D solves with the sponge, on grids
  * of up to about two million points, run each sweep as one cooperative launch
  * whose blocks wait for each other at every step or two; all other solves, and
- * these where such a launch is refused, launch every step.  The results are the
- * same bits.  polls bounds the calling thread's waits from here on, in polls of
- * about 1 us of a block's running time; polls < 0: the default, 2^26 (about a
- * minute), which only blocks that cannot run together reach (another kernel
- * holding part of the GPU throughout).  polls = 0: no such sweeps on this thread
- * -- for a GPU that several processes use at once, where the runtime runs the
- * cooperative launches of different processes in long turns (two processes with
- * gradients on 1024^2 grids: 156 ms a call against 20 with single steps).
- * An engine follows the thread that calls stride_engine_run.  Always returns
- * STRIDE_OK. */
+ * these where such a launch is refused or the stream is being captured, launch
+ * every step.  The results are the same bits.  polls bounds the calling thread's
+ * waits from here on, in polls of about 1 us of a block's running time; polls < 0:
+ * the default, 2^26 (about a minute), which only blocks that cannot run together
+ * reach (another kernel holding part of the GPU throughout).  A call whose blocks
+ * reach the bound leaves its outputs NaN and returns STRIDE_E_HIP where it checks
+ * them (stride_check_finite); with that check off the NaN outputs are the only
+ * sign.  For an engine see stride_engine_check.  polls = 0: no such sweeps on this
+ * thread -- for a GPU that several processes use at once, where the runtime runs
+ * the cooperative launches of different processes in long turns (two processes
+ * with gradients on 1024^2 grids: 24 and 156 ms a call, against 20 and 20 with a
+ * launch per step).  An engine follows the thread that calls stride_engine_run.
+ * Always returns STRIDE_OK. */
 int stride_sweep_wait(int64_t polls);
 
 /* Tracing of the time loops.  While enabled on the calling thread, every solve

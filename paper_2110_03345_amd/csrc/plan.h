@@ -134,6 +134,15 @@ inline long long phys_points(const stride_plan& P)
 // word 4 the scan of the outputs).
 inline unsigned* resident_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 5; }
 
+// Whether a stream is being captured into a graph.  2D sweeps kept on the chip need
+// the runtime's word that all their blocks run together, which it gives for a
+// cooperative launch, not for a replayed node: captured calls launch every step.
+inline bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return s && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone);
+}
+
 // Polls the calling thread's 2D sweeps wait for (stride_sweep_wait); 0: no such sweeps.
 int sweep_wait();
 

@@ -970,11 +970,12 @@ thread_local int g_sweep_wait = kResidentPatience;
 // `words` (zeroed here).  False when the plan or the calling thread has no such
 // sweeps, the sweep is shorter than two steps (blocks then do not wait for each
 // other, and one could store its final state before a neighbour has loaded its
-// frame) or the launch is refused; the caller then runs single steps.
+// frame), the stream is being captured or the launch is refused; the caller then
+// runs single steps.
 bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
                   hipStream_t s)
 {
-    if (!P.res.rs.tiles || !g_sweep_wait || p.count < 2 || p.count > (int)kResidentSteps)
+    if (!P.res.rs.tiles || !g_sweep_wait || p.count < 2 || p.count > (int)kResidentSteps || capturing(s))
         return false;
     launch_fill(words, resident_word_bytes(P.R, P.res.rs) / 4, 0.f, s);
     p.words = reinterpret_cast<unsigned long long*>(words);

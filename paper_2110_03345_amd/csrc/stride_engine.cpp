@@ -469,7 +469,7 @@ bool resident_sweep(const stride_engine* E, SlotJob& J, int count, int* mode, Re
 int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStream_t s)
 {
     // (after blocks have given up, not until the caller has heard of it)
-    if (!E->words || !sweep_wait() || *(volatile unsigned*)E->late)
+    if (!E->words || !sweep_wait() || *(volatile unsigned*)E->late || capturing(s))
         return STRIDE_OK;
     const ResidentShape& rs = E->shape_plan->shared.rs;
     const long long area = resident_word_bytes(E->R, rs) / 8;

@@ -213,3 +213,30 @@ def test_inversion_and_server_refuse_stopped_sweeps():
         torch.cuda.synchronize()
     finally:
         srv.close()
+
+
+def test_captured_backward_launches_every_step():
+    """stride_backward, the one call that waits for nothing with the finite check off,
+    captured: a kernel node per adjoint step and no cooperative launch, and right on
+    every replay."""
+    import ctypes
+    x = Shot()
+    ws = x.plan.workspace(S.STRIDE_MODE_GRADIENT)
+    _, dref, wref = x.autograd(ws)
+    dvp, dwav = torch.empty_like(dref), torch.empty_like(wref)
+    _abi.stride_check_finite(False)
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        _abi.stride_backward(x.plan.handle, x.vp, x.wav, x.data, dvp, dwav, ws)
+    n = ctypes.c_size_t()
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value > x.w.nt
+    g.instantiate()
+    for k in range(4):
+        dvp.fill_(float(k))
+        dwav.zero_()
+        x.forward()         # eager work, with a sweep of its own, between the replays
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dvp, dref) and torch.equal(dwav, wref), k
