@@ -142,6 +142,13 @@ constexpr int kResidentThreads = 1024;
 constexpr int kResidentItems = 2;    // quads per thread, at most
 constexpr unsigned kResidentSteps = (1u << 21) - 1;   // highest step number of a sweep
 constexpr int kResidentSide = 256;   // side of a tile with its ring, at most
+// Shortest sweep worth a cooperative launch: it costs about 25 us more than a
+// step's (48 x 56, us a gradient with sweeps / with a launch per step: nt 3 182 / 142,
+// 9 205 / 197, 13 213 / 231, 17 228 / 268; 200^2: 177 / 150, 197 / 200, 209 / 234,
+// 219 / 270).  At least 2 by its protocol: blocks of a sweep of one step do not wait
+// for each other, and one could store its final state before a neighbour has loaded
+// its frame.
+constexpr int kResidentLeast = 10;
 // Polls after which a block gives up waiting for its neighbours' words: a poll
 // takes about 1 us, so about a minute of the block's own running.
 constexpr int kResidentPatience = 1 << 26;

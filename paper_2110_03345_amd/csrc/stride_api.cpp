@@ -966,16 +966,18 @@ unsigned* finite_flag(void* ws) { return reinterpret_cast<unsigned*>(ws) + 4; }
 // Polls a 2D sweep of the calling thread waits for (stride_sweep_wait).
 thread_local int g_sweep_wait = kResidentPatience;
 
+// Whether solves of a plan may run 2D sweeps kept on the chip (and their flag counts).
+bool may_sweep(const stride_plan& P) { return P.res.rs.tiles && P.nt >= kResidentLeast; }
+
 // One 2D sweep kept on the chip, its exchange words in the two fields at
 // `words` (zeroed here).  False when the plan or the calling thread has no such
-// sweeps, the sweep is shorter than two steps (blocks then do not wait for each
-// other, and one could store its final state before a neighbour has loaded its
-// frame), the stream is being captured or the launch is refused; the caller then
-// runs single steps.
+// sweeps, the sweep is shorter than kResidentLeast steps, the stream is being
+// captured or the launch is refused; the caller then runs single steps.
 bool run_resident(const stride_plan& P, int mode, ResidentParams p, float* words, unsigned* err,
                   hipStream_t s)
 {
-    if (!P.res.rs.tiles || !g_sweep_wait || p.count < 2 || p.count > (int)kResidentSteps || capturing(s))
+    if (!may_sweep(P) || !g_sweep_wait || p.count < kResidentLeast || p.count > (int)kResidentSteps ||
+        capturing(s))
         return false;
     launch_fill(words, resident_word_bytes(P.R, P.res.rs) / 4, 0.f, s);
     p.words = reinterpret_cast<unsigned long long*>(words);
@@ -1571,7 +1573,7 @@ int forward_solve(const stride_plan& P, const float* vp, const float* wavelet, f
         return rc;
     launch_prep_k(P.dims, vp, P.g.dt, k, s);
     const std::initializer_list<OutArray> outs = {{traces, nullptr, (long long)P.nrec * P.nt, "traces"}};
-    if (P.res.rs.tiles) {
+    if (may_sweep(P)) {
         launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
         int id = g_timer.begin(s);
         if (run_resident(P, kStep, resident_forward(P, k, wavelet, 0, P.nt - 1, traces, true), u[0],
@@ -2034,7 +2036,8 @@ int forward_save(const stride_plan& P, const float* vp, const float* wavelet, fl
         return rc;
     float* tr = traces ? traces : W.traces;
     launch_prep_k(P.dims, vp, P.g.dt, W.k, s);
-    launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
+    if (may_sweep(P))
+        launch_fill(reinterpret_cast<float*>(resident_flag(ws)), 1, 0.f, s);
     TraceRange range_("forward sweep");
     Runner run(P, W, s, wavelet);
     const float* last;
@@ -2098,7 +2101,7 @@ int backward(const stride_plan& P, const float* vp, const float* wavelet, const 
     // the fourth-order accumulator holds k G
     launch_finalize_dvp(P.dims, W.G, P.torder == 4 ? W.k : nullptr, vp, dvp, W.w[0], W.w[1], s);
     // (also where only the forward's sweeps were kept on the chip)
-    if (P.res.rs.tiles)
+    if (may_sweep(P))
         launch_poison(resident_flag(ws), {{dvp, dwavelet}, {phys_points(P), (long long)P.nsrc * P.nt}}, s);
     HIP_TRY(hipGetLastError());
     return STRIDE_OK;
@@ -2592,7 +2595,7 @@ int stride_forward_save(const stride_plan_t* plan, const float* vp, const float*
         return rc;
     return check_finite(finite_flag(ws), s,
                         {{traces ? traces : W.traces, nullptr, (long long)plan->nrec * plan->nt, "traces"}},
-                        true);
+                        may_sweep(*plan));
 }
 
 int stride_backward(const stride_plan_t* plan, const float* vp, const float* wavelet,
@@ -2610,7 +2613,7 @@ int stride_backward(const stride_plan_t* plan, const float* vp, const float* wav
     return check_finite(finite_flag(ws), s,
                         {{dvp, nullptr, phys_points(*plan), "dvp"},
                          {dwavelet, nullptr, dwavelet ? (long long)plan->nsrc * plan->nt : 0, "dwavelet"}},
-                        true);
+                        may_sweep(*plan));
 }
 
 int stride_plan_gradient(const stride_plan_t* plan, const float* vp, const float* wavelet,
@@ -2637,7 +2640,7 @@ int stride_plan_gradient(const stride_plan_t* plan, const float* vp, const float
                         {{W.traces, nullptr, (long long)plan->nrec * plan->nt, "traces"},
                          {nullptr, misfit, 1, "misfit"},
                          {dvp, nullptr, phys_points(*plan), "dvp"}},
-                        true);
+                        may_sweep(*plan));
 }
 
 int stride_workspace_query(const stride_grid_t* grid, int32_t nsrc, int32_t nrec, int32_t mode,

@@ -240,3 +240,12 @@ def test_captured_backward_launches_every_step():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(dvp, dref) and torch.equal(dwav, wref), k
+
+
+@pytest.mark.parametrize("nt,want", [(2, (1, 1, 2, 2)), (9, (8, 8, 9, 9)), (10, (9, 9, 10, 1)),
+                                     (11, (10, 1, 11, 1))])
+def test_short_sweeps_launch_every_step(nt, want):
+    """Sweeps of fewer than ten steps, which a cooperative launch would slow down."""
+    x = Shot(nt=nt)
+    assert launches(x.gradient) == want
+    assert launches(x.forward) == want[:2] + (0, 0)
