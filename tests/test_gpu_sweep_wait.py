@@ -249,3 +249,60 @@ def test_short_sweeps_launch_every_step(nt, want):
     x = Shot(nt=nt)
     assert launches(x.gradient) == want
     assert launches(x.forward) == want[:2] + (0, 0)
+
+
+@pytest.mark.parametrize("kw", [dict(shape=(50, 41)), *GIVE_UP], ids=["one_tile", "two_steps", "one_quad", "two_quads"])
+@pytest.mark.parametrize("frac", [1.0, 0.7, 0.5])
+def test_histories_run_as_sweeps(kw, frac):
+    """Full history: one launch forward and one adjoint.  Segmented: the forward in a
+    launch up to each stored start, the last two segments in one, a launch to
+    recompute each segment but the last, and one adjoint launch a segment.  The
+    binomial schedule launches every step.  The same bits throughout."""
+    x = Shot(**dict(kw, nt=60))
+    ref = x.gradient()
+    ws = x.plan.workspace(S.STRIDE_MODE_GRADIENT,
+                          int(x.plan.workspace_bytes(S.STRIDE_MODE_GRADIENT) * frac))
+    path, steps, K = x.plan.gradient_path(ws.numel())
+    assert path == (S.STRIDE_PATH_FULL_HISTORY if frac == 1.0 else S.STRIDE_PATH_SEGMENTED)
+    want = (59, 1, 60, 1) if frac == 1.0 else (steps, 2 * (K - 1), 60, K)
+    assert launches(lambda: x.gradient(ws)) == want
+    assert all(torch.equal(a, b) for a, b in zip(x.gradient(ws), ref))
+    if frac == 0.5:
+        x.plan = S.Plan.from_workload(x.w, checkpointing=1)
+        assert x.plan.gradient_path(ws.numel())[0] == S.STRIDE_PATH_BINOMIAL
+        fs, fl, as_, al = launches(lambda: x.gradient(ws))
+        assert fs == fl >= 59 and as_ == al == 60
+        assert all(torch.equal(a, b) for a, b in zip(x.gradient(ws), ref))
+
+
+def test_sweeps_beside_other_work():
+    """Threads with a stream each: sweeps of one tile, of many and of two quads a
+    thread, and 3D steps that fill the GPU: the bits of each alone."""
+    shots = [Shot(shape=(50, 41), nt=300), Shot(nt=200), Shot(shape=(400, 390), nt=120, space_order=10),
+             Shot(shape=(1010, 1037), nt=60)]
+    w3 = W.tiny_3d(n=(140, 150, 130), nt=40)
+    p3 = S.Plan.from_workload(w3)
+    vp3, wav3 = torch.from_numpy(w3.vp).cuda(), torch.from_numpy(w3.wavelet).cuda()
+    jobs = [x.gradient for x in shots] + [lambda: (p3.forward(vp3, wav3),)]
+    refs = [f() for f in jobs]
+    torch.cuda.synchronize()
+    wrong, gate = [], threading.Barrier(len(jobs))
+
+    def work(f, ref):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                gate.wait()
+                for k in range(12):
+                    out = f()
+                    s.synchronize()
+                    if not all(torch.equal(a, b) for a, b in zip(out, ref)):
+                        wrong.append(("bits", k))
+        except Exception as e:      # (an assertion in a thread is not the test's)
+            wrong.append(repr(e))
+    threads = [threading.Thread(target=work, args=jr) for jr in zip(jobs, refs)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
