@@ -555,12 +555,10 @@ __global__ __launch_bounds__(64 * WAVES) void step2d_batched(Dims d, StencilCoef
     step2d_body<R, ADJ, RY, WAVES, MODE>(d, cf, st.sp, st.p, ls, blockIdx.x);
 }
 
-// Occupancy of the single-shot 3D kernels: the leapfrog steps, the fourth-order
-// launches with one stencil field and the y = 0 medium step stay within 128
-// VGPRs (4 waves per SIMD) by themselves; the attribute holds the compiler to
-// it where the launch shapes count on it.  (The batched kernels hold their
-// slot's parameters in registers as well; they are left to the compiler, which
-// keeps them free of spills.)
+// Occupancy of the 3D kernels: the leapfrog steps, the fourth-order launches with
+// one stencil field and the y = 0 medium step stay within 128 VGPRs (4 waves per
+// SIMD) by themselves; the attribute holds the compiler to it for a single shot,
+// whose launch shapes count on it.
 template <bool ADJ, int MODE>
 constexpr int min_waves_3d()
 {
@@ -579,7 +577,11 @@ template <int R, bool ADJ, int VX, int WAVES, int MODE>
 __global__ __launch_bounds__(64 * WAVES) void step3d_batched(Dims d, StencilCoef cf, LaunchShape ls,
                                                              const SlotStep* table)
 {
-    const SlotStep st = table[blockIdx.y];
+    // as constant memory, so that the parameters are loaded where they are used, like
+    // a single shot's: a copy of them lives in registers throughout (131 VGPRs at
+    // order 10 with one stencil field, three waves per SIMD, instead of 110 and four)
+    const SlotStep& st =
+        (const SlotStep&)((const __attribute__((address_space(4))) SlotStep*)(uintptr_t)table)[blockIdx.y];
     if (!st.active)
         return;
     step3d_body<R, ADJ, VX, WAVES, MODE, true>(d, cf, st.sp, st.p, ls, blockIdx.x);

@@ -69,3 +69,20 @@ def test_2d_sweeps_fit_their_block():
     assert len(sweeps) == 15, sorted(sweeps)
     bad = {k: r for k, r in sweeps.items() if r["vgpr"] > 128 or r["occupancy"] < 4}
     assert not bad, bad
+
+
+def test_batched_3d_steps_meet_the_single_shots_occupancy():
+    """The batched forms of the same kernels, whose slots' parameters come from a
+    table in memory: four waves per SIMD as well."""
+    import re
+    res = _resources()
+    want = {(R, adj, vx, mode) for R in (4, 5)
+            for adj, vx, modes in ((0, 4, (0, 1, 2, 4)), (1, 4, (5, 6)), (1, 2, (0,))) for mode in modes}
+    seen = {}
+    for name, r in res.items():
+        m = re.search(r"step3d_batchedILi(\d)ELb(\d)ELi(\d)ELi4ELi(\d)E", name)
+        if m:
+            seen[tuple(int(x) for x in m.groups())] = r
+    assert not want - set(seen), want - set(seen)
+    bad = {k: seen[k] for k in want if seen[k]["vgpr"] > 128 or seen[k]["occupancy"] < 4}
+    assert not bad, bad
