@@ -404,9 +404,24 @@ int get_exec(stride_engine* E, int ticks, const int* gy, hipStream_t s, hipGraph
     return STRIDE_OK;
 }
 
-// Shortest chunk worth launches of its own: at 592^2 eight steps of four slots
-// take about 35 us (launch, state in and out), as ticks 55.
+// Shortest chunk run as sweeps kept on the chip.
 constexpr int kResidentChunk = 8;
+
+// Whether `shots` sweeps of one kind and `count` steps, in `launches` launches, take
+// no longer than ticks of these slots.  A tick is one launch for all of them; a
+// sweep's launch, with its states in and out, holds as many as the chip does, which
+// at 1064^2 is one: short chunks of many large shots tick.  Times in us, fitted to
+// engine runs of 1 to 16 shots at 104^2 to 1064^2 (a chunk of ticks costs 24 beside
+// them).  300 steps at 1064^2, as sweeps / as ticks: gradients of 8 shots in chunks
+// of 8 27.9 / 22.6 ms, of 16 19.8 / 22.1, of 64 13.8 / 21.6; forward solves of 16
+// shots in chunks of 16 17.4 / 13.6, of 64 11.8 / 13.9.
+bool sweeps_pay(const Dims& d, int mode, int shots, int launches, int count)
+{
+    const double step = mode == kStep ? 2.2 : mode == kStepV ? 2.4 : 2.9;
+    const double point = mode == kStep ? 2.3e-6 : mode == kStepV ? 2.6e-6 : 3.8e-6;
+    const double tick = 5.2 + shots * ((mode == kImageV ? 0.25 : 0.1) + point * (double)d.total);
+    return launches * (27.0 + count * step) <= 24.0 + count * tick;
+}
 
 // The next `count` ticks of a slot as one sweep kept on the chip: forward solves
 // and full histories of second order in time.  False: they run as ticks.
@@ -493,6 +508,8 @@ int run_sweeps(stride_engine* E, int ticks, std::vector<long long>& used, hipStr
             injects = injects || w.p.injects;
         const size_t per = (size_t)E->shape_plan->shared.slots;
         const size_t launches = (v.size() + per - 1) / per;
+        if (!sweeps_pay(E->dims, mode, (int)v.size(), (int)launches, ticks))
+            continue;
         for (size_t l = 0; l < launches; ++l) {
             const size_t from = l * v.size() / launches, to = (l + 1) * v.size() / launches;
             if (E->tag + (unsigned)ticks > kResidentSteps) {
@@ -722,8 +739,7 @@ int stride_engine_attach(stride_engine_t* E, const stride_plan_t* plan, int32_t 
         if (rc)
             return rc;
         launch_prep_k(plan->dims, vp, plan->g.dt, J.F.k, s);
-        launch_fill(J.F.u[0], plan->dims.total, 0.f, s);
-        launch_fill(J.F.u[1], plan->dims.total, 0.f, s);
+        launch_fill(J.F.u[0], (J.F.u[1] - J.F.u[0]) + plan->dims.total, 0.f, s);   // u^0, u^-1
         J.left = plan->nt - 1;
     } else if (mode == STRIDE_MODE_GRADIENT) {
         if ((!observed && plan->nrec > 0) || !misfit || !dvp)
@@ -740,14 +756,14 @@ int stride_engine_attach(stride_engine_t* E, const stride_plan_t* plan, int32_t 
         J.path = grad_path(*plan, (long long)J.W.pool.size(), J.W.snaps);
         J.history = J.path.kind == GradPath::kFull;
         J.seg = J.path.kind == GradPath::kSegmented;
+        // G and the adjoint fields, which follow one another
+        launch_fill(J.W.G, (J.W.w[1] - J.W.G) + plan->dims.total, 0.f, s);
         if (J.history || J.seg) {
-            for (float* f : {J.W.G, J.W.w[0], J.W.w[1]})
-                launch_fill(f, plan->dims.total, 0.f, s);
             J.fc = J.W.w[0];
             J.fp = J.W.w[1];
         } else {
             J.cursor = std::make_unique<StepCursor>(plan->nt, J.W.snaps, J.W.peak);
-            for (float* f : {J.W.pool[0], J.W.pool[1], J.W.G, J.W.w[0], J.W.w[1]})
+            for (float* f : {J.W.pool[0], J.W.pool[1]})
                 launch_fill(f, plan->dims.total, 0.f, s);
         }
         J.phase = 0;

@@ -306,3 +306,31 @@ def test_sweeps_beside_other_work():
     for t in threads:
         t.join()
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("chunk,sweeps", [(8, False), (64, True)])
+def test_engine_takes_the_cheaper_of_sweeps_and_ticks(chunk, sweeps):
+    """Eight shots of a grid of which the chip holds one sweep: short chunks tick, all
+    shots in one launch, long ones sweep shot after shot.  (A bound of one poll tells
+    them apart.)"""
+    shots = [Shot(shape=(1010, 1037), nt=65, seed=i) for i in range(8)]
+    ref = [x.forward() for x in shots]
+    eng = _abi.stride_engine_create(S.make_grid(**shots[0].w.grid_kwargs()), 8, 16, chunk, True)
+    stream = torch.cuda.Stream()
+    try:
+        for bound in (-1, 1):
+            out = [_attach(eng, x, S.STRIDE_MODE_FORWARD, stream) for x in shots]
+            _abi.stride_sweep_wait(bound)
+            while _abi.stride_engine_run(eng, chunk, 8, stream)[0]:
+                pass
+            stream.synchronize()
+            if sweeps and bound == 1:
+                with pytest.raises(S.StrideError):
+                    _abi.stride_engine_check(eng)
+            else:
+                _abi.stride_engine_check(eng)
+                assert all(torch.equal(o[0], r) for (o, _), r in zip(out, ref))
+            for slot in range(8):
+                _abi.stride_engine_detach(eng, slot)
+    finally:
+        _abi.stride_engine_destroy(eng)
