@@ -9,13 +9,8 @@
 //          G += w^{m+1} (L u^m + S^m)   (gradient w.r.t. k; Sec. 2.2 reduced
 //          gradient <grad_m L* w, dm>).
 //
-// The kernels are HBM-bound (16 B per forward update, 28 B per adjoint update):
-// no MFMA.  Tiles are 64 wide along the contiguous axis (one wave64 per tile
-// row, 256 B coalesced) and 16 rows high; the u^n tile plus its halo sits in
-// LDS.  In 3D each block marches along axis 0 over a chunk of planes, keeping
-// the 2r+1 values of its column in registers (2.5D blocking), so each plane of
-// u^n is read once from HBM and the axis-0 neighbours never touch LDS.
-
+// The step kernels and what bounds them: step_kernels.h, step3d_body.h (3D) and
+// step2d_resident.h (2D sweeps kept on the chip).
 //
 // This file holds the small kernels and the launchers; the step kernels
 // live in step_kernels.h and compile in their own translation units.
@@ -624,7 +619,7 @@ __device__ __forceinline__ float pml_decay(const PmlGeom& g, const PmlParams& pp
 // others keep their memory variables and get no term); corr: the sum so far.
 // Neighbours are read with buffer loads, whose range check gives the zeros
 // beyond the array: one select per load instead of one per value.
-template <int R, int AX>
+template <int R, bool NT, int AX>
 __device__ __forceinline__ void pml_axis_term(const StencilCoef& cf, const PmlParams& pp,
                                               const PmlGeom& g, const PmlAt& at, const bool* on,
                                               PmlVec& corr)
@@ -713,13 +708,13 @@ __device__ __forceinline__ void pml_axis_term(const StencilCoef& cf, const PmlPa
         next[k] = on[k] ? n : p0[k];
         corr[k] = on[k] ? corr[k] - (d1p[k] + c) : corr[k];
     }
-    bstorev<4>(rc, at.off, chi);
-    bstorev<4>(plane_rsrc(pp.psin[a] + at.plane, at.plane_bytes), at.off, next);
+    bstorev<4, NT ? 2 : 0>(rc, at.off, chi);
+    bstorev<4, NT ? 2 : 0>(plane_rsrc(pp.psin[a] + at.plane, at.plane_bytes), at.off, next);
 }
 
 // The correction of points (i0, i1, 4 q ..), i0 uniform over the wave.  Rows are
 // pitched to whole quads; points past the end of a row keep what they hold.
-template <int R>
+template <int R, bool NT>
 __device__ __forceinline__ void pml_quad(const StencilCoef& cf, const PmlParams& pp, const PmlGeom& g,
                                          int i0, int i1, int q)
 {
@@ -743,17 +738,17 @@ __device__ __forceinline__ void pml_quad(const StencilCoef& cf, const PmlParams&
     PmlVec un = bloadv<4, 0>(rn, at.off);
     const PmlVec kv = bloadv<4, 0>(plane_rsrc(pp.k + at.plane, at.plane_bytes), at.off);
     if (z)
-        pml_axis_term<R, 0>(cf, pp, g, at, live, corr);
+        pml_axis_term<R, NT, 0>(cf, pp, g, at, live, corr);
     if (y)
-        pml_axis_term<R, 1>(cf, pp, g, at, live, corr);
+        pml_axis_term<R, NT, 1>(cf, pp, g, at, live, corr);
     if (any)
-        pml_axis_term<R, 2>(cf, pp, g, at, x, corr);
+        pml_axis_term<R, NT, 2>(cf, pp, g, at, x, corr);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         on[k] = x[k] || (live[k] && (z || y));
         un[k] = on[k] ? fmaf(kv[k], corr[k], un[k]) : un[k];
     }
-    bstorev<4>(rn, at.off, un);
+    bstorev<4, NT ? 2 : 0>(rn, at.off, un);
 }
 
 // Ranges of a correction launch: blocks of kPmlWaves waves (one per plane or row
@@ -767,7 +762,8 @@ struct PmlRanges {
 
 constexpr int kPmlWaves = 4;
 
-template <int R>
+// NT: non-temporal stores.
+template <int R, bool NT>
 __global__ __launch_bounds__(64 * kPmlWaves) void pml_layer_kernel(StencilCoef cf, PmlParams pp, PmlGeom g,
                                                         PmlRanges r)
 {
@@ -784,7 +780,7 @@ __global__ __launch_bounds__(64 * kPmlWaves) void pml_layer_kernel(StencilCoef c
         if (zl >= g.b0 || t >= g.nn[1] * r.nq)
             return;
         const int i1 = t / r.nq;
-        pml_quad<R>(cf, pp, g, side ? g.b0 + g.pl[0] + zl : zl, i1, t - i1 * r.nq);
+        pml_quad<R, NT>(cf, pp, g, side ? g.b0 + g.pl[0] + zl : zl, i1, t - i1 * r.nq);
     } else if (b < r.end1) {
         const int groups = (2 * g.b + kPmlWaves - 1) / kPmlWaves;
         const int e = b - r.end0, plane = e / (groups * r.cols1), f = e - plane * groups * r.cols1;
@@ -792,14 +788,14 @@ __global__ __launch_bounds__(64 * kPmlWaves) void pml_layer_kernel(StencilCoef c
         const int rl = (f - col * groups) * kPmlWaves + wave, q = col * 64 + lane;
         if (rl >= 2 * g.b || q >= r.nq)
             return;
-        pml_quad<R>(cf, pp, g, g.b0 + plane, rl < g.b ? rl : g.pl[1] + rl, q);
+        pml_quad<R, NT>(cf, pp, g, g.b0 + plane, rl < g.b ? rl : g.pl[1] + rl, q);
     } else if (b < r.end2) {
         const int nl = r.ql + r.nq - r.qr;
         const int e = b - r.end1, plane = e / r.cols2;
         const int t = (e - plane * r.cols2) * (64 * kPmlWaves) + (int)threadIdx.x, i1 = t / nl, ql = t - i1 * nl;
         if (i1 >= g.pl[1])
             return;
-        pml_quad<R>(cf, pp, g, g.b0 + plane, g.b + i1, ql < r.ql ? ql : r.qr + ql - r.ql);
+        pml_quad<R, NT>(cf, pp, g, g.b0 + plane, g.b + i1, ql < r.ql ? ql : r.qr + ql - r.ql);
     }
 }
 
@@ -833,10 +829,19 @@ void launch_pml_correction(const Dims& d, int R, const StencilCoef& cf, const Pm
     r.end1 = r.end0 + (2 * g.b + kPmlWaves - 1) / kPmlWaves * r.cols1 * g.pl[0];
     r.end2 = r.end1 + r.cols2 * g.pl[0];
     const dim3 grid((unsigned)((r.end2 + kXcds - 1) / kXcds * kXcds));
-    if (R == 4)
-        hipLaunchKernelGGL(pml_layer_kernel<4>, grid, dim3(64 * kPmlWaves), 0, s, cf, pp, g, r);
-    else
-        hipLaunchKernelGGL(pml_layer_kernel<5>, grid, dim3(64 * kPmlWaves), 0, s, cf, pp, g, r);
+    // What it writes is read in the next step: kept in the Infinity Cache while what a
+    // step touches (u, u', k, and psi, psi', chi of the layer of each axis) fits 0.85 of
+    // it.  Beyond that non-temporal stores leave the room to what is read in this
+    // launch; us a step with the leapfrog, order 10, layer 30, ordinary / non-temporal:
+    // 160^3 51 / 64, 200^3 85 / 109, 210^3 (210 MiB) 112 / 119, 220^3 (226 MiB) 131 / 127,
+    // 316^3 312 / 308.
+    double fields = 3.0;
+    for (int ax = three ? 0 : 1; ax < 3; ++ax)
+        fields += 3.0 * 2.0 * (ax == 0 ? g.b0 : g.b) / g.nn[ax];
+    const bool nt = fields * 4.0 * (double)d.total > 0.85 * (double)kCacheBytes;
+    const auto kernel = R == 4 ? (nt ? pml_layer_kernel<4, true> : pml_layer_kernel<4, false>)
+                               : (nt ? pml_layer_kernel<5, true> : pml_layer_kernel<5, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * kPmlWaves), 0, s, cf, pp, g, r);
 }
 
 // Padded coordinates of linear index t over the padded grid (no pitch) and the
@@ -970,7 +975,7 @@ __global__ __launch_bounds__(256) void medium_adjoint_kernel(Dims d, StencilCoef
 // come from register queues, those in the plane from LDS (y over the tile and
 // its whole frame, gam_1 w^{m+1} over the rows of the frame, gam_2 w^{m+1} over its
 // columns; two buffers, one barrier per plane).  Bound by memory: eleven fields
-// pass once per step.  At 252^3, order 10: 168 us a step (4.2 TB/s of needed
+// pass once per step.  At 252^3, order 10: 172 us a step (4.1 TB/s of needed
 // bytes); 337 with a thread per point and every tap along axis 0 loaded again.
 template <int R, bool Y2>
 __global__ __launch_bounds__(256) void medium_adjoint3d_kernel(Dims d, StencilCoef cf, SpongeCoef sp,

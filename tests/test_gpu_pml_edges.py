@@ -33,3 +33,24 @@ def test_pml_edges(shape, nb, order):
     plan = S.Plan.from_workload(w, boundary=1)
     tr = plan.forward(torch.from_numpy(w.vp).cuda(), torch.from_numpy(w.wavelet).cuda())
     check_traces(tr.cpu().numpy(), ref, 1e-4)
+
+
+@pytest.mark.parametrize("order", [8, 10])
+def test_pml_beyond_the_cache(order):
+    """A grid whose layer writes past the Infinity Cache (non-temporal stores), with
+    sources and receivers at corners of the physical grid and a layer of a thousand
+    times the usual strength, so that in a few steps it changes the traces by a
+    twelfth to a quarter."""
+    shape, nt = (171, 150, 163), 26
+    w = W.tiny_3d(n=shape, nt=nt, space_order=order, nb=30, nsrc=4, nrec=40, seed=order, vref=1.5e6)
+    rng = np.random.default_rng(order)
+    ext = np.array([(n - 1) * w.spacing for n in shape])
+    # four corners; a source and ten receivers within two cells of each
+    edge = np.repeat(rng.integers(0, 2, (4, 3)), 11, axis=0) * ext
+    points = edge + np.where(edge > 0, -1, 1) * rng.uniform(0, 2, (44, 3)) * w.spacing
+    w.src_xyz, w.rec_xyz = points[::11], np.delete(points, np.s_[::11], axis=0)
+    w.wavelet = rng.standard_normal((4, nt)).astype(np.float32)
+    ref = oracle.forward_pml(oracle.Grid(**w.grid_kwargs()), w.vp, w.src_xyz, w.wavelet, w.rec_xyz)
+    plan = S.Plan.from_workload(w, boundary=1)
+    tr = plan.forward(torch.from_numpy(w.vp).cuda(), torch.from_numpy(w.wavelet).cuda()).cpu().numpy()
+    check_traces(tr, ref, 1e-4)
