@@ -21,7 +21,8 @@ adjoint step without imaging (reads w^{m+1}, w^{m+2}, k; writes w^m: 16 bytes)
 and one adding two imaging terms (also reads v^m, v^{m+1}, G and writes G: 32
 bytes), 24 bytes per grid-point update on average; the fused adjoint of
 binomial checkpointing reads u^m, w^{m+1}, w^{m+2}, k, G and writes w^m, G (28
-bytes).  The line gives both fractions.  Beside it, the forward step at 16
+bytes).  The line gives both fractions (2D sweeps kept on the chip move v only
+and name the exchange between blocks as their bound).  Beside it, the forward step at 16
 bytes (reads u^n, u^{n-1}, k; writes u^{n+1}).  Kernel times come from HIP
 events the library records on the solve stream around its time loops during
 the timed steps, with the step and launch counts.  The "binomial" key times
@@ -57,9 +58,6 @@ MEASURED_TRAFFIC = {
     # turn; per-dispatch figures averaged over the pair), "fused" = the adjoint
     # with its own stencil of u^m (mode 0, binomial checkpointing), "forward" =
     # the plain forward step of a forward solve
-    "config2/pair": {"sha256": "a3a270b9d6f6091d300dcb38d0a3b444e81e7962e9e1de5ce89ad9c84cea5057",
-                     "fetch_kib": 10940.59, "write_kib": 7153.05,
-                     "copy_fetch_kib": 524308.00, "copy_write_kib": 1048576.0},
     "config4/pair": {"sha256": "a3a270b9d6f6091d300dcb38d0a3b444e81e7962e9e1de5ce89ad9c84cea5057",
                      "fetch_kib": 338138.13, "write_kib": 187230.00,
                      "copy_fetch_kib": 524315.50, "copy_write_kib": 1048576.0},
@@ -97,6 +95,10 @@ ADJ_BYTES = 28   # read u^m, w^{m+1}, w^{m+2}, k, G; write w^m, G
 # full history: the adjoint reads v^m instead of u^m and G is read and written
 # every other step (two imaging terms per even step): 16 B and 32 B in turn
 ADJ_BYTES_PAIRED = 24
+# a 2D sweep kept on the chip moves v only: stored by the forward, read by the
+# adjoint (a forward solve moves nothing per step); its steps are bound by the
+# exchange between blocks, not by HBM
+V_BYTES = 4
 # fourth-order adjoint step: read u^m, k, write p; read w^{m+1}, k, write q;
 # read q, p, w^{m+1}, w^{m+2}, k, H, write w^m, H
 ADJ4_BYTES = 56
@@ -508,12 +510,13 @@ def measure(name, args, dev, headline, built=None, checkpointing=0, forward=True
     path, path_fsteps, nseg = plan.gradient_path(ws_bytes)
     full_history = path == S.STRIDE_PATH_FULL_HISTORY
     from_v = path != S.STRIDE_PATH_BINOMIAL
-    adj_bytes = ADJ_BYTES_PAIRED if from_v else ADJ_BYTES
+    adj_swept, fwd_swept = adj_spl > 1, f_n > f_l     # sweeps kept on the chip
+    adj_bytes = V_BYTES if adj_swept else ADJ_BYTES_PAIRED if from_v else ADJ_BYTES
     adj_gbs = adj_bytes * npad / adj_step_s / 1e9
     # segmented: the steps before the last segment run once without v (first
     # sweep) and once with it (recomputation); every other step keeps v
     v_steps = w.nt - 1 if from_v else 0
-    fwd_in_grad_bytes = (FWD_BYTES * path_fsteps + 4 * v_steps) / path_fsteps
+    fwd_in_grad_bytes = ((0 if fwd_swept else FWD_BYTES) * path_fsteps + 4 * v_steps) / path_fsteps
     path_name = {S.STRIDE_PATH_FULL_HISTORY: "full history",
                  S.STRIDE_PATH_SEGMENTED: "segmented history, %d segments" % nseg,
                  S.STRIDE_PATH_BINOMIAL: "binomial checkpointing"}[path]
@@ -530,15 +533,16 @@ def measure(name, args, dev, headline, built=None, checkpointing=0, forward=True
         "adjoint": {
             "kernel": ("adjoint leapfrog steps, imaging from the stored v, a sweep of %.0f steps "
                        "per launch kept on the chip (step2d_resident<R, 5, ., .>)" % adj_spl)
-                      if from_v and adj_spl > 1 else
+                      if adj_swept else
                       ("adjoint leapfrog steps, imaging from the stored v two terms per even step "
                        "(step%dd_kernel<R, true, ., ., 6> and <..., 5> in turn; per-launch figures "
                        "average the pair)" % w.ndim) if from_v else
                       "adjoint leapfrog step + imaging (step%dd_kernel<R, true, ., ., 0>)" % w.ndim,
+            "bound": "exchange between blocks" if adj_swept else "hbm",
             "bytes_per_point": adj_bytes,
             "achieved": adj_gbs,
             "frac": adj_gbs / HBM_PEAK_GBS,
-            "frac_at_28B": ADJ_BYTES * npad / adj_step_s / 1e9 / HBM_PEAK_GBS,
+            "frac_at_28B": None if adj_swept else ADJ_BYTES * npad / adj_step_s / 1e9 / HBM_PEAK_GBS,
             "us_per_launch": adj_launch_s * 1e6,
             "us_per_step": adj_step_s * 1e6,
             "steps_per_launch": adj_spl,
@@ -556,14 +560,16 @@ def measure(name, args, dev, headline, built=None, checkpointing=0, forward=True
         el_f, (ff_ms, ff_n, ff_l, _, _, _) = _timed(
             lambda _: plan.forward(vp_m, wav, traces=traces, ws=fws), steps)
         f_step = ff_ms * 1e-3 / max(ff_n, 1)
+        f_bytes = 0 if ff_n > ff_l else FWD_BYTES       # a sweep kept on the chip moves no field
         out["forward"] = {
             "kernel": ("forward leapfrog step (step%dd_kernel<R, false, ., ., 0>)" % w.ndim
-                       if ff_n <= ff_l else "forward leapfrog sweep (step2d_resident<R, 0, ., .>)"),
+                       if f_bytes else "forward leapfrog sweep (step2d_resident<R, 0, ., .>)"),
+            "bound": "hbm" if f_bytes else "exchange between blocks",
             "updates_per_s": npad * (w.nt - 1) * steps / el_f,
             "ms_per_solve": 1e3 * el_f / steps,
-            "bytes_per_point": FWD_BYTES,
-            "achieved": FWD_BYTES * npad / f_step / 1e9,
-            "frac": FWD_BYTES * npad / f_step / 1e9 / HBM_PEAK_GBS,
+            "bytes_per_point": f_bytes,
+            "achieved": f_bytes * npad / f_step / 1e9,
+            "frac": f_bytes * npad / f_step / 1e9 / HBM_PEAK_GBS,
             "us_per_launch": ff_ms * 1e3 / max(ff_l, 1),
             "us_per_step": f_step * 1e6,
         }
@@ -794,7 +800,7 @@ def main():
     adj = m["adjoint"]
     traffic = measured_traffic(m["traffic_key"])
     roofline = {
-        "bound": "hbm",
+        "bound": adj["bound"],
         "kernel": adj["kernel"],
         "achieved": adj["achieved"],
         "peak": HBM_PEAK_GBS,

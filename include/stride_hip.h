@@ -304,7 +304,7 @@ int stride_workspace_query(const stride_grid_t* grid, int32_t nsrc, int32_t nrec
  *     adjoint recomputing L u^m itself.
  * The library takes path 1 over path 2 when its cost model of the step
  * kernels says it is faster; all three give the same bits.  forward_steps:
- * forward step launches per gradient.  Errors: INVALID_ARG, WORKSPACE. */
+ * forward steps per gradient (fourth order: launches, two a step).  Errors: INVALID_ARG, WORKSPACE. */
 #define STRIDE_PATH_FULL_HISTORY 0
 #define STRIDE_PATH_SEGMENTED 1
 #define STRIDE_PATH_BINOMIAL 2
@@ -419,9 +419,8 @@ int stride_sweep_wait(int64_t polls);
  * stride_timing_read waits for the recorded events and returns, since the last
  * read, the time (ms), the time steps and the kernel launches of forward steps
  * (recomputation included) and of adjoint steps (recomputation excluded), then
- * clears them.  Every launch advances one step today; the counts are kept
- * apart so that a launch that advances several steps can be reported.  Any
- * output pointer may be NULL. */
+ * clears them.  A step takes one launch or more, a 2D sweep kept on the chip one
+ * launch for all its steps.  Any output pointer may be NULL. */
 int stride_timing_enable(int32_t on);
 int stride_timing_read(double* fwd_ms, int64_t* fwd_steps, int64_t* fwd_launches, double* adj_ms,
                        int64_t* adj_steps, int64_t* adj_launches);

@@ -355,7 +355,8 @@ void launch_step_mode(const Dims& d, int R, bool adjoint, int mode, const Stenci
                       const SpongeCoef& sp, const LaunchShape& ls, const StepParams& p, hipStream_t s);
 
 // One sweep kept on the chip; hipSuccess, or the launch error (nothing ran).
-// The exchange words must be zero (resident_word_bytes of them).
+// No exchange word (resident_word_bytes of them) may hold a step number of the sweep,
+// (tag, tag + count]: zero before the first, numbered on after that.
 hipError_t launch_resident(const Dims& d, int R, int mode, const StencilCoef& cf,
                            const ResidentShape& rs, const ResidentBatch& b, hipStream_t s);
 // Outputs of a solve (p NULL: none).

@@ -120,7 +120,7 @@ __device__ __forceinline__ void step3d_body(const Dims& d, const StencilCoef& cf
     const int gx = x0 + col, gy = y0 + row;
     const float* F[2] = {p.A, ADJ ? p.U : (MED2 ? p.B : p.A)};
 
-    // plane-independent geometry: byte offsets within a plane (-1 = outside)
+    // plane-independent geometry: byte offsets within a plane (kNoByte: outside)
     const int plane_bytes = (int)(s0 * 4);
     const int bo = gx < n2 && gy < n1 ? (gy * s1 + gx) * 4 : kNoByte;
     const int lo = (row + R) * LW + col + HQ;       // own points in the LDS tile

@@ -9,13 +9,12 @@
 //          G += w^{m+1} (L u^m + S^m)   (gradient w.r.t. k; Sec. 2.2 reduced
 //          gradient <grad_m L* w, dm>).
 //
-// The kernels are HBM-bound (16 B per forward update, 28 B per adjoint update):
-// no MFMA.  Tiles are 64 wide along the contiguous axis (one wave64 per tile
-// row, 256 B coalesced) and 16 rows high; the u^n tile plus its halo sits in
-// LDS.  In 3D each block marches along axis 0 over a chunk of planes, keeping
-// the 2r+1 values of its column in registers (2.5D blocking), so each plane of
-// u^n is read once from HBM and the axis-0 neighbours never touch LDS.
-
+// A step launch is HBM-bound (16 B per forward update, 28 B per adjoint update):
+// no MFMA.  Tiles are 64 wide along the contiguous axis; the u^n tile plus its
+// halo sits in LDS.  2D: 16 rows, one wave64 per tile row.  3D: a thread owns four
+// or two points of a row, a wave as many rows, and each block marches along axis
+// 0 over a chunk of planes, keeping the 2r+1 values of its columns in registers
+// (2.5D blocking), so that the axis-0 neighbours never touch LDS.
 //
 // This header holds the step kernels and their launch templates; the
 // translation units step2d.hip, step3d_fwd.hip and step3d_adj.hip each
@@ -60,8 +59,8 @@ __device__ __forceinline__ void unrolled_while(Fn&& fn)
 
 // Raw buffer access (CDNA): a descriptor over [base, base + bytes) returns 0
 // for any byte offset at or beyond `bytes`, so loads of points outside the
-// grid need no branch: their offset is set to 0xffffffff, and a plane outside
-// the grid gets bytes = 0.  Third descriptor word of the gfx9 family.
+// grid need no branch: their offset is set beyond any field (0xffffffff for single
+// values, kNoByte for vectors), and a plane outside the grid gets bytes = 0.  Third descriptor word of the gfx9 family.
 constexpr int kBufWord3 = 0x00020000;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const float* base, int bytes)
@@ -596,7 +595,7 @@ constexpr int vec3d()
     return (ADJ && !one) || MODE == kMedium ? kVx3dTwo : kVx3dOne;
 }
 
-// 2D tile shapes with compiled kernels (rows per thread, waves); tile_shape()
+// 2D tile shapes with compiled kernels (rows per thread, waves); tile_shape_2d()
 // returns one of these.  Without STRIDE_TILE_SWEEP: the shape of common.h.
 #ifdef STRIDE_TILE_SWEEP
 #define STRIDE_DISPATCH2D(L)                                                                      \

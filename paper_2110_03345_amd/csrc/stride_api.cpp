@@ -408,8 +408,15 @@ HostSamples build_resident_samples(const stride_plan& P, const ResidentShape& rs
 //    for each other: at 592^2 2.26 with 68 x 60, 2.7 with 40 x 37);
 //  - two quads per thread in small tiles (a step is mostly the items: at 1104^2
 //    2.4 us with 92 x 53, 2.5 with 92 x 69; two steps per exchange 2.5).
+// The weights of `cost` come from the steps measured with 1875 shapes on seven grids
+// (160 x 180 to 1104^2, order 8, and 522 x 551, order 10), fitted by least squares
+// and rounded: one quad per thread, per step, 2 ns a tile, 1.6 a frame quad and 0.8
+// less for each quad of a tile, in units of 0.4 ns; elsewhere only the order counts.
+// The shapes taken are within 1 % of the best measured with two steps per exchange,
+// within 13 % with one (6 % on average).
 // `shared`: the most steps per time of several sweeps side by side (592^2: four on
-// 56 tiles, 2.7 us a step of all four; two on 90 tiles 2.1).
+// 56 tiles, 2.7 us a step of all four; two on 90 tiles 2.1).  Its 2.1 and 2.6 us a
+// step are the means of such launches at one quad per thread and at two.
 struct ResidentChoice {
     ResidentShape one{}, shared{};
 };
@@ -703,8 +710,11 @@ bool stride::make_segments(long long nt, long long fields, std::vector<int>& sta
 
 // Full history when every state fits; otherwise the segmented history when a
 // cost model of the step kernels prefers it to the binomial schedule (whose
-// adjoint recomputes L u^m itself).  Step costs relative to the plain
-// second-order forward step, measured on MI355X (3D 316^3 / 2D 1104^2):
+// adjoint recomputes L u^m itself).  Costs of one launch per step relative to
+// the plain second-order forward step, measured on MI355X (3D 316^3 / 2D 1104^2)
+// with earlier forms of the 3D kernels and kept, since they fix the path a
+// workspace gets (3D now 1.27, 1.44, 2.08; 2D sweeps kept on the chip, which the
+// binomial schedule does not have, only widen the margin):
 // second order, forward keeping v 1.18 / 1.04, adjoint imaging from v in
 // pairs 1.48 / 1.30, fused adjoint 2.04 / 1.69; fourth order, forward 2.0
 // (two launches, keeping p or not), adjoint from the kept p 3.13 / 2.63
@@ -1037,7 +1047,7 @@ void geometry_free_plan(const stride_grid_t* grid, int nrec, stride_plan& P)
 // sweep visits every index once); with run = false it only replays the
 // bookkeeping, which stride_backward uses to find the pool state the forward
 // sweep left behind.  backward_phase launches recomputation and adjoint steps.
-// One launch advances one step, so steps and launches count alike.
+// Steps and launches count apart: a 2D sweep kept on the chip is one launch.
 struct Runner {
     const stride_plan& P;
     GradWs& W;
