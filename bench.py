@@ -58,15 +58,15 @@ MEASURED_TRAFFIC = {
     # turn; per-dispatch figures averaged over the pair), "fused" = the adjoint
     # with its own stencil of u^m (mode 0, binomial checkpointing), "forward" =
     # the plain forward step of a forward solve
-    "config4/pair": {"sha256": "a3a270b9d6f6091d300dcb38d0a3b444e81e7962e9e1de5ce89ad9c84cea5057",
-                     "fetch_kib": 338138.13, "write_kib": 187230.00,
-                     "copy_fetch_kib": 524315.50, "copy_write_kib": 1048576.0},
-    "config4/fused": {"sha256": "a3a270b9d6f6091d300dcb38d0a3b444e81e7962e9e1de5ce89ad9c84cea5057",
-                      "fetch_kib": 477481.36, "write_kib": 249640.00,
-                      "copy_fetch_kib": 524308.00, "copy_write_kib": 1048576.0},
-    "config4/forward": {"sha256": "a3a270b9d6f6091d300dcb38d0a3b444e81e7962e9e1de5ce89ad9c84cea5057",
-                        "fetch_kib": 240994.32, "write_kib": 124852.00,
-                        "copy_fetch_kib": 524315.50, "copy_write_kib": 1048576.0},
+    "config4/pair": {"sha256": "dfb6ee035c65e552305d2a7850b64b4d775e6ef0811150c3f29664f5d83b476f",
+                     "fetch_kib": 339116.43, "write_kib": 187230.00,
+                     "copy_fetch_kib": 524308.31, "copy_write_kib": 1048576.0},
+    "config4/fused": {"sha256": "dfb6ee035c65e552305d2a7850b64b4d775e6ef0811150c3f29664f5d83b476f",
+                      "fetch_kib": 477147.04, "write_kib": 249640.00,
+                      "copy_fetch_kib": 524315.69, "copy_write_kib": 1048576.0},
+    "config4/forward": {"sha256": "dfb6ee035c65e552305d2a7850b64b4d775e6ef0811150c3f29664f5d83b476f",
+                        "fetch_kib": 249256.09, "write_kib": 124852.00,
+                        "copy_fetch_kib": 524308.31, "copy_write_kib": 1048576.0},
 }
 
 
@@ -95,9 +95,10 @@ ADJ_BYTES = 28   # read u^m, w^{m+1}, w^{m+2}, k, G; write w^m, G
 # full history: the adjoint reads v^m instead of u^m and G is read and written
 # every other step (two imaging terms per even step): 16 B and 32 B in turn
 ADJ_BYTES_PAIRED = 24
-# a 2D sweep kept on the chip moves v only: stored by the forward, read by the
-# adjoint (a forward solve moves nothing per step); its steps are bound by the
-# exchange between blocks, not by HBM
+# a 2D sweep kept on the chip moves v only, stored by the forward and read by the
+# adjoint (beside its exchange words, 3 bytes a point and step at 1104^2, of which
+# a forward solve's traffic consists); its steps are bound by the exchange between
+# blocks, not by HBM
 V_BYTES = 4
 # fourth-order adjoint step: read u^m, k, write p; read w^{m+1}, k, write q;
 # read q, p, w^{m+1}, w^{m+2}, k, H, write w^m, H
