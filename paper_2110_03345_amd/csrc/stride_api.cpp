@@ -713,7 +713,7 @@ bool stride::make_segments(long long nt, long long fields, std::vector<int>& sta
 // adjoint recomputes L u^m itself).  Costs of one launch per step relative to
 // the plain second-order forward step, measured on MI355X (3D 316^3 / 2D 1104^2)
 // with earlier forms of the 3D kernels and kept, since they fix the path a
-// workspace gets (3D now 1.27, 1.44, 2.08; 2D sweeps kept on the chip, which the
+// workspace gets (3D now 1.22, 1.44, 2.08; 2D sweeps kept on the chip, which the
 // binomial schedule does not have, only widen the margin):
 // second order, forward keeping v 1.18 / 1.04, adjoint imaging from v in
 // pairs 1.48 / 1.30, fused adjoint 2.04 / 1.69; fourth order, forward 2.0
