@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from typing import Optional, Sequence
 
 import numpy as np
@@ -251,10 +252,19 @@ def stride_check_finite(on: bool) -> None:
     _check(lib().stride_check_finite(1 if on else 0))
 
 
+_thread = threading.local()
+
+
 def stride_sweep_wait(polls: int) -> None:
     """Bound, in polls, on the waits of this thread's 2D sweeps kept on the chip
     (< 0: the default; 0: single steps instead of such sweeps)."""
     _check(lib().stride_sweep_wait(int(polls)))
+    _thread.sweep_wait = int(polls)
+
+
+def thread_sweep_wait() -> int:
+    """What this thread has set with stride_sweep_wait (-1: nothing)."""
+    return getattr(_thread, "sweep_wait", -1)
 
 
 def stride_timing_read():

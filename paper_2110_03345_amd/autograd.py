@@ -35,6 +35,8 @@ class StrideWave(torch.autograd.Function):
         ctx.save_for_backward(vp, wavelet)
         ctx.plan = plan
         ctx.ws = ws
+        # backward runs on a thread of torch's: with the forward's choice of sweeps
+        ctx.sweep_wait = _abi.thread_sweep_wait()
         return traces
 
     @staticmethod
@@ -44,8 +46,13 @@ class StrideWave(torch.autograd.Function):
                                "workspace has been consumed (retain_graph is not supported)")
         vp, wavelet = ctx.saved_tensors
         want_wav = bool(ctx.needs_input_grad[1])
-        dvp, dwav = ctx.plan.backward(vp, wavelet, grad_traces.contiguous(), ctx.ws,
-                                      want_dwavelet=want_wav)
+        before = _abi.thread_sweep_wait()
+        _abi.stride_sweep_wait(ctx.sweep_wait)
+        try:
+            dvp, dwav = ctx.plan.backward(vp, wavelet, grad_traces.contiguous(), ctx.ws,
+                                          want_dwavelet=want_wav)
+        finally:
+            _abi.stride_sweep_wait(before)
         ctx.ws = None
         return (dvp if ctx.needs_input_grad[0] else None), dwav, None, None
 

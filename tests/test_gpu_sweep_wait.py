@@ -334,3 +334,28 @@ def test_engine_takes_the_cheaper_of_sweeps_and_ticks(chunk, sweeps):
                 _abi.stride_engine_detach(eng, slot)
     finally:
         _abi.stride_engine_destroy(eng)
+
+
+def test_autograd_backward_keeps_the_forwards_choice():
+    """torch runs backward on a thread of its own, which has made no choice."""
+    from paper_2110_03345_amd.autograd import wave_traces
+    x = Shot()
+    grads = []
+    for polls, want in ((-1, (60, 1)), (0, (60, 60)), (-1, (60, 1))):
+        _abi.stride_sweep_wait(polls)
+        vp = x.vp.clone().requires_grad_()
+        seen = []
+        traces = wave_traces(vp, x.wav, x.plan)
+        # hooks on the backward's thread, before and after it
+        traces.register_hook(lambda g: _abi.stride_timing_enable(True))
+
+        def after(g):
+            seen.append(_abi.stride_timing_read()[4:])
+            _abi.stride_timing_enable(False)
+        vp.register_hook(after)
+        _abi.stride_sweep_wait(-1)
+        (traces * x.data).sum().backward()
+        torch.cuda.synchronize()
+        assert seen == [want], (polls, seen)
+        grads.append(vp.grad)
+    assert torch.equal(grads[0], grads[1]) and torch.equal(grads[0], grads[2])
