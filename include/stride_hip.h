@@ -65,7 +65,7 @@ enum {
     STRIDE_E_CFL = -2,         /* dt * vp_max violates the stability limit of the scheme */
     STRIDE_E_GEOMETRY = -3,    /* a source or receiver lies outside the physical grid */
     STRIDE_E_WORKSPACE = -4,   /* ws_bytes below what the call needs */
-    STRIDE_E_HIP = -5,         /* a HIP runtime call failed */
+    STRIDE_E_HIP = -5,         /* a HIP runtime call failed, or a 2D sweep gave up (stride_sweep_wait) */
     STRIDE_E_NONFINITE = -6    /* NaN or infinity in a solve's outputs (stride_check_finite) */
 };
 
